@@ -28,21 +28,12 @@ namespace flame {
 
 namespace {
 
-// Table entry i of the power-of-two plan of S (the layout of
-// ff::build_twiddles), computed from its definition in double precision.
-template <class S>
+// The twiddles come from their definition (ff::tw_butterfly), a butterfly at a
+// time: one double-precision sine and cosine per butterfly instead of one per
+// twiddle.
 struct ComputedTw {
-  __device__ __forceinline__ float2 operator()(int i) const {
-    int q = 1;
-    while (q + 1 < S::NBF && i >= S::tw_off(q + 1)) ++q;
-    const int ns = S::ns(q), r = S::radix(q);
-    const int rel = i - S::tw_off(q);
-    const int m = rel / ns + 1, k = rel % ns;
-    const long long e = (long long)k * m % (long long)(ns * r);
-    double sn, cs;
-    sincos(-2.0 * M_PI * double(e) / (double(ns) * double(r)), &sn, &cs);
-    return make_float2((float)cs, (float)sn);
-  }
+  static constexpr bool whole = true;
+  __device__ __forceinline__ float2 operator()(int) const { return make_float2(0.f, 0.f); }  // every pass is in registers
 };
 
 template <int LOGN>
@@ -109,7 +100,7 @@ __global__ void __launch_bounds__(CircleCfg<LOGN>::THREADS)
   const int ca = 2 * pair, cb = 2 * pair + 1;
   const bool live_a = ca < d.n_circles, live_b = cb < d.n_circles;
   float2* my = lds + p;
-  const ff::RegTwS<S, ComputedTw<S>, 2> tw(ComputedTw<S>{}, t);
+  const ff::RegTwS<S, ComputedTw, 2> tw(ComputedTw{}, t);
   gf2* const sg = glob(d.S);
   // loads without conditions: a circle past the batch reads circle 0 (never stored)
   const size_t oa = (size_t)(live_a ? ca : 0) * H, ob = (size_t)(live_b ? cb : 0) * H;
@@ -179,7 +170,7 @@ __global__ void __launch_bounds__(CircleCfg<LOGN>::THREADS)
   const int ca = 2 * pair, cb = 2 * pair + 1;
   const bool live_a = ca < d.n_circles, live_b = cb < d.n_circles;
   float2* my = lds + p;
-  const ff::RegTwS<S, ComputedTw<S>, 2> tw(ComputedTw<S>{}, t);
+  const ff::RegTwS<S, ComputedTw, 2> tw(ComputedTw{}, t);
   gf2* const sg = glob(d.S);
   const size_t oa = (size_t)(live_a ? ca : 0) * H, ob = (size_t)(live_b ? cb : 0) * H;
   float2 sa[4], sb[4];

@@ -1,7 +1,7 @@
 // Persistent ensemble kernel of the flame step (gfx950): the steps of every
 // flame of a plan in one launch whose workgroups are all resident at once (a
 // cooperative launch). Each workgroup runs the bodies of the step kernels
-// (step_bodies.hpp) on the row-pair groups and column tiles of its
+// (mixed_bodies.hpp) on the row-pair groups and column tiles of its
 // EnsembleItem, step after step. A flame stepped by one workgroup needs only
 // that workgroup's barriers between its phases; a flame shared by several
 // meets at its arrival counter after each phase, because the column pass of
@@ -13,13 +13,13 @@
 
 #include "flame_dev.hpp"
 #include "flame_kernels.hpp"
-#include "step_bodies.hpp"
+#include "mixed_bodies.hpp"
 
 namespace flame {
 
-static_assert(ColCfg<kEnsMinLog1, 12>::THREADS == kEnsThreads && ColCfg<kEnsMaxLog1, 12>::THREADS == kEnsThreads,
+static_assert(ColMix<kEnsMinLog1>::THREADS == kEnsThreads && ColMix<kEnsMaxLog1>::THREADS == kEnsThreads,
               "column bodies of the ensemble kernel: 256 threads");
-static_assert(RowCfg<kEnsMinLog2, 16>::THREADS == kEnsThreads && RowCfg<kEnsMaxLog2, 16>::THREADS == kEnsThreads,
+static_assert(RowMix<kEnsMinLog2>::THREADS == kEnsThreads && RowMix<kEnsMaxLog2>::THREADS == kEnsThreads,
               "row bodies of the ensemble kernel: 256 threads");
 
 namespace {
@@ -29,7 +29,7 @@ constexpr int ens_col_lds() {
   if constexpr (L > kEnsMaxLog1) {
     return 0;
   } else {
-    return ColCfg<L, 12>::LDS_BYTES > ens_col_lds<L + 1>() ? ColCfg<L, 12>::LDS_BYTES : ens_col_lds<L + 1>();
+    return ColMix<L>::LDS_BYTES > ens_col_lds<L + 1>() ? ColMix<L>::LDS_BYTES : ens_col_lds<L + 1>();
   }
 }
 template <int L>
@@ -37,20 +37,20 @@ constexpr int ens_row_lds() {
   if constexpr (L > kEnsMaxLog2) {
     return 0;
   } else {
-    return RowCfg<L, 16>::LDS_BYTES > ens_row_lds<L + 1>() ? RowCfg<L, 16>::LDS_BYTES : ens_row_lds<L + 1>();
+    return RowMix<L>::LDS_BYTES > ens_row_lds<L + 1>() ? RowMix<L>::LDS_BYTES : ens_row_lds<L + 1>();
   }
 }
 constexpr int kEnsLds = ens_col_lds<kEnsMinLog1>() > ens_row_lds<kEnsMinLog2>() ? ens_col_lds<kEnsMinLog1>()
                                                                                  : ens_row_lds<kEnsMinLog2>();
 
 template <int L>
-__device__ __forceinline__ void ens_row(int logn2, const FlameDev& f, long long n, int group, int tid) {
+__device__ __forceinline__ void ens_row(int logn2, const FlameDev& f, int group, int tid) {
   if constexpr (L <= kEnsMaxLog2) {
     if (logn2 != L) {
-      ens_row<L + 1>(logn2, f, n, group, tid);
+      ens_row<L + 1>(logn2, f, group, tid);
       return;
     }
-    row_body<L, ROW_STEP, 16, false>(f, n, nullptr, nullptr, group, group, tid);
+    rowm_body<L, false>(f, group, tid);
   }
 }
 
@@ -61,7 +61,7 @@ __device__ __forceinline__ void ens_col(int logn1, const FlameDev& f, long long 
       ens_col<L + 1>(logn1, f, n, tile, tid);
       return;
     }
-    col_body<L, COL_STEP, 12, VAR_EULER>(f, n, nullptr, tile, tid);
+    colm_body<L, COL_STEP, VAR_EULER>(f, n, nullptr, tile, tid);
   }
 }
 
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(kEnsThreads) __attribute__((amdgpu_waves_per_e
     const long long n = n0 + s;
     for (int fi = 0; fi < it.nfl; ++fi)
       for (int g = it.part; g < it.rtiles; g += it.parts) {
-        ens_row<kEnsMinLog2>(it.logn2, fls[it.flame + fi], n, g, opaque_tid());
+        ens_row<kEnsMinLog2>(it.logn2, fls[it.flame + fi], g, opaque_tid());
         __syncthreads();  // the next body reuses the LDS; Q is read by this workgroup next
       }
     if (it.parts > 1 && !ens_meet(cnt, (unsigned)(2 * s + 1) * (unsigned)it.parts, err, limit)) return;

@@ -15,11 +15,19 @@
 // inserts spare slots to break the power-of-two bank strides (lds_pad,
 // lds_pad32 and lds_pad32_256 below; a Shape chooses them per exchange).
 //
-// Twiddles come from a table built on the host in double precision and
-// rounded once to float: pass p >= 1 with Ns = 16^p and radix R stores
-// w(k, r) = exp(-2 pi i r k / (Ns R)) at [(r - 1) * Ns + k], 0 < r < R,
-// k < Ns, so that the lanes of a wave (consecutive k) read consecutive
-// addresses for each r.
+// Twiddles come from a table built in double precision and rounded once to
+// float: pass p >= 1 of radix R stores, for the twiddle w(k, r) =
+// exp(-2 pi i r k / (Ns R)) = c_r (1 - i t_r), the pair (t_r, rho_r) at
+// [(r - 1) * Ns + k], 0 < r < R, k < Ns, so that the lanes of a wave
+// (consecutive k) read consecutive addresses for each r. rho_r = c_r / c_q is
+// the cosine relative to that of the input q = tw_parent(R, r) that input r
+// meets first in the butterfly. The kernels are bound by the vector ALU, and
+// in this form a twiddle costs two fused multiply-adds per point instead of
+// four operations: x (1 - i t) needs two, and the cosines ride on the
+// butterfly's additions (a +- rho b), which become fused multiply-adds. The
+// butterflies' own roots take the same form. A radix-16 pass is 180
+// operations per 16 points instead of 220 (144 instead of 160 without
+// twiddles). The last radix-6 pass of Shape6 keeps plain (cos, -sin) twiddles.
 //
 // The pass functions are __host__ __device__ so the same code can be
 // driven thread by thread on the CPU to check the index maps.
@@ -220,20 +228,6 @@ __host__ __device__ __forceinline__ float2 mul_q(float2 a) {
   return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
 }
 
-// multiply by exp(-+ i pi/4) (the eighth root of the transform's direction)
-template <bool INV>
-__host__ __device__ __forceinline__ float2 mul_e1(float2 a) {
-  constexpr float c = 0.70710678118654752440f;
-  return INV ? make_float2(c * (a.x - a.y), c * (a.x + a.y)) : make_float2(c * (a.x + a.y), c * (a.y - a.x));
-}
-
-// multiply by exp(-+ 3 i pi/4)
-template <bool INV>
-__host__ __device__ __forceinline__ float2 mul_e3(float2 a) {
-  constexpr float c = 0.70710678118654752440f;
-  return INV ? make_float2(-c * (a.x + a.y), c * (a.x - a.y)) : make_float2(c * (a.y - a.x), -c * (a.x + a.y));
-}
-
 // multiply by exp(s * i * theta) with (cos, sin) given for the forward sign convention
 template <bool INV>
 __host__ __device__ __forceinline__ float2 mul_root(float2 a, float c, float s) {
@@ -260,66 +254,103 @@ __host__ __device__ __forceinline__ void dft4(float2& x0, float2& x1, float2& x2
   x3 = csub(a1, a3);
 }
 
+// x (1 -+ i t): a root or twiddle exp(-+ i a) without its cosine, t = tan a
+// (forward; the inverse transform takes the conjugate).
 template <bool INV>
-__host__ __device__ __forceinline__ void dft8(float2* x) {
-  float2 e0 = x[0], e1 = x[2], e2 = x[4], e3 = x[6];
-  float2 o0 = x[1], o1 = x[3], o2 = x[5], o3 = x[7];
-  dft4<INV>(e0, e1, e2, e3);
-  dft4<INV>(o0, o1, o2, o3);
-  o1 = mul_e1<INV>(o1);
-  o2 = mul_q<INV>(o2);
-  o3 = mul_e3<INV>(o3);
-  x[0] = cadd(e0, o0);
-  x[4] = csub(e0, o0);
-  x[1] = cadd(e1, o1);
-  x[5] = csub(e1, o1);
-  x[2] = cadd(e2, o2);
-  x[6] = csub(e2, o2);
-  x[3] = cadd(e3, o3);
-  x[7] = csub(e3, o3);
+__host__ __device__ __forceinline__ float2 tmul(float2 x, float t) {
+  return INV ? make_float2(__builtin_fmaf(-t, x.y, x.x), __builtin_fmaf(t, x.x, x.y))
+             : make_float2(__builtin_fmaf(t, x.y, x.x), __builtin_fmaf(-t, x.x, x.y));
 }
 
+// a + s b
+__host__ __device__ __forceinline__ float2 axpy(float2 a, float s, float2 b) {
+  return make_float2(__builtin_fmaf(s, b.x, a.x), __builtin_fmaf(s, b.y, a.y));
+}
+
+// dft4 of (x0, r1 x1, r2 x2, r1 r3 x3): the scales of the inputs ride on the
+// additions. r3 is the scale of x3 relative to x1's.
 template <bool INV>
-__host__ __device__ __forceinline__ void dft16(float2* x) {
-  // r = 4 r1 + r2, m = m1 + 4 m2: length-4 transforms over r1, inner roots, length-4 over r2
-  constexpr float c1 = 0.92387953251128675613f;  // cos(pi/8)
-  constexpr float s1 = 0.38268343236508977173f;  // sin(pi/8)
+__host__ __device__ __forceinline__ void dft4s(float2& x0, float2& x1, float2& x2, float2& x3, float r1, float r2,
+                                               float r3) {
+  const float2 a0 = axpy(x0, r2, x2), a1 = axpy(x0, -r2, x2);
+  const float2 a2 = axpy(x1, r3, x3), a3 = mul_q<INV>(axpy(x1, -r3, x3));
+  x0 = axpy(a0, r1, a2);
+  x2 = axpy(a0, -r1, a2);
+  x1 = axpy(a1, r1, a3);
+  x3 = axpy(a1, -r1, a3);
+}
+
+constexpr float kSqrtHalf = 0.70710678118654752440f;  // cos(pi/4)
+constexpr float kCos8 = 0.92387953251128675613f;      // cos(pi/8)
+constexpr float kSin8 = 0.38268343236508977173f;      // sin(pi/8) = cos(3 pi/8)
+constexpr float kTan8 = 0.41421356237309504880f;      // tan(pi/8) = tan(9 pi/8)
+constexpr float kTan38 = 2.41421356237309504880f;     // tan(3 pi/8)
+
+// Length-8 DFT of inputs that carry scales: x[r] stands for c_r x[r] with
+// rho[r] = c_r / c_parent(r) (tw_parent; rho[0] unused, c_0 = 1).
+template <bool INV>
+__host__ __device__ __forceinline__ void dft8s(float2* x, const float* rho) {
+  float2 e0 = x[0], e1 = x[2], e2 = x[4], e3 = x[6];
+  float2 o0 = x[1], o1 = x[3], o2 = x[5], o3 = x[7];
+  dft4s<INV>(e0, e1, e2, e3, rho[2], rho[4], rho[6]);
+  dft4s<INV>(o0, o1, o2, o3, rho[3], rho[5], rho[7]);
+  const float r1 = rho[1], r1h = kSqrtHalf * rho[1];
+  o1 = tmul<INV>(o1, 1.f);   // w8 without cos(pi/4)
+  o2 = mul_q<INV>(o2);
+  o3 = tmul<INV>(o3, -1.f);  // w8^3 without -cos(pi/4)
+  x[0] = axpy(e0, r1, o0);
+  x[4] = axpy(e0, -r1, o0);
+  x[1] = axpy(e1, r1h, o1);
+  x[5] = axpy(e1, -r1h, o1);
+  x[2] = axpy(e2, r1, o2);
+  x[6] = axpy(e2, -r1, o2);
+  x[3] = axpy(e3, -r1h, o3);
+  x[7] = axpy(e3, r1h, o3);
+}
+
+// Second half of the length-16 DFT: y[4 r2 + m1] holds the length-4
+// transforms over r1 (r = 4 r1 + r2, m = m1 + 4 m2), scaled by c_{r2}; the
+// inner roots w16^(r2 m1), then the length-4 transforms over r2.
+template <bool INV>
+__host__ __device__ __forceinline__ void dft16_tail(float2* x, float2* y, float r1, float r2, float r3) {
+  dft4s<INV>(y[0], y[4], y[8], y[12], r1, r2, r3);
+  y[5] = tmul<INV>(y[5], kTan8);     // w^1, cos(pi/8)
+  y[9] = tmul<INV>(y[9], 1.f);       // w^2, cos(pi/4)
+  y[13] = tmul<INV>(y[13], kTan38);  // w^3, cos(3 pi/8)
+  dft4s<INV>(y[1], y[5], y[9], y[13], kCos8 * r1, kSqrtHalf * r2, (kSin8 / kCos8) * r3);
+  y[6] = tmul<INV>(y[6], 1.f);     // w^2
+  y[10] = mul_q<INV>(y[10]);       // w^4
+  y[14] = tmul<INV>(y[14], -1.f);  // w^6, -cos(pi/4)
+  dft4s<INV>(y[2], y[6], y[10], y[14], kSqrtHalf * r1, r2, -r3);
+  y[7] = tmul<INV>(y[7], kTan38);  // w^3
+  y[11] = tmul<INV>(y[11], -1.f);  // w^6
+  y[15] = tmul<INV>(y[15], kTan8);  // w^9, -cos(pi/8)
+  dft4s<INV>(y[3], y[7], y[11], y[15], kSin8 * r1, -kSqrtHalf * r2, -(kCos8 / kSin8) * r3);
+#pragma unroll
+  for (int m1 = 0; m1 < 4; ++m1)
+#pragma unroll
+    for (int m2 = 0; m2 < 4; ++m2) x[m1 + 4 * m2] = y[4 * m2 + m1];
+}
+
+// Length-16 DFT of inputs that carry scales, as dft8s.
+template <bool INV>
+__host__ __device__ __forceinline__ void dft16s(float2* x, const float* rho) {
   float2 y[16];
 #pragma unroll
   for (int r2 = 0; r2 < 4; ++r2) {
     float2 a = x[r2], b = x[r2 + 4], c = x[r2 + 8], d = x[r2 + 12];
-    dft4<INV>(a, b, c, d);
+    dft4s<INV>(a, b, c, d, rho[r2 + 4], rho[r2 + 8], rho[r2 + 12]);
     y[4 * r2 + 0] = a;
     y[4 * r2 + 1] = b;
     y[4 * r2 + 2] = c;
     y[4 * r2 + 3] = d;
   }
-  // y[4 r2 + m1] *= w16^(r2 m1)
-  y[5] = mul_root<INV>(y[5], c1, s1);    // w^1
-  y[6] = mul_e1<INV>(y[6]);              // w^2
-  y[7] = mul_root<INV>(y[7], s1, c1);    // w^3: cos(3pi/8) = sin(pi/8)
-  y[9] = mul_e1<INV>(y[9]);              // w^2
-  y[10] = mul_q<INV>(y[10]);             // w^4
-  y[11] = mul_e3<INV>(y[11]);            // w^6
-  y[13] = mul_root<INV>(y[13], s1, c1);  // w^3
-  y[14] = mul_e3<INV>(y[14]);            // w^6
-  y[15] = mul_root<INV>(y[15], -c1, -s1);  // w^9: cos(9pi/8) = -cos(pi/8), sin(9pi/8) = -sin(pi/8)
-#pragma unroll
-  for (int m1 = 0; m1 < 4; ++m1) {
-    float2 a = y[m1], b = y[4 + m1], c = y[8 + m1], d = y[12 + m1];
-    dft4<INV>(a, b, c, d);
-    x[m1] = a;
-    x[m1 + 4] = b;
-    x[m1 + 8] = c;
-    x[m1 + 12] = d;
-  }
+  dft16_tail<INV>(x, y, rho[1], rho[2], rho[3]);
 }
 
 // dft16 for inputs x[4..11] == 0 (only the first and last quarter set).
 template <bool INV>
 __host__ __device__ __forceinline__ void dft16_outer(float2* x) {
-  constexpr float c1 = 0.92387953251128675613f;
-  constexpr float s1 = 0.38268343236508977173f;
   float2 y[16];
 #pragma unroll
   for (int r2 = 0; r2 < 4; ++r2) {
@@ -330,24 +361,7 @@ __host__ __device__ __forceinline__ void dft16_outer(float2* x) {
     y[4 * r2 + 2] = csub(a, d);
     y[4 * r2 + 3] = cadd(a, qd);
   }
-  y[5] = mul_root<INV>(y[5], c1, s1);
-  y[6] = mul_e1<INV>(y[6]);
-  y[7] = mul_root<INV>(y[7], s1, c1);
-  y[9] = mul_e1<INV>(y[9]);
-  y[10] = mul_q<INV>(y[10]);
-  y[11] = mul_e3<INV>(y[11]);
-  y[13] = mul_root<INV>(y[13], s1, c1);
-  y[14] = mul_e3<INV>(y[14]);
-  y[15] = mul_root<INV>(y[15], -c1, -s1);
-#pragma unroll
-  for (int m1 = 0; m1 < 4; ++m1) {
-    float2 a = y[m1], b = y[4 + m1], c = y[8 + m1], d = y[12 + m1];
-    dft4<INV>(a, b, c, d);
-    x[m1] = a;
-    x[m1 + 4] = b;
-    x[m1 + 8] = c;
-    x[m1 + 12] = d;
-  }
+  dft16_tail<INV>(x, y, 1.f, 1.f, 1.f);
 }
 
 // dft8 for inputs x[2..5] == 0.
@@ -357,17 +371,17 @@ __host__ __device__ __forceinline__ void dft8_outer(float2* x) {
   const float2 qe = mul_q<INV>(x[6]), qo = mul_q<INV>(x[7]);
   const float2 e0 = cadd(x[0], x[6]), e1 = csub(x[0], qe), e2 = csub(x[0], x[6]), e3 = cadd(x[0], qe);
   float2 o0 = cadd(x[1], x[7]), o1 = csub(x[1], qo), o2 = csub(x[1], x[7]), o3 = cadd(x[1], qo);
-  o1 = mul_e1<INV>(o1);
+  o1 = tmul<INV>(o1, 1.f);
   o2 = mul_q<INV>(o2);
-  o3 = mul_e3<INV>(o3);
+  o3 = tmul<INV>(o3, -1.f);
   x[0] = cadd(e0, o0);
   x[4] = csub(e0, o0);
-  x[1] = cadd(e1, o1);
-  x[5] = csub(e1, o1);
+  x[1] = axpy(e1, kSqrtHalf, o1);
+  x[5] = axpy(e1, -kSqrtHalf, o1);
   x[2] = cadd(e2, o2);
   x[6] = csub(e2, o2);
-  x[3] = cadd(e3, o3);
-  x[7] = csub(e3, o3);
+  x[3] = axpy(e3, -kSqrtHalf, o3);
+  x[7] = axpy(e3, kSqrtHalf, o3);
 }
 
 // length-3 DFT: w3 = exp(-+ 2 pi i / 3) = -1/2 -+ i sqrt(3)/2
@@ -406,14 +420,28 @@ __host__ __device__ __forceinline__ void dft6(float2* x) {
   x[5] = b2;
 }
 
+// dft3 of (y, s1 q, s1 r3 r): r3 is the scale of r relative to q's.
+template <bool INV>
+__host__ __device__ __forceinline__ void dft3s(float2& y, float2& q, float2& r, float s1, float r3) {
+  constexpr float h = 0.86602540378443864676f;  // sqrt(3)/2
+  const float2 s = axpy(q, r3, r), d = axpy(q, -r3, r);
+  const float2 m = axpy(y, -0.5f * s1, s);
+  const float hs = INV ? -h * s1 : h * s1;  // forward: X1 = m - i h d, X2 = m + i h d
+  y = axpy(y, s1, s);
+  q = make_float2(__builtin_fmaf(hs, d.y, m.x), __builtin_fmaf(-hs, d.x, m.y));
+  r = make_float2(__builtin_fmaf(-hs, d.y, m.x), __builtin_fmaf(hs, d.x, m.y));
+}
+
 // length-12 DFT as 4 x 3: r = 3 a + b, m = c + 4 d. Length-4 transforms over
 // a for each b, the inner roots w12^(b c), then length-3 transforms over b:
 // X[c + 4 d] = sum_b w3^(b d) w12^(b c) sum_a x[3 a + b] w4^(a c).
-// ZMID: the caller guarantees x[4..7] == 0 (a spectrum kept in the first and
-// last third), which drops the terms that vanish.
+// x[r] carries the scale c_r, as in dft8s. ZMID: the caller guarantees
+// x[4..7] == 0 (a spectrum kept in the first and last third) and no scales,
+// which drops the terms that vanish.
 template <bool INV, bool ZMID = false>
-__host__ __device__ __forceinline__ void dft12(float2* x) {
+__host__ __device__ __forceinline__ void dft12s(float2* x, const float* rho) {
   constexpr float h = 0.86602540378443864676f;  // sqrt(3)/2 = cos(pi/6)
+  constexpr float t30 = 0.57735026918962576451f, t60 = 1.73205080756887729353f;
   float2 y[3][4];
 #pragma unroll
   for (int b = 0; b < 3; ++b) {
@@ -440,44 +468,99 @@ __host__ __device__ __forceinline__ void dft12(float2* x) {
         y[b][3] = cadd(d02, qa3);
       }
     } else {
-      dft4<INV>(a0, a1, a2, a3);
+      dft4s<INV>(a0, a1, a2, a3, rho[b + 3], rho[b + 6], rho[b + 9]);
       y[b][0] = a0;
       y[b][1] = a1;
       y[b][2] = a2;
       y[b][3] = a3;
     }
   }
-  // inner roots: w12^1 = (h, -+1/2), w12^2 = (1/2, -+h), w12^3 = -+i, w12^4 = (-1/2, -+h), w12^6 = -1
-  y[1][1] = mul_root<INV>(y[1][1], h, 0.5f);
-  y[1][2] = mul_root<INV>(y[1][2], 0.5f, h);
-  y[1][3] = mul_q<INV>(y[1][3]);
-  y[2][1] = mul_root<INV>(y[2][1], 0.5f, h);
-  y[2][2] = mul_root<INV>(y[2][2], -0.5f, h);
-  y[2][3] = make_float2(-y[2][3].x, -y[2][3].y);
+  const float r1 = ZMID ? 1.f : rho[1], r2 = ZMID ? 1.f : rho[2];
+  dft3s<INV>(y[0][0], y[1][0], y[2][0], r1, r2);
+  y[1][1] = tmul<INV>(y[1][1], t30);   // w12, cos h
+  y[2][1] = tmul<INV>(y[2][1], t60);   // w12^2, cos 1/2
+  dft3s<INV>(y[0][1], y[1][1], y[2][1], h * r1, (0.5f / h) * r2);
+  y[1][2] = tmul<INV>(y[1][2], t60);   // w12^2
+  y[2][2] = tmul<INV>(y[2][2], -t60);  // w12^4, cos -1/2
+  dft3s<INV>(y[0][2], y[1][2], y[2][2], 0.5f * r1, -r2);
+  y[1][3] = mul_q<INV>(y[1][3]);       // w12^3; y[2][3] takes w12^6 = -1
+  dft3s<INV>(y[0][3], y[1][3], y[2][3], r1, -r2);
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    float2 p = y[0][c], q = y[1][c], r = y[2][c];
-    dft3<INV>(p, q, r);
-    x[c] = p;
-    x[c + 4] = q;
-    x[c + 8] = r;
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[c + 4 * d] = y[d][c];
+}
+
+// Length-R DFT of inputs that carry scales (dft8s); rho[0] is not read.
+template <int R, bool INV>
+__host__ __device__ __forceinline__ void dfts(float2* x, const float* rho) {
+  if constexpr (R == 2) {
+    const float2 a = x[0];
+    x[0] = axpy(a, rho[1], x[1]);
+    x[1] = axpy(a, -rho[1], x[1]);
+  } else if constexpr (R == 4) {
+    dft4s<INV>(x[0], x[1], x[2], x[3], rho[1], rho[2], rho[3]);
+  } else if constexpr (R == 8) {
+    dft8s<INV>(x, rho);
+  } else if constexpr (R == 12) {
+    dft12s<INV>(x, rho);
+  } else {
+    static_assert(R == 16, "radix");
+    dft16s<INV>(x, rho);
   }
 }
 
-template <int R, bool INV>
-__host__ __device__ __forceinline__ void dft(float2* x) {
-  if constexpr (R == 2) {
-    dft2<INV>(x[0], x[1]);
-  } else if constexpr (R == 4) {
-    dft4<INV>(x[0], x[1], x[2], x[3]);
-  } else if constexpr (R == 8) {
-    dft8<INV>(x);
-  } else if constexpr (R == 12) {
-    dft12<INV>(x);
-  } else {
-    static_assert(R == 16, "radix");
-    dft16<INV>(x);
+// The input whose scale that of input r is stored relative to: the one it
+// meets first in dft4s, dft8s, dft16s (r without its highest bit) or dft12s.
+__host__ __device__ constexpr int tw_parent(int radix, int r) {
+  if (radix == 12) return r >= 6 ? r - 6 : (r >= 3 ? r - 3 : r - 1);
+  int h = 1;
+  while (2 * h <= r) h *= 2;
+  return r - h;
+}
+
+// Twiddles of one butterfly, r = 1 .. radix - 1: w(r) = (t_r, rho_r) of
+// exp(-2 pi i r k / (ns radix)), stored through `put(r, entry)`. The powers of
+// one root by multiplication in double, so one sine and cosine per butterfly.
+// A quarter turn has no cosine: it takes 2^-28 instead, which is an error of
+// 4e-9 in the twiddle. Each rho and t is formed with the cosines as rounded
+// so far, so that every product c_r and c_r t_r is rounded once. Every
+// operation is written out (no contraction left to the compiler), so that the
+// tables built on the host and on the device agree.
+template <int R, class PUT>
+__host__ __device__ __forceinline__ void tw_butterfly(int ns, int k, const PUT& put) {
+  const double ang = 2.0 * M_PI * (double)k / ((double)ns * R);
+  const double c1 = cos(ang), s1 = sin(ang);
+  double inv[R], have[R];
+  have[0] = inv[0] = 1.0;
+  double c = 1.0, s = 0.0;
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    const double cn = __builtin_fma(c, c1, -(s * s1));
+    s = __builtin_fma(s, c1, c * s1);
+    c = cn;
+    const double cc = fabs(c) < 0x1p-28 ? (c < 0.0 ? -0x1p-28 : 0x1p-28) : c;
+    const int q = tw_parent(R, r);
+    const float rho = (float)(cc * inv[q]);
+    have[r] = (double)rho * have[q];
+    inv[r] = 1.0 / have[r];
+    put(r, make_float2((float)(s * inv[r]), rho));
   }
+}
+template <class PUT>
+__host__ __device__ inline void tw_butterfly(int radix, int ns, int k, const PUT& put) {
+  switch (radix) {
+    case 2: return tw_butterfly<2>(ns, k, put);
+    case 4: return tw_butterfly<4>(ns, k, put);
+    case 8: return tw_butterfly<8>(ns, k, put);
+    case 12: return tw_butterfly<12>(ns, k, put);
+    default: return tw_butterfly<16>(ns, k, put);
+  }
+}
+// The table of one pass: entry r of butterfly k at out[(r - 1) ns + k].
+inline void build_twiddle_pass(int ns, int radix, float2* out) {
+  for (int k = 0; k < ns; ++k)
+    tw_butterfly(radix, ns, k, [=](int r, float2 w) { out[(r - 1) * ns + k] = w; });
 }
 
 // ------------------------------------------------------------ Stockham passes
@@ -510,6 +593,17 @@ constexpr int six_twiddles() {
     return 0;
   }
 }
+
+// A fetch type whose member `whole` is true computes all entries of a
+// butterfly at once (tw_butterfly) instead of returning one at an index.
+template <class F, class = void>
+struct WholeButterfly {
+  static constexpr bool value = false;
+};
+template <class F>
+struct WholeButterfly<F, decltype((void)F::whole)> {
+  static constexpr bool value = F::whole;
+};
 
 // Twiddle source holding in registers the twiddles thread t needs in the
 // passes with Ns >= MIN_NS (others are read from the table at each use; a pass
@@ -553,8 +647,12 @@ struct RegTwS {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
           const int k = mod_ns<NS>(t + b * S::G);
+          if constexpr (WholeButterfly<F>::value) {
+            tw_butterfly<R>(NS, k, [&](int r, float2 e) { w[offset(P) + b * (R - 1) + r - 1] = e; });
+          } else {
 #pragma unroll
-          for (int r = 1; r < R; ++r) w[offset(P) + b * (R - 1) + (r - 1)] = fetch(S::tw_off(P) + (r - 1) * NS + k);
+            for (int r = 1; r < R; ++r) w[offset(P) + b * (R - 1) + (r - 1)] = fetch(S::tw_off(P) + (r - 1) * NS + k);
+          }
         }
       }
       load_pass<P + 1>();
@@ -582,7 +680,7 @@ struct FftS {
 
   // Pass P < S::NBF: thread t runs PTS/R butterflies on its registers.
   // Butterfly b has global index j = t + b*G and inputs x[j + r*N/R] =
-  // v[b + r*PTS/R]; it applies the twiddles w(j mod Ns, r), the radix-R DFT,
+  // v[b + r*PTS/R]; it applies the twiddles w(j mod Ns, r) (tmul and the scales), the radix-R DFT,
   // and sends output r to position (j / Ns) * Ns * R + (j mod Ns) + r * Ns:
   // into LDS, or, in the last pass (Ns * R = N), back into the same registers.
   // OUTER: the caller guarantees v[PTS/4 .. 3PTS/4 - 1] == 0 on entry to
@@ -601,22 +699,25 @@ struct FftS {
       for (int r = 0; r < R; ++r) x[r] = v[b + r * NB];
       const int j = t + b * S::G;
       const int k = mod_ns<NS>(j);
-      if constexpr (P > 0) {
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          float2 wr = tw.template get<P>(b, r);
-          if (INV) wr.y = -wr.y;
-          x[r] = cmul(x[r], wr);
-        }
-      }
       if constexpr (OUTER && P == 0 && R == 16 && PTS == 16) {
         dft16_outer<INV>(x);
       } else if constexpr (OUTER && P == 0 && R == 8 && PTS == 8) {
         dft8_outer<INV>(x);
       } else if constexpr (OUTER && P == 0 && R == 12 && PTS == 12) {
-        dft12<INV, true>(x);
+        dft12s<INV, true>(x, nullptr);
       } else {
-        dft<R, INV>(x);
+        float rho[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) rho[r] = 1.f;
+        if constexpr (P > 0) {
+#pragma unroll
+          for (int r = 1; r < R; ++r) {
+            const float2 w = tw.template get<P>(b, r);
+            x[r] = tmul<INV>(x[r], w.x);
+            rho[r] = w.y;
+          }
+        }
+        dfts<R, INV>(x, rho);
       }
       if constexpr (LAST) {
 #pragma unroll
@@ -678,37 +779,15 @@ using Fft = FftS<Shape<LOGN, PTS>, INV>;
 
 // Host: fill the twiddle table of a pass plan (tw_size entries).
 inline void build_twiddles_plan(const PassPlan& p, float2* out) {
-  for (int q = 1; q < p.npass; ++q) {
-    const int ns = p.ns[q], r = p.radix[q];
-    const double span = double(ns) * double(r);
-    for (int m = 1; m < r; ++m)
-      for (int k = 0; k < ns; ++k) {
-        const long long e = (long long)k * m % (long long)(ns * r);
-        const double ang = -2.0 * M_PI * double(e) / span;
-        out[p.tw_off[q] + (m - 1) * ns + k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
-      }
-  }
+  for (int q = 1; q < p.npass; ++q) build_twiddle_pass(p.ns[q], p.radix[q], out + p.tw_off[q]);
 }
 
 // Host: fill the twiddle table of a length 2^logn transform with pts points
 // per thread (tw_size entries of that pass plan).
-inline void build_twiddles(int logn, float2* out, int pts = kPts) {
-  const PassPlan p = make_pass_plan(logn, pts);
-  for (int q = 1; q < p.npass; ++q) {
-    const int ns = p.ns[q], r = p.radix[q];
-    const double span = double(ns) * double(r);
-    for (int m = 1; m < r; ++m)
-      for (int k = 0; k < ns; ++k) {
-        // reduce m*k modulo span exactly in integers before the angle
-        const long long e = (long long)k * m % (long long)(ns * r);
-        const double ang = -2.0 * M_PI * double(e) / span;
-        out[p.tw_off[q] + (m - 1) * ns + k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
-      }
-  }
-}
+inline void build_twiddles(int logn, float2* out, int pts = kPts) { build_twiddles_plan(make_pass_plan(logn, pts), out); }
 
 // Host: the twiddle table of a length 6*2^logp transform (Shape6 layout): the
-// power-of-two passes' table, then exp(-2 pi i r k / N) at TW6 + (r-1)*N6 + k.
+// power-of-two passes' table, then plain exp(-2 pi i r k / N) at TW6 + (r-1)*N6 + k.
 inline void build_twiddles6(int logp, float2* out, int pts = kPts) {
   build_twiddles(logp, out, pts);
   const PassPlan p = make_pass_plan(logp, pts);

@@ -16,6 +16,7 @@
 #include "flame.h"
 #include "flame_dev.hpp"
 #include "flame_kernels.hpp"
+#include "mixed_fft.hpp"
 
 namespace {
 
@@ -103,7 +104,7 @@ struct Layout {
   size_t off_tw8[flame::kMaxLog + 1];  // twiddles, 8 points per thread
   size_t off_tw6[flame::kMaxLog + 1];  // twiddles of the length-3N1/4 transform (product grid)
   size_t off_tw6_8[flame::kMaxLog + 1];
-  size_t off_tw12[flame::kMaxLog + 1];  // length 3*2^l/4 in the 12-point plan (product grids)
+  size_t off_twm[flame::kMaxLog + 1];  // length 3*2^l/4 (product grids)
   size_t off_dev;
   size_t off_dev_full;  // device flame table whose W is the adjoint scratch (physical-grid W for diagnostics)
   size_t off_counter;  // step index read by graph replays
@@ -116,14 +117,14 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
   if (!descs || nfl <= 0) return fail(FLAME_ERR_INVALID_ARG, "need at least one flame descriptor");
   L->sizes.resize(nfl);
   size_t off = 0;
-  bool need_tw[flame::kMaxLog + 1] = {}, need_tw6[flame::kMaxLog + 1] = {}, need_tw12[flame::kMaxLog + 1] = {};
+  bool need_tw[flame::kMaxLog + 1] = {}, need_tw6[flame::kMaxLog + 1] = {}, need_twm[flame::kMaxLog + 1] = {};
   for (int f = 0; f < nfl; ++f) {
     int rc = check_desc(&descs[f], &L->sizes[f]);
     if (rc) return rc;
     need_tw[L->sizes[f].logn1] = need_tw[L->sizes[f].logn2] = true;
     need_tw6[L->sizes[f].logn1] = L->sizes[f].logn1 >= flame::kMinLogProduct;
-    if (L->sizes[f].logn1 >= flame::kMinLogProduct) need_tw12[L->sizes[f].logn1] = true;
-    if (L->sizes[f].logn2 >= flame::kMinLogRow12) need_tw12[L->sizes[f].logn2] = true;
+    if (L->sizes[f].logn1 >= flame::kMinLogProduct) need_twm[L->sizes[f].logn1] = true;
+    if (L->sizes[f].logn2 >= flame::kMinLogRowProduct) need_twm[L->sizes[f].logn2] = true;
   }
   for (int f = 0; f < nfl; ++f) {
     const Sizes& s = L->sizes[f];
@@ -153,8 +154,8 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
     if (need_tw6[l]) off = align_up(off + (size_t)ff::twiddles6_size(l - 3, 16) * sizeof(float2));
     L->off_tw6_8[l] = off;
     if (need_tw6[l]) off = align_up(off + (size_t)ff::twiddles6_size(l - 3, 8) * sizeof(float2));
-    L->off_tw12[l] = off;
-    if (need_tw12[l]) off = align_up(off + (size_t)std::max(1, ff::make_plan12(l - 4).tw_size) * sizeof(float2));
+    L->off_twm[l] = off;
+    if (need_twm[l]) off = align_up(off + (size_t)ff::mix_tables_size(l) * sizeof(float2));
   }
   L->off_dev = off;
   off = align_up(off + (size_t)nfl * sizeof(flame::FlameDev));
@@ -191,9 +192,20 @@ struct Group {
   bool nt_q() const { return nt == 1 || nt == 3; }  // the row kernel's stores of Q
   bool nt_w() const { return nt == 1 || nt == 2; }  // the column kernel's stores of Wp and Wm
   int rows() const { return product ? 3 * (1 << logn1) / 4 : (1 << logn1); }
-  // phi points of the quadratic term's grid: the 12-point row kernel forms it on 3 N2/4
-  int cols() const { return row_pts == 12 ? 3 * (1 << logn2) / 4 : (1 << logn2); }
+  // phi points of the quadratic term's grid: 3 N2/4 where the row kernel has that length
+  int cols() const { return logn2 >= flame::kMinLogRowProduct ? 3 * (1 << logn2) / 4 : (1 << logn2); }
   int rgroups() const { return (rows() / 2 + rpairs - 1) / rpairs; }
+  // Points per thread that the kernels are asked for: on a product grid 8
+  // selects the bodies for few transforms, 12 the others, and 16 (the default)
+  // whichever pays for `flames` flames in one launch (flame::split_pays).
+  int col_kernel_pts(int flames) const {
+    if (!product || col_pts != ff::kPts) return col_pts;
+    return flame::split_pays(logn1, (long long)flames << (logn2 - 2), true) ? 8 : ff::kPts;
+  }
+  int row_kernel_pts(int flames) const {
+    if (logn2 < flame::kMinLogRowProduct || row_pts != ff::kPts) return row_pts;
+    return flame::split_pays(logn2, (long long)flames * rows() / 2, false) ? 8 : ff::kPts;
+  }
 };
 
 class DeviceGuard {
@@ -225,7 +237,7 @@ struct flame_plan_s {
   std::vector<std::vector<float2>> tw_host8;  // 8 points per thread
   std::vector<std::vector<float2>> tw_host6;  // length-3N1/4 transforms (16 and 8 points per thread)
   std::vector<std::vector<float2>> tw_host6_8;
-  std::vector<std::vector<float2>> tw_host12;  // length 3*2^l/4, 12 points per thread
+  std::vector<std::vector<float2>> tw_hostm;  // length 3*2^l/4
   flame::FlameDev* ddev = nullptr;
   flame::FlameDev* ddev_full = nullptr;       // same flames, W in the adjoint scratch
   std::vector<flame::FlameDev> hdev_full;
@@ -367,7 +379,7 @@ int rebuild_w(flame_plan p, int flame) {
     Timed tm(p, KIND_OTHER);
     if (p->groups[p->group_of[flame]].product)
       flame::launch_colp(s.logn1, flame::COL_FIRST, s.tiles, 1, p->stream, p->ddev + flame, p->n, nullptr,
-                         p->groups[p->group_of[flame]].col_pts);
+                         p->groups[p->group_of[flame]].col_kernel_pts(1));
     else
       flame::launch_col(s.logn1, flame::COL_FIRST, s.tiles, 1, p->stream, p->ddev + flame, p->n);
   }
@@ -396,14 +408,14 @@ int apply_rows(flame_plan p, int gi) {
 void launch_step_row(flame_plan p, const Group& gr, long long n, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr,
                      hipStream_t st = nullptr) {
   flame::launch_row(gr.logn2, flame::ROW_STEP, gr.rgroups(), gr.count, st ? st : p->stream, p->ddev + gr.first, n,
-                    nullptr, nullptr, gr.row_pts, e0, e1, gr.nt_q());
+                    nullptr, nullptr, gr.row_kernel_pts(gr.count), e0, e1, gr.nt_q());
 }
 
 void launch_step_col(flame_plan p, const Group& gr, long long n, int pass, hipEvent_t e0 = nullptr,
                      hipEvent_t e1 = nullptr, hipStream_t st = nullptr) {
   if (gr.product)
     flame::launch_colp(gr.logn1, flame::COL_STEP, gr.tiles, gr.count, st ? st : p->stream, p->ddev + gr.first, n,
-                       nullptr, gr.col_pts, e0, e1, gr.col_var(pass));
+                       nullptr, gr.col_kernel_pts(gr.count), e0, e1, gr.col_var(pass));
   else
     flame::launch_col(gr.logn1, flame::COL_STEP, gr.tiles, gr.count, st ? st : p->stream, p->ddev + gr.first, n,
                       nullptr, gr.col_pts, e0, e1, gr.col_var(pass));
@@ -443,9 +455,10 @@ int build_graph(flame_plan p) {
   // one pass of group gi at step offset s: row node, then column node, chained after the group's last node
   auto add_pass = [&](size_t gi, int s, int pass) -> int {
     const Group& gr = p->groups[gi];
-    const flame::KernelLaunch rk = flame::row_step_kernel(gr.logn2, gr.row_pts, gr.nt_q());
+    const flame::KernelLaunch rk = flame::row_step_kernel(gr.logn2, gr.row_kernel_pts(gr.count), gr.nt_q());
     const flame::KernelLaunch ck =
-        gr.product ? flame::colp_kernel_info(gr.logn1, flame::COL_STEP, gr.col_pts, gr.col_var(pass))
+        gr.product ? flame::colp_kernel_info(gr.logn1, flame::COL_STEP, gr.col_kernel_pts(gr.count),
+                                                gr.col_var(pass))
                    : flame::col_step_kernel(gr.logn1, gr.col_pts, gr.col_var(pass));
     if (!rk.func || !ck.func) return fail(FLAME_ERR_UNSUPPORTED_SIZE, "no step kernel for this grid");
     const flame::FlameDev* fl = p->ddev + gr.first;
@@ -458,7 +471,7 @@ int build_graph(flame_plan p) {
     void* cargs[] = {&fl, &n, &nb, &src};
     hipKernelNodeParams rp{};
     rp.func = const_cast<void*>(rk.func);
-    rp.gridDim = dim3(gr.rgroups(), gr.count);
+    rp.gridDim = dim3(gr.rgroups() * rk.mult, gr.count);
     rp.blockDim = dim3(rk.threads);
     rp.sharedMemBytes = rk.lds;
     rp.kernelParams = rargs;
@@ -467,7 +480,7 @@ int build_graph(flame_plan p) {
     if (e != hipSuccess) return hip_fail(e, "hipGraphAddKernelNode (row)");
     hipKernelNodeParams cp{};
     cp.func = const_cast<void*>(ck.func);
-    cp.gridDim = dim3(gr.tiles, gr.count);
+    cp.gridDim = dim3(gr.tiles * ck.mult, gr.count);
     cp.blockDim = dim3(ck.threads);
     cp.sharedMemBytes = ck.lds;
     cp.kernelParams = cargs;
@@ -523,11 +536,11 @@ int scratch_address(int dev, void** out) {
   return FLAME_OK;
 }
 
-// One twiddle table: passes q = 1 .. npass-1 of a Stockham plan hold
-// exp(-2 pi i r k / (ns_q R_q)) at off_q + (r - 1) ns_q + k, 0 < r < R_q,
-// k < ns_q (the layout of ff::build_twiddles and, with the radix-6 pass as
-// its last pass, of ff::build_twiddles6). Built on the device in double
-// precision and rounded once, like the host tables of flame_init.
+// One twiddle table: passes q = 1 .. npass-1 of a Stockham plan hold entry r
+// of butterfly k (ff::tw_butterfly) at off_q + (r - 1) ns_q + k, 0 < r < R_q,
+// k < ns_q (the layout of ff::build_twiddles and ff::build_mix_tables). Built
+// on the device in double precision and rounded once, like the host tables of
+// flame_init.
 struct TwSpec {
   float2* out;
   int npass;
@@ -544,15 +557,11 @@ __global__ void noalloc_setup_kernel(flame::FlameDev fd, flame::FlameDev* dst, T
   if (blockIdx.x == 0 && threadIdx.x == 0) *dst = fd;
   for (int ti = 0; ti < specs.ntab; ++ti) {
     const TwSpec& s = specs.t[ti];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < s.count; i += gridDim.x * blockDim.x) {
-      int q = 1;
-      while (q + 1 < s.npass && i >= s.off[q + 1]) ++q;
-      const int rel = i - s.off[q];
-      const int ns = s.ns[q], r = s.radix[q];
-      const int m = rel / ns + 1, k = rel % ns;
-      const long long e = (long long)k * m % (long long)(ns * r);
-      const double ang = -2.0 * M_PI * double(e) / (double(ns) * double(r));
-      s.out[i] = make_float2((float)cos(ang), (float)sin(ang));
+    for (int q = 1; q < s.npass; ++q) {
+      const int ns = s.ns[q];
+      float2* const out = s.out + s.off[q];
+      for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < ns; k += gridDim.x * blockDim.x)
+        ff::tw_butterfly(s.radix[q], ns, k, [=](int r, float2 w) { out[(r - 1) * ns + k] = w; });
     }
   }
 }
@@ -571,15 +580,18 @@ TwSpec tw_spec_pow2(float2* out, int logn, int pts) {
   return s;
 }
 
-// Shape6 of length 6 * 2^logp: the power-of-two passes, then the radix-6 pass.
-TwSpec tw_spec_six(float2* out, int logp, int pts) {
-  TwSpec s = tw_spec_pow2(out, logp, pts);
-  const int q = s.npass;
-  s.ns[q] = 1 << logp;
-  s.radix[q] = 6;
-  s.off[q] = s.count;
-  s.npass = q + 1;
-  s.count += 5 * (1 << logp);
+// One direction's plan of length 3 * 2^logn / 4 (ff::MixPlan).
+TwSpec tw_spec_mixed(float2* out, int logn, bool forward) {
+  const ff::MixPassList l = ff::mix_passes(logn, forward);
+  TwSpec s{};
+  s.out = out;
+  s.npass = l.npass;
+  for (int q = 0; q < l.npass; ++q) {
+    s.ns[q] = l.ns[q];
+    s.radix[q] = l.radix[q];
+    s.off[q] = l.off[q];
+  }
+  s.count = l.size;
   return s;
 }
 
@@ -683,15 +695,24 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   TwSpecs specs{};
   size_t off = align_up(sizeof(flame::FlameDev));
   size_t tw_off[kMaxTwTables] = {};
-  auto add_table = [&](const TwSpec& t) {
+  auto add_table = [&](const TwSpec& t, bool last) {
     tw_off[specs.ntab] = off;
     specs.t[specs.ntab++] = t;
-    off = align_up(off + (size_t)std::max(t.count, 1) * sizeof(float2));
+    off += (size_t)std::max(t.count, 1) * sizeof(float2);
+    if (last) off = align_up(off);
+  };
+  auto add_mixed = [&](int logn) {  // ff::build_mix_tables: the inverse plan's table, then the forward plan's
+    add_table(tw_spec_mixed(nullptr, logn, false), false);
+    add_table(tw_spec_mixed(nullptr, logn, true), true);
   };
   // pointers are filled in once the scratch address is known
-  if (product) add_table(tw_spec_six(nullptr, s.logn1 - 3, ff::kPts));
-  else add_table(tw_spec_pow2(nullptr, s.logn1, ff::kPts));
-  add_table(tw_spec_pow2(nullptr, s.logn2, ff::kPts));
+  const bool product2 = s.logn2 >= flame::kMinLogRowProduct;
+  const size_t tw_col_off = off;
+  if (product) add_mixed(s.logn1);
+  else add_table(tw_spec_pow2(nullptr, s.logn1, ff::kPts), true);
+  const size_t tw_row_off = off;
+  if (product2) add_mixed(s.logn2);
+  else add_table(tw_spec_pow2(nullptr, s.logn2, ff::kPts), true);
   const size_t off_w = off;
   off = align_up(off + 2 * wq * sizeof(float2));
   const size_t off_q = off;
@@ -721,18 +742,19 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   fd.Wp = reinterpret_cast<float2*>(base + off_w);
   fd.Wm = fd.Wp + wq;
   fd.Q = reinterpret_cast<float2*>(base + off_q);
-  const float2* tw_col = specs.t[0].out;
-  const float2* tw_row = specs.t[1].out;
+  const float2* tw_col = reinterpret_cast<const float2*>(base + tw_col_off);
+  const float2* tw_row = reinterpret_cast<const float2*>(base + tw_row_off);
   fd.tw1 = product ? nullptr : tw_col;
-  fd.tw6 = product ? tw_col : nullptr;
-  fd.tw2 = tw_row;
+  fd.twma = product ? tw_col : nullptr;
+  fd.tw2 = product2 ? nullptr : tw_row;
+  fd.twmb = product2 ? tw_row : nullptr;
   fd.n1 = desc->n1;
   fd.n2 = desc->n2;
   fd.m = desc->n2 / 4;
   fd.h1 = desc->n1 / 2;
   fd.tshift = ilog2_exact(s.tq);
   fd.rows = rows;
-  fd.cols = desc->n2;
+  fd.cols = product2 ? 3 * desc->n2 / 4 : desc->n2;
   const bool lit = desc->axis_scale[0] == 0.0;
   fd.s1 = (float)(lit ? desc->theta_pi : desc->axis_scale[0]);
   fd.s2 = (float)(lit ? desc->theta_pi : desc->axis_scale[1]);
@@ -747,15 +769,17 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   rc = last_launch("flame_step_noalloc setup launch");
   if (rc) return rc;
   // W from the state, then the steps (the kernel sequence of flame_step)
+  Group gr{s.logn1, s.logn2, 0, 1, s.tiles, s.rpairs};
+  gr.product = product;
   if (product)
-    flame::launch_colp(s.logn1, flame::COL_FIRST, s.tiles, 1, st, dfl, n, nullptr, ff::kPts);
+    flame::launch_colp(s.logn1, flame::COL_FIRST, s.tiles, 1, st, dfl, n, nullptr, gr.col_kernel_pts(1));
   else
     flame::launch_col(s.logn1, flame::COL_FIRST, s.tiles, 1, st, dfl, n);
-  const int rgroups = (rows / 2 + s.rpairs - 1) / s.rpairs;
   for (int i = 0; i < nsteps; ++i) {
-    flame::launch_row(s.logn2, flame::ROW_STEP, rgroups, 1, st, dfl, n + i, nullptr, nullptr, ff::kPts);
+    flame::launch_row(s.logn2, flame::ROW_STEP, gr.rgroups(), 1, st, dfl, n + i, nullptr, nullptr,
+                      gr.row_kernel_pts(1));
     if (product)
-      flame::launch_colp(s.logn1, flame::COL_STEP, s.tiles, 1, st, dfl, n + i, nullptr, ff::kPts);
+      flame::launch_colp(s.logn1, flame::COL_STEP, s.tiles, 1, st, dfl, n + i, nullptr, gr.col_kernel_pts(1));
     else
       flame::launch_col(s.logn1, flame::COL_STEP, s.tiles, 1, st, dfl, n + i, nullptr, ff::kPts);
   }
@@ -873,17 +897,16 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
       }
     }
   }
-  p->tw_host12.resize(flame::kMaxLog + 1);
-  for (int l = flame::kMinLogRow12; l <= flame::kMaxLog; ++l) {
+  p->tw_hostm.resize(flame::kMaxLog + 1);
+  for (int l = flame::kMinLogRowProduct; l <= flame::kMaxLog; ++l) {
     bool used = false;
     for (const Sizes& s : L.sizes)
       used |= (s.logn1 == l && l >= flame::kMinLogProduct) || s.logn2 == l;
     if (!used) continue;
-    const ff::PassPlan pp = ff::make_plan12(l - 4);
-    auto& host = p->tw_host12[l];
-    host.assign(std::max(1, pp.tw_size), make_float2(1.f, 0.f));
-    ff::build_twiddles_plan(pp, host.data());
-    e = hipMemcpyAsync(base + L.off_tw12[l], host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice,
+    auto& host = p->tw_hostm[l];
+    host.assign(ff::mix_tables_size(l), make_float2(1.f, 0.f));
+    ff::build_mix_tables(l, host.data());
+    e = hipMemcpyAsync(base + L.off_twm[l], host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice,
                        p->stream);
     if (e != hipSuccess) {
       delete p;
@@ -912,8 +935,8 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
     const bool p6 = s.logn1 >= flame::kMinLogProduct;
     fd.tw6 = p6 ? reinterpret_cast<const float2*>(base + L.off_tw6[s.logn1]) : nullptr;
     fd.tw6_8 = p6 ? reinterpret_cast<const float2*>(base + L.off_tw6_8[s.logn1]) : nullptr;
-    fd.tw12a = p6 ? reinterpret_cast<const float2*>(base + L.off_tw12[s.logn1]) : nullptr;
-    fd.tw12b = s.logn2 >= flame::kMinLogRow12 ? reinterpret_cast<const float2*>(base + L.off_tw12[s.logn2]) : nullptr;
+    fd.twma = p6 ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn1]) : nullptr;
+    fd.twmb = s.logn2 >= flame::kMinLogRowProduct ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn2]) : nullptr;
     fd.n1 = d.n1;
     fd.n2 = d.n2;
     fd.m = d.n2 / 4;
@@ -1474,8 +1497,8 @@ int flame_set_points_per_thread(flame_plan p, int32_t n1, int32_t n2, int32_t co
     if (col_pts == 12 && !gr.product)
       return fail(FLAME_ERR_INVALID_ARG, "col_pts = 12 runs on the product grid: enable it first (n1 >= %d)",
                   1 << flame::kMinLogProduct);
-    if (row_pts == 12 && gr.logn2 < flame::kMinLogRow12)
-      return fail(FLAME_ERR_UNSUPPORTED_SIZE, "row_pts = 12 needs n2 >= %d", 1 << flame::kMinLogRow12);
+    if (row_pts == 12 && gr.logn2 < flame::kMinLogRowProduct)
+      return fail(FLAME_ERR_UNSUPPORTED_SIZE, "row_pts = 12 needs n2 >= %d", 1 << flame::kMinLogRowProduct);
     if ((col_pts == 8 && gr.logn1 > flame::kMaxLog8) || (row_pts == 8 && gr.logn2 > flame::kMaxLog8))
       return fail(FLAME_ERR_UNSUPPORTED_SIZE, "8 points per thread needs lengths up to %d", 1 << flame::kMaxLog8);
   }
@@ -1484,13 +1507,8 @@ int flame_set_points_per_thread(flame_plan p, int32_t n1, int32_t n2, int32_t co
   for (size_t gi = 0; gi < p->groups.size(); ++gi) {
     Group& gr = p->groups[gi];
     if ((1 << gr.logn1) != n1 || (1 << gr.logn2) != n2) continue;
-    const bool cols_change = (gr.row_pts == 12) != (row_pts == 12);
     gr.col_pts = col_pts;
     gr.row_pts = row_pts;
-    if (cols_change) {
-      rc = apply_rows(p, (int)gi);
-      if (rc) return rc;
-    }
   }
   drop_graph(p);
   return FLAME_OK;
@@ -1595,7 +1613,7 @@ static std::vector<TuneCfg> tune_cfgs(const Group& gr) {
   std::vector<TuneCfg> cfgs;
   std::vector<int> rows = {16};
   if (gr.logn2 <= flame::kMaxLog8) rows.push_back(8);
-  if (gr.logn2 >= flame::kMinLogRow12) rows.push_back(12);
+  if (gr.logn2 >= flame::kMinLogRowProduct) rows.push_back(12);
   std::vector<int> cols = {16}, pcols = {16};
   if (gr.logn1 <= flame::kMaxLog8) {
     cols.push_back(8);
@@ -1614,7 +1632,7 @@ static std::vector<TuneCfg> tune_cfgs(const Group& gr) {
 
 static int tune_select(flame_plan p, size_t gi, const TuneCfg& cf) {
   Group& gr = p->groups[gi];
-  const bool grid_change = gr.product != cf.product || (gr.row_pts == 12) != (cf.r == 12);
+  const bool grid_change = gr.product != cf.product;
   gr.col_pts = cf.c;
   gr.row_pts = cf.r;
   gr.nt = cf.nt;

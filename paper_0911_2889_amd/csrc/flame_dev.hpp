@@ -39,8 +39,8 @@ struct FlameDev {
   const float2* tw2_8;
   const float2* tw6;   // twiddles of the length-3N1/4 transform (product grid), or null
   const float2* tw6_8; // the same for 8 points per thread
-  const float2* tw12a; // twiddles of the length-3N1/4 transform, 12 points per thread (Shape12), or null
-  const float2* tw12b; // the same for the length-3N2/4 transform
+  const float2* twma;  // twiddles of the length-3N1/4 transforms (ff::MixTables), or null
+  const float2* twmb;  // the same for length 3N2/4
   double* part;        // per-workgroup partial sums of the diagnostics
   const double* r0tab; // reference-radius table {r0(t_n), I1_n, I2_n} (r0_law = 1), or null for r0 = t
   long long r0n;       // its entries
@@ -68,21 +68,14 @@ struct CircleDev {
   double t0, dt;
 };
 
-// Register shape of a length-N transform with PTS points per thread: the
-// power-of-two plans (8 or 16 points), or, for PTS = 12, the length-3N/4
-// transform of a product grid in the 12-point plan (ff::Shape12), which also
-// uses N/16 threads. LOW, HIGH: registers i < LOW hold the spectral positions
-// k = t + G i >= 0 of the retained box, i >= HIGH the negative ones (k - L,
-// L the transform length); the registers between hold padding.
+// Register shape of a length-N transform with PTS (8 or 16) points per
+// thread. LOW, HIGH: registers i < LOW hold the spectral positions
+// k = t + G i >= 0 of the retained box, i >= HIGH the negative ones (k - N);
+// the registers between hold padding.
 template <int LOGN, int PTS>
 struct TfShape {
   using S = ff::Shape<LOGN, PTS>;
   static constexpr int LOW = PTS / 4, HIGH = 3 * PTS / 4;
-};
-template <int LOGN>
-struct TfShape<LOGN, 12> {
-  using S = ff::Shape12<LOGN - 4>;
-  static constexpr int LOW = 4, HIGH = 8;
 };
 template <int LOGN, int PTS>
 using TShape = typename TfShape<LOGN, PTS>::S;
@@ -115,12 +108,29 @@ struct ColCfg {
 // instead of N1. The product of two fields with |k1| <= K1 = N1/4 - 1 has
 // |k1| <= 2 K1, and on M1 >= 3 K1 + 1 rows no alias of it lands in
 // |k1| <= K1, so the truncated quadratic term is the same as on N1 rows up to
-// rounding. The column transforms have length M1 = 6 * N1/8 (Shape6:
-// radix-PTS passes, then radix 6), with G = M1/PTS threads per column. Used
-// for N1 >= 128.
+// rounding. Used for N1 >= 128. The same holds along phi: the step's row
+// kernel forms the term on 3 N2/4 points for N2 >= 64 (mixed_bodies.hpp).
+// ColCfgP is the adjoint's column kernel on that grid: length M1 = 6 * N1/8
+// (Shape6: radix-PTS passes, then radix 6), with G = M1/PTS threads per column.
 constexpr int kMinLogProduct = 7;
-// The phi product grid (3 N2/4 points, 12 points per thread) needs N2 >= 64.
-constexpr int kMinLogRow12 = 6;
+constexpr int kMinLogRowProduct = 6;
+
+// Whether a step kernel on a product grid runs the bodies for few transforms
+// (mixed_bodies.hpp, "few transforms"): `transforms` columns or row pairs of
+// length 2^logn in the launch, which the other bodies run on N/16 lanes each.
+// Measured: up to 2048 points they win while those lanes make at most half a
+// wave per SIMD of the chip for the columns (512 waves: 1024x2048 10.3 against
+// 11.7 us; at 1024 waves, 1024x4096, 16.0 against 14.9) and one wave per SIMD
+// for the rows (768 waves: 8.8 against 9.3 us). At 4096 points a workgroup of
+// either kind is one transform and fills its compute unit's issue slots, and
+// side by side is slower (9.5 against 8.5 us for 96 row pairs). At 8192 points
+// the variant is 512 lanes instead of 256: faster while every compute unit
+// has at most one transform (128x8192 14.1 against 16.5 us), slower where two
+// workgroups of 256 threads can share one (8192x8192: 196 against 161 us).
+constexpr bool split_pays(int logn, long long transforms, bool columns) {
+  const long long waves = transforms * ((1 << logn) / 16) / 64;
+  return logn <= 11 ? waves <= (columns ? 512 : 1024) : logn == 13 && transforms <= 256;
+}
 
 template <int LOGN1, int PTS = 16>
 struct ColCfgP {
@@ -136,37 +146,6 @@ struct ColCfgP {
   static_assert(THREADS % 64 == 0, "whole waves");
 };
 
-// Split variant of the product-grid column kernel: per column 2G threads
-// (G = M1/16) run the forward transform with 8 points each (Shape6 with
-// PTS 8), then split into two groups of G threads that run the Wp and the Wm
-// inverse transforms side by side with 16 points each, each group in its own
-// LDS buffer. Twice the waves of ColCfgP<., 16> for the same columns.
-template <int LOGN1>
-struct ColCfgQ {
-  using SF = ff::Shape6<LOGN1 - 3, 8>;   // forward
-  using SI = ff::Shape6<LOGN1 - 3, 16>;  // inverse
-  static constexpr int M1 = SF::N;
-  static constexpr int G8 = SF::G, G16 = SI::G;
-  static constexpr int T = ColCfgP<LOGN1, 16>::T;
-  static constexpr int TQ = ColCfgP<LOGN1, 16>::TQ;
-  static constexpr int QS = ColCfgP<LOGN1, 16>::QS;
-  static constexpr int SLOTS = SF::LDS;  // padded slots of one buffer
-  static constexpr int THREADS = T * G8;
-  static constexpr int LDS_BYTES = 2 * SLOTS * T * 8;
-  static_assert(G8 == 2 * G16, "two inverse groups");
-  static_assert(THREADS % 64 == 0, "whole waves");
-};
-
-// The row kernel's 12-point plan keeps the twiddles of the passes with
-// Ns >= this in registers and reads the others from a copy in LDS (SplitTw).
-constexpr int kRow12MinNs = 192;
-// Table entries of the passes p >= 1 with Ns < min_ns (they come first in the table).
-constexpr int lds_twiddles(const ff::PassPlan& p, int min_ns) {
-  int q = 1;
-  while (q < p.npass && p.ns[q] < min_ns) ++q;
-  return p.tw_off[q] > 0 ? p.tw_off[q] : 1;
-}
-
 // Row kernel: B = max(1, 16*256/N2) row pairs per workgroup, interleaved.
 // WPE: the minimum waves per SIMD it is compiled for; at N2 = 8192 with 16
 // points per thread a workgroup is 8 waves (2 per SIMD), which may then use
@@ -177,11 +156,8 @@ struct RowCfg {
   static constexpr int G = TShape<LOGN2, PTS>::G;
   static constexpr int B = G16 >= 256 ? 1 : 256 / G16;
   static constexpr int THREADS = B * G;
-  static constexpr int DATA_SLOTS = TShape<LOGN2, PTS>::LDS * B;  // transform exchange area
-  // with 12 points per thread, the small-Ns passes' twiddles follow in LDS (SplitTw)
-  static constexpr int TW_SLOTS = PTS == 12 ? lds_twiddles(TShape<LOGN2, PTS>::plan, kRow12MinNs) : 0;
-  static constexpr int LDS_BYTES = (DATA_SLOTS + TW_SLOTS) * 8;
-  static constexpr int WPE = THREADS >= 512 && PTS >= 12 ? 2 : ROW_WAVES_PER_EU;
+  static constexpr int LDS_BYTES = TShape<LOGN2, PTS>::LDS * B * 8;
+  static constexpr int WPE = THREADS >= 512 && PTS == 16 ? 2 : ROW_WAVES_PER_EU;
 };
 
 constexpr int col_tile(int logn1) { return col_tile_for((1 << logn1) / ff::kPts); }
@@ -230,8 +206,7 @@ constexpr bool kPrune = FLAME_PRUNE != 0;
 constexpr int kMinLog = 4;
 constexpr int kMaxLog = 14;
 // Lengths up to 2^kMaxLog8 have the 8-points-per-thread kernels (beyond it
-// they would need more than 1024 threads per workgroup), and so does the
-// split product-grid column kernel.
+// they would need more than 1024 threads per workgroup).
 constexpr int kMaxLog8 = 13;
 constexpr int kDiagThreads = 256;
 
@@ -246,9 +221,8 @@ struct EnsembleItem {
   int logn1, logn2;    // the grid of its flames
   int rtiles, ctiles;  // row-pair groups and column tiles of one flame
 };
-// Its step kernels' bodies: the product-grid column transforms with 12
-// points per thread (N1 = 2^7 .. 2^10) and the row transforms with 16 (N2 =
-// 2^7 .. 2^11), all of them 256 threads per workgroup.
+// Its step kernels' bodies: the product-grid columns (N1 = 2^7 .. 2^10) and
+// rows (N2 = 2^7 .. 2^11), all of them 256 threads per workgroup.
 constexpr int kEnsThreads = 256;
 constexpr int kEnsMinLog1 = 7, kEnsMaxLog1 = 10;
 constexpr int kEnsMinLog2 = 7, kEnsMaxLog2 = 11;

@@ -13,6 +13,7 @@ struct KernelLaunch {
   const void* func;
   int threads;
   int lds;
+  int mult = 1;  // workgroups per column tile (or row group) of the flame's Sizes
 };
 
 // The step kernels for a transform length (arguments: fls, n, nbase, src / in, out).
@@ -37,7 +38,11 @@ void launch_col(int logn1, int mode, int tiles, int nfl, hipStream_t st, const F
 
 // Column kernel of the step on the product grid (3 N1/4 rows; N1 >= 128),
 // mode COL_STEP or COL_FIRST; colp_kernel_info gives its function and shape
-// (func null for an unsupported size).
+// (func null for an unsupported size). rowp_kernel_info: the row kernel on
+// 3 N2/4 phi points (N2 >= 64). mixed_lds_bytes: the most LDS either asks for
+// at length 2^logn.
+KernelLaunch rowp_kernel_info(int logn2, int pts, bool nt);
+int mixed_lds_bytes(int logn);
 KernelLaunch colp_kernel_info(int logn1, int mode, int pts, int var = VAR_EULER);
 void launch_colp(int logn1, int mode, int tiles, int nfl, hipStream_t st, const FlameDev* fl, long long n,
                  const void* src = nullptr, int pts = ff::kPts, hipEvent_t ev_start = nullptr,

@@ -36,8 +36,7 @@ __device__ __forceinline__ void fft(float2 (&v)[PTS], int t, float2* lds, int st
   fft_passes<LOGN, INV, OUTER, PTS, 0>(v, t, lds, stride, tw);
 }
 
-// The same for any register shape S (ff::Shape, ff::Shape12); with
-// ff::Shape12, OUTER means the middle third of the registers vanishes.
+// The same with the register shape S as a parameter.
 template <class S, bool INV, bool OUTER = false, int P = 0, class TW>
 __device__ __forceinline__ void fft_s(float2 (&v)[S::PTS], int t, float2* lds, int stride, const TW& tw) {
   if constexpr (P < S::NPASS) {
@@ -108,59 +107,6 @@ struct KernelTw {
   }
 };
 
-// Twiddles of a step kernel's transform along an axis of 2^LOGN points with
-// PTS points per thread: the power-of-two plans (tables p16, p8), or, for
-// PTS = 12, the length-3*2^LOGN/4 transform of the 12-point plan (table p12),
-// cached in registers.
-template <int LOGN, int PTS>
-struct AxisTw {
-  using Type = typename std::conditional<PTS == 12, ff::RegTwS<TShape<LOGN, PTS>, GlobalFetch, kTwCacheMinNs>,
-                                         typename KernelTw<LOGN, PTS == 12 ? 16 : PTS>::Type>::type;
-  static __device__ __forceinline__ Type make(const float2* p16, const float2* p8, const float2* p12, int t) {
-    if constexpr (PTS == 12) {
-      return Type(GlobalFetch{(const gf2*)p12}, t);
-    } else {
-      return KernelTw<LOGN, PTS>::make(PTS == 8 ? p8 : p16, t);
-    }
-  }
-};
-
-// Twiddle source for kernels short of registers: the passes with
-// Ns >= MIN_NS keep their twiddles in registers for the kernel's lifetime
-// (loaded from the global table), the passes with smaller Ns read theirs at
-// each use from a copy of the first LDS_ENTRIES entries of the table in LDS
-// (those passes' part), which the kernel writes before its first transform's
-// second pass. The passes with small Ns have few distinct twiddles, so the
-// lanes of a wave read few LDS addresses.
-template <class S, int MIN_NS>
-struct SplitTw {
-  using Reg = ff::RegTwS<S, GlobalFetch, MIN_NS>;
-  static constexpr int first_cached() {
-    int p = 1;
-    while (p < S::NBF && !Reg::cached(p)) ++p;
-    return p;
-  }
-  static constexpr int LDS_ENTRIES = S::tw_off(first_cached()) > 0 ? S::tw_off(first_cached()) : 1;
-  Reg reg;
-  const float2* tab;
-  int t;
-  __device__ __forceinline__ SplitTw(const float2* global_tab, const float2* lds_tab, int t_)
-      : reg(GlobalFetch{(const gf2*)global_tab}, t_), tab(lds_tab), t(t_) {}
-  // copy the table's first LDS_ENTRIES entries into LDS (every thread of the workgroup calls it)
-  static __device__ __forceinline__ void stage(float2* lds_tab, const float2* global_tab, int tid, int threads) {
-    for (int i = tid; i < LDS_ENTRIES; i += threads) lds_tab[i] = ld((const gf2*)global_tab + i);
-  }
-  template <int P>
-  __device__ __forceinline__ float2 get(int b, int r) const {
-    if constexpr (Reg::cached(P)) {
-      return reg.template get<P>(b, r);
-    } else {
-      constexpr int NS = S::ns(P);
-      return tab[S::tw_off(P) + (r - 1) * NS + ff::mod_ns<NS>(t + b * S::G)];
-    }
-  }
-};
-
 // Twiddles of a length 6*2^LOGP transform, cached in registers.
 template <int LOGP, int PTS>
 struct KernelTw6 {
@@ -221,6 +167,7 @@ __device__ __forceinline__ double r0_at(const FlameDev& f, long long n) {
 // 3 N1/4 theta rows, N2 or 3 N2/4 phi points): the forward transforms are
 // unnormalised, so a = dt c_n / (rows cols).
 __device__ __forceinline__ StepScalars step_scalars(const FlameDev& f, long long n, int rows, int cols) {
+#pragma clang fp contract(off)  // one rounding whatever body this is compiled into
   StepScalars s;
   if (f.r0tab) {
     const double* e = r0_entry(f, n);
@@ -243,7 +190,48 @@ __device__ __forceinline__ StepScalars step_scalars(const FlameDev& f, long long
 // The hardware exp2 and square root: the exponent's rounding costs a relative
 // error of about |x| 2^-24 in E, which matters only where E << 1.
 __device__ __forceinline__ float growth_factor(float kk2, const StepScalars& sc, float gamma) {
-  return __expf(-kk2 * sc.i2 + 0.5f * gamma * __builtin_amdgcn_sqrtf(kk2) * sc.i1);
+#pragma clang fp contract(off)
+  return __expf(__builtin_fmaf(-kk2, sc.i2, 0.5f * gamma * __builtin_amdgcn_sqrtf(kk2) * sc.i1));
+}
+
+// The step's formulas, each operation written out: the kernels that run them
+// on different splits of the work (mixed_bodies.hpp) round alike, so that a
+// flame's bits do not depend on how many others share its launch.
+// |kappa|^2
+__device__ __forceinline__ float norm2(float a, float b) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(a, a, b * b);
+}
+// (i kappa1 + kp) s
+__device__ __forceinline__ float2 slope(float kap1, float kp, float2 s) {
+#pragma clang fp contract(off)
+  return make_float2(__builtin_fmaf(kp, s.x, -(kap1 * s.y)), __builtin_fmaf(kp, s.y, kap1 * s.x));
+}
+// One mode's update (Euler, or Heun's predictor; Heun's corrector): q the raw
+// transform of |grad Phi|^2, a and ac its factors, prd Heun's predictor.
+template <int VAR>
+__device__ __forceinline__ float update1(float e, float old, float q, float frc, float prd, float a, float ac,
+                                         float dt) {
+#pragma clang fp contract(off)
+  if constexpr (VAR == VAR_HEUN_C) {
+    return 0.5f * __builtin_fmaf(dt, frc, __builtin_fmaf(ac, q, __builtin_fmaf(e, old, prd)));
+  } else {
+    float x = __builtin_fmaf(a, q, old);
+    if constexpr (VAR != VAR_EULER) x = __builtin_fmaf(dt, frc, x);
+    return e * x;
+  }
+}
+template <int VAR>
+__device__ __forceinline__ float2 update_mode(float e, float2 old, float2 q, float2 frc, float2 prd, float a, float ac,
+                                              float dt) {
+  return make_float2(update1<VAR>(e, old.x, q.x, frc.x, prd.x, a, ac, dt),
+                     update1<VAR>(e, old.y, q.y, frc.y, prd.y, a, ac, dt));
+}
+// Rows a and b of a packed real pair from Y(k) and Y(-k): (Y(k) + conj Y(-k))/2, (Y(k) - conj Y(-k))/(2i)
+__device__ __forceinline__ void split_pair(float2 yk, float2 ym, float2& a, float2& b) {
+#pragma clang fp contract(off)
+  a = make_float2(0.5f * (yk.x + ym.x), 0.5f * (yk.y - ym.y));
+  b = make_float2(0.5f * (yk.y + ym.y), 0.5f * (ym.x - yk.x));
 }
 
 // f~_k of Eq. (1) for stored column m and wavenumber k1, read from the bound
@@ -295,8 +283,7 @@ __device__ __forceinline__ int xcd_swizzle(int b, int nb) {
 
 // Register slot kk (0..7) of the kept spectral positions: registers
 // 0..LOW-1 hold k = t + G*i >= 0, registers HIGH..PTS-1 hold k = t + G*i - L < 0
-// (the first and last quarter of a padded length L = N, or the first and
-// last third of a product-grid length L = 3N/4; TfShape).
+// (the first and last quarter of the padded length; TfShape).
 template <int LOGN, int PTS>
 __device__ __forceinline__ constexpr int kept_reg(int kk) {
   return kk < TfShape<LOGN, PTS>::LOW ? kk : kk + (TfShape<LOGN, PTS>::HIGH - TfShape<LOGN, PTS>::LOW);

@@ -1,7 +1,7 @@
-// Bodies of the step's column and row kernels: one workgroup's work on one
-// column tile or one group of row pairs of a flame. The kernels of
-// flame_kernels.hip run one body per workgroup; the persistent ensemble kernel
-// (ensemble_kernel.hip) runs many, one after another.
+// Bodies of the column and row kernels on the power-of-two grid (the step's on
+// N1 rows or fewer than 64 phi points, and the projection, synthesis and
+// diagnostics): one workgroup's work on one column tile or one group of row
+// pairs of a flame.
 
 #pragma once
 
@@ -15,21 +15,13 @@
 
 namespace flame {
 
-// PTS 16 or 8: the column transforms have length N1 (the grid's theta rows).
-// PTS 12: they have length L = 3 N1/4 (the product grid, N1 >= 128) in the
-// 12-point plan (ff::Shape12), on the same N1/16 threads per column as
-// PTS 16 on N1 rows; the kept modes sit in the first and last third of the
-// registers instead of the first and last quarter (TfShape). COL_STEP and
-// COL_FIRST only for PTS 12.
-//
+// The column transforms have length N1, with PTS (16 or 8) points per thread.
 // col_body is the work of thread tid of a workgroup on column tile `tile` of
-// flame f at step index n: col_kernel runs it on tile xcd_swizzle(blockIdx.x),
-// the persistent ensemble kernel on the tiles of its part of a flame.
+// flame f at step index n.
 template <int LOGN1, int MODE, int PTS = ff::kPts, int SV = VAR_EULER>
 __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const float2* src, int tile, int tid) {
   constexpr int VAR = SV & ~VAR_NT;
   constexpr bool NT = MODE == COL_STEP && (SV & VAR_NT) != 0;
-  static_assert(PTS != 12 || MODE == COL_STEP || MODE == COL_FIRST, "12 points per thread: step modes only");
   using TS = TfShape<LOGN1, PTS>;
   using S = typename TS::S;
   constexpr int G = S::G, T = ColCfg<LOGN1, PTS>::T, N1 = 1 << LOGN1, L = S::N;
@@ -48,7 +40,7 @@ __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const f
   gf2* const Sc = glob((MODE == COL_FIRST || MODE == COL_SYNTH) && src ? const_cast<float2*>(src) : f.S) +
                   (size_t)m * f.h1 + N1 / 4;
   gf2* const Pc = glob(VAR >= VAR_HEUN_P ? f.S2 : f.S) + (size_t)m * f.h1 + N1 / 4;  // Heun's predictor
-  const auto tw1 = AxisTw<LOGN1, PTS>::make(f.tw1, f.tw1_8, f.tw12a, t);
+  const auto tw1 = KernelTw<LOGN1, PTS>::make(PTS == 8 ? f.tw1_8 : f.tw1, t);
 
   float2 v[PTS];
   float2 sv[KEEP];
@@ -185,15 +177,12 @@ __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const f
   }
 }
 
-// PTS 16 or 8: the row transforms have length N2. PTS 12 (ROW_STEP only):
-// the quadratic term is formed on L2 = 3 N2/4 phi points (the product grid
-// along phi, N2 >= 64), with the 12-point plan on N2/16 threads per row pair.
+// The row transforms have length N2, with PTS (16 or 8) points per thread.
 // row_body is the work of thread tid of a workgroup on row-pair group `group`
 // of flame f (ROW_DIAG writes its partial sum to f.part[slot]).
 template <int LOGN2, int MODE, int PTS = ff::kPts, bool NT = false>
 __device__ __forceinline__ void row_body(const FlameDev& f, long long n, const float* __restrict__ phys_in,
                                          float* __restrict__ phys_out, int group, int slot, int tid) {
-  static_assert(PTS != 12 || MODE == ROW_STEP, "12 points per thread: the step only");
   using TS = TfShape<LOGN2, PTS>;
   using S = typename TS::S;
   constexpr int G = S::G, B = RowCfg<LOGN2, PTS>::B, N2 = 1 << LOGN2, L2 = S::N;
@@ -206,18 +195,7 @@ __device__ __forceinline__ void row_body(const FlameDev& f, long long n, const f
   const bool live = pair < n1 / 2;
   const int ja = 2 * pair, jb = 2 * pair + 1;
   float2* my = lds + p;
-  // 12 points per thread: the small-Ns passes read their twiddles from LDS
-  using Tw12 = SplitTw<S, kRow12MinNs>;
-  float2* const lds_tw = lds + RowCfg<LOGN2, PTS>::DATA_SLOTS;
-  if constexpr (PTS == 12) Tw12::stage(lds_tw, f.tw12b, tid, RowCfg<LOGN2, PTS>::THREADS);
-  const auto tw2 = [&] {
-    if constexpr (PTS == 12) {
-      static_assert(Tw12::LDS_ENTRIES <= RowCfg<LOGN2, PTS>::TW_SLOTS, "LDS twiddle area");
-      return Tw12(f.tw12b, lds_tw, t);
-    } else {
-      return AxisTw<LOGN2, PTS>::make(f.tw2, f.tw2_8, f.tw12b, t);
-    }
-  }();
+  const auto tw2 = KernelTw<LOGN2, PTS>::make(PTS == 8 ? f.tw2_8 : f.tw2, t);
   gf2* const Wp = glob(f.Wp);
   gf2* const Wm = glob(f.Wm);
   gf2* const Q = glob(f.Q);
