@@ -12,8 +12,8 @@
 // The area excess J = (1/P) sum sqrt(1 + |grad Phi|^2/r0^2) - 1 has
 //     dJ/dPhi = -Pi div( grad Phi / (P r0^2 sqrt(1 + |grad Phi|^2/r0^2)) ).
 //
-// One adjoint step is three kernels (on the step's grid: N1 rows, or the
-// 3 N1/4-row product grid with adjp_col in place of adj_col):
+// One adjoint step is three kernels on the step's grid: adjm_col (3 N1/4 rows)
+// or adj_col (N1 rows), and adjm_row (3 N2/4 phi points) or adj_row (N2 < 64):
 //  * adj_col<ADJ_A>: mu = E lambda per column; column inverse transforms of mu
 //    (-> Q) and of (i kappa1 -+ kappa2) Phi~^n (-> Wp, Wm, as the forward step);
 //  * adj_row<ROW_ADJ>: per row pair, m (one packed real synthesis for two
@@ -32,6 +32,7 @@
 #include "flame_dev.hpp"
 #include "flame_kernels.hpp"
 #include "kernel_common.hpp"
+#include "mixed_bodies.hpp"
 
 namespace flame {
 
@@ -138,7 +139,7 @@ __global__ void __launch_bounds__(ColCfg<LOGN1>::THREADS) __attribute__((amdgpu_
     float2 out[8];
     const float inv_p = 1.0f / ((float)f.n1 * (float)f.n2);
     StepScalars sc{};
-    if constexpr (MODE == ADJ_C) sc = step_scalars(f, n, f.n1, f.n2);
+    if constexpr (MODE == ADJ_C) sc = step_scalars(f, n, f.n1, f.cols);
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       const int i = kept_reg<LOGN1, ff::kPts>(kk);
@@ -183,159 +184,287 @@ __global__ void __launch_bounds__(ColCfg<LOGN1>::THREADS) __attribute__((amdgpu_
   }
 }
 
-// adj_col on the product grid (ColCfgP, M1 = 3 N1/4 rows; see colp_kernel):
-// ADJ_A and ADJ_C with the length-M1 transforms. ADJ_A's inputs are in the
-// natural map, so its three inverse transforms need no remap; ADJ_C's forward
-// transforms leave A1 and A2 in the radix-6 output map, where the update is
-// formed; the kept modes go through LDS to the natural map (column k2 = 0
-// symmetrised on the way) and are stored from there.
-template <int LOGN1, int MODE>
-__global__ void __launch_bounds__((ColCfgP<LOGN1, 16>::THREADS))
-    __attribute__((amdgpu_waves_per_eu(COL_WAVES_PER_EU)))
-    adjp_col_kernel(const FlameDev* __restrict__ fls, long long n, const float2* state, const float2* lam_in,
+// The product-grid kernels hold NG transforms side by side, on NG groups of G
+// lanes and in NG exchange areas (NG = 3: the three inverse transforms of a
+// column or row pair; NG = 2: the two forward ones of a column), or run them
+// one after another on N/16 lanes (NG = 1). As for the step's kernels
+// (split_pays), side by side is for launches that leave most of the chip idle.
+template <int LOGN, int NG>
+struct AdjMix {
+  static constexpr int N = 1 << LOGN, NB = N / 16;
+  static constexpr int G = NG > 1 ? split_lanes(LOGN) : NB;
+  static constexpr int T = NG > 1 ? (G >= 64 ? 1 : 64 / G) : (G >= 256 ? 1 : 256 / G);
+  // twiddles in registers (MixTw); one after another, a row kernel holds both
+  // rows' inputs and m beside its transform, and from 2048 points on spills
+  static constexpr bool HELD = LOGN < 14, HELD_ROW = NG > 1 || LOGN < 11;
+  using F = ff::Mix<typename ff::MixPlan<LOGN>::F, G, T>;
+  using I = ff::Mix<typename ff::MixPlan<LOGN>::I, G, T>;
+  static constexpr int L = F::N, AREA = F::LDS > I::LDS ? F::LDS : I::LDS;
+  static constexpr int THREADS = NG * G * T;
+  static constexpr int LDS_BYTES = 8 * NG * AREA;
+};
+
+template <int LOGN1, int MODE, int NG>
+__global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
+    __attribute__((amdgpu_waves_per_eu(ADJ_ROW_WAVES_PER_EU)))
+    adjm_col_kernel(const FlameDev* __restrict__ fls, long long n, const float2* state, const float2* lam_in,
                     float2* lam_out) {
   static_assert(MODE == ADJ_A || MODE == ADJ_C, "product-grid adjoint modes");
-  using Cfg = ColCfgP<LOGN1, 16>;
-  using S6 = typename Cfg::S;
-  constexpr int LOGP = LOGN1 - 3;
-  constexpr int G = S6::G, T = Cfg::T, M1 = S6::N, N6 = S6::N6, IT = S6::IT6, N1 = 1 << LOGN1;
-  constexpr int TQ = Cfg::TQ, QS = Cfg::QS, K1 = N1 / 4 - 1;
+  using C = AdjMix<LOGN1, NG>;
+  using F = typename C::F;
+  using I = typename C::I;
+  constexpr int G = C::G, T = C::T, NB = C::NB, L = C::L, N1 = C::N;
+  constexpr int TQ = q_tile_for(NB), QS = ff::ilog2c(TQ);
   extern __shared__ float2 lds[];
   const FlameDev f = fls[blockIdx.y];
   const int tid = threadIdx.x;
-  const int c = tid % T, t = tid / T;
+  const int c = tid % T, u = tid / T;
+  const int h = u / G, t = u % G;
   const int tile = xcd_swizzle(blockIdx.x, gridDim.x);
   const int m = tile * T + c;
   const bool live = m < f.m;
-  float2* my = lds + c;
-  const size_t tile_base = ((((size_t)m >> QS) * M1) << QS) + (m & (TQ - 1));  // column m of Q, A1, A2
+  const bool act = G == NB || t < NB;  // lanes of the radix-12 pass
+  float2* const my = lds + c + h * C::AREA;
+  const size_t tile_base = ((((size_t)m >> QS) * L) << QS) + (m & (TQ - 1));  // column m of Q, A1, A2
   const size_t col = (size_t)m * f.h1 + N1 / 4;  // element k1 of column m at col + k1
-  // loads carry no condition, as in adj_col_kernel; a slot that holds no kept
-  // mode reads k1 = 0 and its value is replaced or unused
+  // loads carry no condition (a branch around a load makes the compiler wait
+  // for every load issued before it): a column past the grid reads column 0
+  // of the spectra and its padded slots of A1 and A2, and is never stored
   const size_t coll = (size_t)(live ? m : 0) * f.h1 + N1 / 4;
-  const auto tw = KernelTw6<LOGP, 16>::make(f.tw6, t);
   const float kap2 = f.s2 * (float)m;
-  const StepScalars sc = step_scalars(f, n, M1, f.n2);
-  auto k1_of = [](int p) { return p < M1 / 2 ? p : p - M1; };
-  auto kept_at = [](int p) { return p < 2 * N6 || p > 4 * N6; };
+  const StepScalars sc = step_scalars(f, n, L, f.cols);
+  const int jt = act ? t : 0;
+  auto k1_of = [&](int kk) { return kk < 4 ? jt + NB * kk : jt - NB * (8 - kk); };
   gf2* const lin = glob(const_cast<float2*>(lam_in));
 
   if constexpr (MODE == ADJ_A) {
-    float2 sv[16], v[16];
+    // job 0: the column synthesis of mu = E lambda -> Q; jobs 1 and 2: Z+ and
+    // Z- of the state, as the forward column kernel -> Wp, Wm
+    float2 lm[8], sv[8];
+    gf2* const one = NG == 1 || h == 0 ? lin : glob(const_cast<float2*>(state));
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int pos = t + G * i;
-      const int k1 = kept_at(pos) ? k1_of(pos) : 0;
-      v[i] = ld(lin + coll + k1);
-      sv[i] = ld(glob(const_cast<float2*>(state)) + coll + k1);
-    }
+    for (int kk = 0; kk < 8; ++kk) lm[kk] = ld(one + coll + k1_of(kk));
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {  // mu = E lambda, zero outside the box (selects, after every load)
-      const int pos = t + G * i;
-      const bool kept = kept_at(pos);
-      const float e = efactor(f, sc, kept ? k1_of(pos) : 0, kap2);
-      v[i] = kept ? ff::cscale(v[i], e) : make_float2(0.f, 0.f);
-      sv[i] = kept ? sv[i] : make_float2(0.f, 0.f);
-    }
-    float2 o[IT * 6];
-    fft6<LOGP, true, 16>(v, o, t, my, T, tw);  // M = column synthesis of mu -> Q
-    if (live) {
+    for (int kk = 0; kk < 8; ++kk)
+      sv[kk] = NG == 1 ? ld(glob(const_cast<float2*>(state)) + coll + k1_of(kk)) : lm[kk];
+    const MixTw<I, C::HELD> tw(f.twma, t);
 #pragma unroll
-      for (int it = 0; it < IT; ++it) {
-        const int j = t + G * it;
-        if (j < N6) {
+    for (int q = 0; q < (NG == 1 ? 3 : 1); ++q) {
+      const int job = NG == 1 ? q : h;
+      const float kp = job == 1 ? -kap2 : kap2;
+      float2 v[I::REGS];
 #pragma unroll
-          for (int r = 0; r < 6; ++r) st(glob(f.Q) + tile_base + (size_t)(j + r * N6) * TQ, o[it * 6 + r]);
-        }
+      for (int kk = 0; kk < 8; ++kk) {
+        const int k1 = k1_of(kk);
+        const float kap1 = f.s1 * (float)k1;
+        const float2 mu = ff::cscale(lm[kk], efactor(f, sc, k1, kap2)), z = slope(kap1, kp, sv[kk]);
+        v[kk < 4 ? kk : kk + 4] = job == 0 ? mu : z;
       }
-    }
-    // Z+ and Z- of the state, as the forward column kernel
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      const float sgn = pass == 0 ? -1.f : 1.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float kap1 = f.s1 * (float)k1_of(t + G * i);
-        v[i] = make_float2(-kap1 * sv[i].y + sgn * kap2 * sv[i].x, kap1 * sv[i].x + sgn * kap2 * sv[i].y);
-      }
-      fft6<LOGP, true, 16>(v, o, t, my, T, tw);
+      mix_fft<I, true, true>(v, my, tw);
       if (live) {
-        gf2* dst = glob(pass == 0 ? f.Wp : f.Wm);
+        constexpr int P = I::NPASS - 1, R = I::radix(P);
+        gf2* const wd = glob(job == 1 ? f.Wp : f.Wm);
+        const float cs = job == 1 ? 1.f : -1.f;  // Wm holds the conjugate
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
-          const int j = t + G * it;
-          if (j < N6) {
+        for (int b = 0; b < I::rounds(P); ++b)
+          if (I::template active<P>(t, b)) {
 #pragma unroll
-            for (int r = 0; r < 6; ++r)
-              st(dst + w_index(j + r * N6, m, f.m), pass == 0 ? o[it * 6 + r] : ff::cconj(o[it * 6 + r]));
+            for (int r = 0; r < R; ++r) {
+              const int j1 = t + G * b + r * I::bf(P);
+              const float2 x = v[b * R + r];
+              if (job == 0)
+                st(glob(f.Q) + tile_base + (size_t)j1 * TQ, x);
+              else
+                st(wd + w_index(j1, m, f.m), make_float2(x.x, cs * x.y));
+            }
           }
-        }
       }
     }
   } else {
-    // lambda^{n+1} at the kept modes, in the radix-6 output map
-    constexpr int KR[4] = {0, 1, 4, 5};
-    float2 lam[IT][4];
+    // forward column transforms of the row transforms of w1 (job 0) and i kappa2 w2 (job 1)
+    float2 lam[8], u1[8], w2[8];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int j = t + G * it;
+    for (int kk = 0; kk < 8; ++kk) lam[kk] = ld(lin + coll + k1_of(kk));
+    const MixTw<F, C::HELD> tw(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, t);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int pos = j + KR[q] * N6;
-        lam[it][q] = ld(lin + coll + (j < N6 && kept_at(pos) ? k1_of(pos) : 0));
-      }
-    }
-    // forward column transforms of the row transforms of w1 and i kappa2 w2
-    float2 ou[IT * 6], ow[IT * 6];
-    {
-      float2 v[16];
+    for (int q = 0; q < (NG == 1 ? 2 : 1); ++q) {
+      const int job = NG == 1 ? q : h;
+      gf2* const srcp = glob(job == 0 ? f.A1 : f.A2) + tile_base;
+      float2 v[F::REGS];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = ld(glob(f.A1) + tile_base + (size_t)(t + G * i) * TQ);
-      fft6<LOGP, false, 16>(v, ou, t, my, T, tw);
+      for (int b = 0; b < F::rounds(0); ++b)
+        if (F::template active<0>(t, b)) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = ld(glob(f.A2) + tile_base + (size_t)(t + G * i) * TQ);
-      fft6<LOGP, false, 16>(v, ow, t, my, T, tw);
-    }
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int j = t + G * it;
-      if (j < N6) {
-#pragma unroll
-        for (int r = 0; r < 6; ++r) {
-          const int pos = j + r * N6;
-          float2 val = make_float2(0.f, 0.f);
-          if (r != 2 && r != 3 && kept_at(pos)) {
-            const int q = r < 2 ? r : r - 2;
-            const int k1 = k1_of(pos);
-            const float kap1 = f.s1 * (float)k1;
-            const float2 u = ou[it * 6 + r], w = ow[it * 6 + r];
-            // raw divergence i kappa1 U1 + V2 (sums without the 1/P factors)
-            const float2 div = make_float2(-kap1 * u.y + w.x, kap1 * u.x + w.y);
-            const float e = efactor(f, sc, k1, kap2);
-            val = make_float2(e * lam[it][q].x - 2.f * sc.a * div.x, e * lam[it][q].y - 2.f * sc.a * div.y);
-          }
-          my[ff::lds_pad(pos) * T] = val;
+          for (int r = 0; r < F::radix(0); ++r)
+            v[b * F::radix(0) + r] = ld(srcp + (size_t)(t + G * b + r * F::bf(0)) * TQ);
         }
-      }
-    }
-    __syncthreads();
-    if (tile == 0) {  // symmetrise column k2 = 0: k1 > 0 conjugated onto -k1, Im at k1 = 0 zeroed
-      if (c == 0) {
+      mix_fft<F, false, false>(v, my, tw);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int k1 = t + G * i;
-          if (k1 >= 1 && k1 <= K1) my[ff::lds_pad(M1 - k1) * T] = ff::cconj(my[ff::lds_pad(k1) * T]);
-        }
-        if (t == 0) my[0].y = 0.f;
+      for (int kk = 0; kk < 8; ++kk) (q == 0 ? u1 : w2)[kk] = v[kk < 4 ? kk : kk + 4];
+    }
+    if constexpr (NG == 2) {  // the second transform's modes to the first group
+      if (h == 1 && act) {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) my[(t + NB * kk) * T] = u1[kk];
       }
       __syncthreads();
-    }
-    if (live) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int pos = t + G * i;
-        if (kept_at(pos)) st(glob(lam_out) + col + k1_of(pos), my[ff::lds_pad(pos) * T]);
+      for (int kk = 0; kk < 8; ++kk) w2[kk] = lds[c + C::AREA + (jt + NB * kk) * T];
+    }
+    float2 out[8];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const int k1 = k1_of(kk);
+      const float kap1 = f.s1 * (float)k1;
+      // raw divergence i kappa1 U1 + V2 (sums without the 1/P factors)
+      const float2 div = make_float2(-kap1 * u1[kk].y + w2[kk].x, kap1 * u1[kk].x + w2[kk].y);
+      const float e = efactor(f, sc, k1, kap2);
+      out[kk] = make_float2(e * lam[kk].x - 2.f * sc.a * div.x, e * lam[kk].y - 2.f * sc.a * div.y);
+      if (kk == 4 && t == 0) out[kk] = make_float2(0.f, 0.f);  // k1 = -N1/4 lies outside the box
+    }
+    if (tile == 0) {  // symmetrise column k2 = 0: copy k1 > 0 conjugated onto -k1
+      float2* const sym = lds;  // the first group's area; every read of it is behind a barrier
+      if (m == 0 && h == 0 && act) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) sym[k1_of(kk)] = out[kk];
       }
+      __syncthreads();
+      if (m == 0 && h == 0 && act) {
+#pragma unroll
+        for (int kk = 4; kk < 8; ++kk)
+          if (k1_of(kk) > -N1 / 4) out[kk] = ff::cconj(sym[-k1_of(kk)]);
+        if (t == 0) out[0].y = 0.f;
+      }
+    }
+    if (live && act && h == 0) {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) st(glob(lam_out) + col + k1_of(kk), out[kk]);
+    }
+  }
+}
+
+// ROW_ADJ on 3 N2/4 phi points: per row pair m (both rows in one packed real
+// synthesis, job 0), z = g1 + i g2 of each row (jobs 1 and 2), zeta = m z, and
+// the forward transforms of the two zetas.
+template <int LOGN2, int NG>
+__global__ void __launch_bounds__((AdjMix<LOGN2, NG>::THREADS))
+    __attribute__((amdgpu_waves_per_eu(ADJ_ROW_WAVES_PER_EU)))
+    adjm_row_kernel(const FlameDev* __restrict__ fls) {
+  using C = AdjMix<LOGN2, NG>;
+  using F = typename C::F;
+  using I = typename C::I;
+  constexpr int G = C::G, B = C::T, NB = C::NB;
+  static_assert(I::radix(I::NPASS - 1) == F::radix(0) && I::rounds(I::NPASS - 1) == F::rounds(0),
+                "an inverse's last pass and the forward's first share their register map");
+  extern __shared__ float2 lds[];
+  const FlameDev f = fls[blockIdx.y];
+  const int tid = threadIdx.x;
+  const int p = tid % B, u = tid / B;
+  const int h = u / G, t = u % G;
+  const int pair = xcd_swizzle(blockIdx.x, gridDim.x) * B + p;
+  const int n1 = f.rows, ts = f.tshift, mcols = f.m;
+  const bool live = pair < n1 / 2;
+  const int ja = live ? 2 * pair : 0;  // a pair past the grid reads pair 0 (never stored)
+  float2* const my = lds + p + h * C::AREA;
+  const bool act = G == NB || t < NB;
+  const int jt = act ? t : 0;
+  gf2* const Wp = glob(f.Wp);
+  gf2* const Wm = glob(f.Wm);
+  gf2* const Q = glob(f.Q);
+  auto load_z = [&](float2(&v)[I::REGS], int row) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = ld(Wp + w_index(row, jt + NB * r, mcols));
+#pragma unroll
+    for (int r = 8; r < 12; ++r) {
+      const int mm = NB * (12 - r) - jt;  // k2 = -mm; mm = mcols at r = 8, t = 0
+      v[r] = ld(Wm + w_index(row, r > 8 || jt > 0 ? mm : 0, mcols));
+    }
+  };
+  auto load_m = [&](float2(&v)[I::REGS]) {
+    // Y = X_a + i X_b, X(k2) = M(k2), X(-k2) = conj(M(k2))
+#pragma unroll
+    for (int r = 0; r < 12; ++r) {
+      if (r >= 4 && r < 8) continue;
+      const int mm = NB * (12 - r) - jt;
+      const int k = r < 4 ? jt + NB * r : (r > 8 || jt > 0 ? mm : 0);
+      const float2 a = ld(Q + tiled(ja, k, n1, ts)), b = ld(Q + tiled(ja + 1, k, n1, ts));
+      v[r] = r < 4 ? make_float2(a.x - b.y, a.y + b.x) : make_float2(a.x + b.y, -a.y + b.x);
+    }
+  };
+  // forward transform of zeta and its split by Hermitian symmetry: the row
+  // transform of w1, (Xi(k) + conj(Xi(-k)))/2 -> A1, and of i kappa2 w2,
+  // kappa2 (Xi(k) - conj(Xi(-k)))/2 -> A2 (outputs as in rowm_body)
+  auto forward = [&](float2(&y)[F::REGS], const MixTw<F, C::HELD_ROW>& wf, bool store, int row) {
+    mix_fft<F, false, false>(y, my, wf);
+    if (act) {
+#pragma unroll
+      for (int r = 8; r < 12; ++r) my[(t + NB * (r - 8)) * B] = y[r];
+    }
+    __syncthreads();
+    if (store && act) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = t + NB * r;
+        const float2 xk = y[r];
+        const float2 xo = my[(NB * (4 - r) - t - (k == 0 ? 1 : 0)) * B];
+        const float2 xm = k == 0 ? xk : xo;
+        const float hk = 0.5f * f.s2 * (float)k;
+        st(glob(f.A1) + tiled(row, k, n1, ts), make_float2(0.5f * (xk.x + xm.x), 0.5f * (xk.y - xm.y)));
+        st(glob(f.A2) + tiled(row, k, n1, ts), make_float2(hk * (xk.x - xm.x), hk * (xk.y + xm.y)));
+      }
+    }
+  };
+  constexpr int P = I::NPASS - 1, R = I::radix(P), NV = I::rounds(P) * R;
+  const MixTw<I, C::HELD_ROW> wi(f.twmb, t);
+  const float2* const ftab = f.twmb + ff::MixTables<ff::MixPlan<LOGN2>>::F_OFF;
+  if constexpr (NG == 3) {
+    float2 v[I::REGS];
+    if (h == 0)
+      load_m(v);
+    else
+      load_z(v, ja + h - 1);
+    v[8] = jt > 0 ? v[8] : make_float2(0.f, 0.f);  // the position past the box
+    mix_fft<I, true, true>(v, my, wi);
+    const MixTw<F, C::HELD_ROW> wf(ftab, t);
+    // m to the groups of the two rows, in the first group's area
+    float2* const ms = lds + p;
+    if (h == 0) {
+#pragma unroll
+      for (int b = 0; b < I::rounds(P); ++b)
+        if (I::template active<P>(t, b)) {
+#pragma unroll
+          for (int r = 0; r < R; ++r) ms[(t + G * b + r * I::bf(P)) * B] = v[b * R + r];
+        }
+    }
+    __syncthreads();
+    float2 y[F::REGS];
+#pragma unroll
+    for (int b = 0; b < I::rounds(P); ++b)
+      if (I::template active<P>(t, b)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const float2 mm = ms[(t + G * b + r * I::bf(P)) * B];
+          y[b * R + r] = ff::cscale(v[b * R + r], h == 1 ? mm.x : mm.y);
+        }
+      }
+    __syncthreads();  // the first group's forward pass, which nobody reads, writes its area
+    forward(y, wf, live && h > 0, ja + h - 1);
+  } else {
+    float2 v[I::REGS], z[2][I::REGS];
+    load_z(z[0], ja);
+    load_z(z[1], ja + 1);
+    load_m(v);
+    v[8] = jt > 0 ? v[8] : make_float2(0.f, 0.f);
+    mix_fft<I, true, true>(v, my, wi);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      z[half][8] = jt > 0 ? z[half][8] : make_float2(0.f, 0.f);
+      mix_fft<I, true, true>(z[half], my, wi);
+      float2 y[F::REGS];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) y[i] = ff::cscale(z[half][i], half == 0 ? v[i].x : v[i].y);
+      forward(y, MixTw<F, C::HELD_ROW>(ftab, t), live, ja + half);
+      __syncthreads();  // the next transform writes the exchange area
     }
   }
 }
@@ -477,9 +606,13 @@ template <int LOGN>
 struct AdjRowTable {
   static void launch(int mode, dim3 grid, hipStream_t st, const FlameDev* fl, long long n) {
     constexpr int th = RowCfg<LOGN>::THREADS, lds = RowCfg<LOGN>::LDS_BYTES;
-    if (mode == ROW_ADJ)
-      hipLaunchKernelGGL((adj_row_kernel<LOGN, ROW_ADJ>), grid, dim3(th), lds, st, fl, n);
-    else
+    if constexpr (LOGN < kMinLogRowProduct) {
+      if (mode == ROW_ADJ) {
+        hipLaunchKernelGGL((adj_row_kernel<LOGN, ROW_ADJ>), grid, dim3(th), lds, st, fl, n);
+        return;
+      }
+    }
+    if (mode == ROW_SEED)
       hipLaunchKernelGGL((adj_row_kernel<LOGN, ROW_SEED>), grid, dim3(th), lds, st, fl, n);
   }
 };
@@ -496,24 +629,79 @@ void dispatch_adj(int logn, A... args) {
 
 }  // namespace
 
+namespace {
+
+template <int L, int NG>
+void adjm_col_launch(int mode, int columns, hipStream_t st, const FlameDev* fl, long long n, const float2* s,
+                     const float2* li, float2* lo) {
+  using C = AdjMix<L, NG>;
+  const dim3 grid((columns + C::T - 1) / C::T, 1);
+  if (mode == ADJ_A)
+    hipLaunchKernelGGL((adjm_col_kernel<L, ADJ_A, NG>), grid, dim3(C::THREADS), C::LDS_BYTES, st, fl, n, s, li, lo);
+  else
+    hipLaunchKernelGGL((adjm_col_kernel<L, ADJ_C, NG>), grid, dim3(C::THREADS), C::LDS_BYTES, st, fl, n, s, li, lo);
+}
+
 template <int L>
-void dispatch_adjp(int logn, int mode, dim3 grid, hipStream_t st, const FlameDev* fl, long long n, const float2* s,
-                   const float2* li, float2* lo) {
+void dispatch_adjm_col(int logn, int mode, int columns, hipStream_t st, const FlameDev* fl, long long n,
+                       const float2* s, const float2* li, float2* lo) {
   if constexpr (L <= kMaxLog) {
-    if (logn != L) return dispatch_adjp<L + 1>(logn, mode, grid, st, fl, n, s, li, lo);
-    constexpr int th = ColCfgP<L, 16>::THREADS, lds = ColCfgP<L, 16>::LDS_BYTES;
-    if (mode == ADJ_A)
-      hipLaunchKernelGGL((adjp_col_kernel<L, ADJ_A>), grid, dim3(th), lds, st, fl, n, s, li, lo);
-    else
-      hipLaunchKernelGGL((adjp_col_kernel<L, ADJ_C>), grid, dim3(th), lds, st, fl, n, s, li, lo);
+    if (logn != L) return dispatch_adjm_col<L + 1>(logn, mode, columns, st, fl, n, s, li, lo);
+    if constexpr (L <= 11) {
+      if (split_pays(L, columns, true)) {
+        if (mode == ADJ_A) {
+          using C = AdjMix<L, 3>;
+          hipLaunchKernelGGL((adjm_col_kernel<L, ADJ_A, 3>), dim3((columns + C::T - 1) / C::T, 1), dim3(C::THREADS),
+                             C::LDS_BYTES, st, fl, n, s, li, lo);
+        } else {
+          using C = AdjMix<L, 2>;
+          hipLaunchKernelGGL((adjm_col_kernel<L, ADJ_C, 2>), dim3((columns + C::T - 1) / C::T, 1), dim3(C::THREADS),
+                             C::LDS_BYTES, st, fl, n, s, li, lo);
+        }
+        return;
+      }
+    }
+    adjm_col_launch<L, 1>(mode, columns, st, fl, n, s, li, lo);
   }
 }
+
+template <int L>
+void dispatch_adjm_row(int logn, int pairs, hipStream_t st, const FlameDev* fl) {
+  if constexpr (L <= kMaxLog) {
+    if (logn != L) return dispatch_adjm_row<L + 1>(logn, pairs, st, fl);
+    if constexpr (L <= 11) {
+      if (split_pays(L, pairs, false)) {
+        using C = AdjMix<L, 3>;
+        hipLaunchKernelGGL((adjm_row_kernel<L, 3>), dim3((pairs + C::T - 1) / C::T, 1), dim3(C::THREADS), C::LDS_BYTES,
+                           st, fl);
+        return;
+      }
+    }
+    using C = AdjMix<L, 1>;
+    hipLaunchKernelGGL((adjm_row_kernel<L, 1>), dim3((pairs + C::T - 1) / C::T, 1), dim3(C::THREADS), C::LDS_BYTES, st,
+                       fl);
+  }
+}
+
+template <int L>
+int adj_mixed_lds(int logn) {
+  if constexpr (L <= kMaxLog) {
+    if (logn != L) return adj_mixed_lds<L + 1>(logn);
+    if constexpr (L <= 11) return AdjMix<L, 3>::LDS_BYTES > AdjMix<L, 1>::LDS_BYTES ? AdjMix<L, 3>::LDS_BYTES : AdjMix<L, 1>::LDS_BYTES;
+    return AdjMix<L, 1>::LDS_BYTES;
+  }
+  return 0;
+}
+
+}  // namespace
+
+int adj_mixed_lds_bytes(int logn) { return logn < kMinLogRowProduct ? 0 : adj_mixed_lds<kMinLogRowProduct>(logn); }
 
 void launch_adjp_col(int logn1, int mode, int tiles, hipStream_t st, const FlameDev* fl, long long n,
                      const void* state, const void* lam_in, void* lam_out) {
   if (logn1 < kMinLogProduct || (mode != ADJ_A && mode != ADJ_C)) return;
-  dispatch_adjp<kMinLogProduct>(logn1, mode, dim3(tiles, 1), st, fl, n, static_cast<const float2*>(state),
-                                static_cast<const float2*>(lam_in), static_cast<float2*>(lam_out));
+  dispatch_adjm_col<kMinLogProduct>(logn1, mode, tiles * col_tile(logn1), st, fl, n, static_cast<const float2*>(state),
+                                    static_cast<const float2*>(lam_in), static_cast<float2*>(lam_out));
 }
 
 void launch_adj_col(int logn1, int mode, int tiles, hipStream_t st, const FlameDev* fl, long long n,
@@ -523,6 +711,10 @@ void launch_adj_col(int logn1, int mode, int tiles, hipStream_t st, const FlameD
 }
 
 void launch_adj_row(int logn2, int mode, int groups, hipStream_t st, const FlameDev* fl, long long n) {
+  if (mode == ROW_ADJ && logn2 >= kMinLogRowProduct) {  // as the step's row kernel, on 3 N2/4 points
+    dispatch_adjm_row<kMinLogRowProduct>(logn2, groups * row_pairs(logn2), st, fl);
+    return;
+  }
   dispatch_adj<AdjRowTable, kMinLog>(logn2, mode, dim3(groups, 1), st, fl, n);
 }
 

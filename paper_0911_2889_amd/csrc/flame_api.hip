@@ -102,8 +102,6 @@ struct Layout {
   std::vector<size_t> off_w, off_q, off_a1, off_a2, off_part;
   size_t off_tw[flame::kMaxLog + 1];   // twiddles, 16 points per thread
   size_t off_tw8[flame::kMaxLog + 1];  // twiddles, 8 points per thread
-  size_t off_tw6[flame::kMaxLog + 1];  // twiddles of the length-3N1/4 transform (product grid)
-  size_t off_tw6_8[flame::kMaxLog + 1];
   size_t off_twm[flame::kMaxLog + 1];  // length 3*2^l/4 (product grids)
   size_t off_dev;
   size_t off_dev_full;  // device flame table whose W is the adjoint scratch (physical-grid W for diagnostics)
@@ -117,12 +115,11 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
   if (!descs || nfl <= 0) return fail(FLAME_ERR_INVALID_ARG, "need at least one flame descriptor");
   L->sizes.resize(nfl);
   size_t off = 0;
-  bool need_tw[flame::kMaxLog + 1] = {}, need_tw6[flame::kMaxLog + 1] = {}, need_twm[flame::kMaxLog + 1] = {};
+  bool need_tw[flame::kMaxLog + 1] = {}, need_twm[flame::kMaxLog + 1] = {};
   for (int f = 0; f < nfl; ++f) {
     int rc = check_desc(&descs[f], &L->sizes[f]);
     if (rc) return rc;
     need_tw[L->sizes[f].logn1] = need_tw[L->sizes[f].logn2] = true;
-    need_tw6[L->sizes[f].logn1] = L->sizes[f].logn1 >= flame::kMinLogProduct;
     if (L->sizes[f].logn1 >= flame::kMinLogProduct) need_twm[L->sizes[f].logn1] = true;
     if (L->sizes[f].logn2 >= flame::kMinLogRowProduct) need_twm[L->sizes[f].logn2] = true;
   }
@@ -150,10 +147,6 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
       const ff::PassPlan pp = ff::make_pass_plan(l, 8);
       off = align_up(off + (size_t)(pp.tw_size > 0 ? pp.tw_size : 1) * sizeof(float2));
     }
-    L->off_tw6[l] = off;
-    if (need_tw6[l]) off = align_up(off + (size_t)ff::twiddles6_size(l - 3, 16) * sizeof(float2));
-    L->off_tw6_8[l] = off;
-    if (need_tw6[l]) off = align_up(off + (size_t)ff::twiddles6_size(l - 3, 8) * sizeof(float2));
     L->off_twm[l] = off;
     if (need_twm[l]) off = align_up(off + (size_t)ff::mix_tables_size(l) * sizeof(float2));
   }
@@ -235,8 +228,6 @@ struct flame_plan_s {
   std::vector<flame::FlameDev> hdev;
   std::vector<std::vector<float2>> tw_host;   // host copies of the tables (16 points per thread)
   std::vector<std::vector<float2>> tw_host8;  // 8 points per thread
-  std::vector<std::vector<float2>> tw_host6;  // length-3N1/4 transforms (16 and 8 points per thread)
-  std::vector<std::vector<float2>> tw_host6_8;
   std::vector<std::vector<float2>> tw_hostm;  // length 3*2^l/4
   flame::FlameDev* ddev = nullptr;
   flame::FlameDev* ddev_full = nullptr;       // same flames, W in the adjoint scratch
@@ -879,24 +870,6 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
       }
     }
   }
-  p->tw_host6.resize(flame::kMaxLog + 1);
-  p->tw_host6_8.resize(flame::kMaxLog + 1);
-  for (int l = flame::kMinLogProduct; l <= flame::kMaxLog; ++l) {
-    bool used = false;
-    for (const Sizes& s : L.sizes) used |= s.logn1 == l;
-    if (!used) continue;
-    for (int pts : {16, 8}) {
-      auto& host = pts == 16 ? p->tw_host6[l] : p->tw_host6_8[l];
-      host.assign(ff::twiddles6_size(l - 3, pts), make_float2(1.f, 0.f));
-      ff::build_twiddles6(l - 3, host.data(), pts);
-      e = hipMemcpyAsync(base + (pts == 16 ? L.off_tw6[l] : L.off_tw6_8[l]), host.data(),
-                         host.size() * sizeof(float2), hipMemcpyHostToDevice, p->stream);
-      if (e != hipSuccess) {
-        delete p;
-        return hip_fail(e, "twiddle upload");
-      }
-    }
-  }
   p->tw_hostm.resize(flame::kMaxLog + 1);
   for (int l = flame::kMinLogRowProduct; l <= flame::kMaxLog; ++l) {
     bool used = false;
@@ -932,10 +905,8 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
     fd.tw2 = reinterpret_cast<const float2*>(base + L.off_tw[s.logn2]);
     fd.tw1_8 = reinterpret_cast<const float2*>(base + L.off_tw8[s.logn1]);
     fd.tw2_8 = reinterpret_cast<const float2*>(base + L.off_tw8[s.logn2]);
-    const bool p6 = s.logn1 >= flame::kMinLogProduct;
-    fd.tw6 = p6 ? reinterpret_cast<const float2*>(base + L.off_tw6[s.logn1]) : nullptr;
-    fd.tw6_8 = p6 ? reinterpret_cast<const float2*>(base + L.off_tw6_8[s.logn1]) : nullptr;
-    fd.twma = p6 ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn1]) : nullptr;
+    const bool p1 = s.logn1 >= flame::kMinLogProduct;
+    fd.twma = p1 ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn1]) : nullptr;
     fd.twmb = s.logn2 >= flame::kMinLogRowProduct ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn2]) : nullptr;
     fd.n1 = d.n1;
     fd.n2 = d.n2;

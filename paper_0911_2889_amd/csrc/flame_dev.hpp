@@ -37,8 +37,6 @@ struct FlameDev {
   const float2* tw2;   // twiddles of the length-N2 transform, 16 points per thread
   const float2* tw1_8; // the same for 8 points per thread
   const float2* tw2_8;
-  const float2* tw6;   // twiddles of the length-3N1/4 transform (product grid), or null
-  const float2* tw6_8; // the same for 8 points per thread
   const float2* twma;  // twiddles of the length-3N1/4 transforms (ff::MixTables), or null
   const float2* twmb;  // the same for length 3N2/4
   double* part;        // per-workgroup partial sums of the diagnostics
@@ -110,8 +108,6 @@ struct ColCfg {
 // |k1| <= K1, so the truncated quadratic term is the same as on N1 rows up to
 // rounding. Used for N1 >= 128. The same holds along phi: the step's row
 // kernel forms the term on 3 N2/4 points for N2 >= 64 (mixed_bodies.hpp).
-// ColCfgP is the adjoint's column kernel on that grid: length M1 = 6 * N1/8
-// (Shape6: radix-PTS passes, then radix 6), with G = M1/PTS threads per column.
 constexpr int kMinLogProduct = 7;
 constexpr int kMinLogRowProduct = 6;
 
@@ -131,20 +127,6 @@ constexpr bool split_pays(int logn, long long transforms, bool columns) {
   const long long waves = transforms * ((1 << logn) / 16) / 64;
   return logn <= 11 ? waves <= (columns ? 512 : 1024) : logn == 13 && transforms <= 256;
 }
-
-template <int LOGN1, int PTS = 16>
-struct ColCfgP {
-  using S = ff::Shape6<LOGN1 - 3, PTS>;
-  static constexpr int M1 = S::N;
-  static constexpr int G = S::G;
-  static constexpr int G16 = ff::Shape<LOGN1>::G;
-  static constexpr int T = col_tile_for(G16);
-  static constexpr int TQ = q_tile_for(G16);
-  static constexpr int QS = ff::ilog2c(TQ);
-  static constexpr int THREADS = T * G;
-  static constexpr int LDS_BYTES = S::LDS * T * 8;
-  static_assert(THREADS % 64 == 0, "whole waves");
-};
 
 // Row kernel: B = max(1, 16*256/N2) row pairs per workgroup, interleaved.
 // WPE: the minimum waves per SIMD it is compiled for; at N2 = 8192 with 16

@@ -21,6 +21,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <initializer_list>
 #include <type_traits>
 
 #include "fft_engine.hpp"
@@ -294,8 +295,6 @@ int col_lds(int logn1) {
   if constexpr (L <= kMaxLog) {
     if (logn1 != L) return col_lds<L + 1>(logn1);
     int b = ColCfg<L, 16>::LDS_BYTES > ColCfg<L, 8>::LDS_BYTES ? ColCfg<L, 16>::LDS_BYTES : ColCfg<L, 8>::LDS_BYTES;
-    if constexpr (L >= kMinLogProduct)
-      if (ColCfgP<L, 16>::LDS_BYTES > b) b = ColCfgP<L, 16>::LDS_BYTES;
     return b;
   }
   return 0;
@@ -316,8 +315,10 @@ int row_lds(int logn2) {
 int lds_bytes_needed(int logn1, int logn2) {
   const int c = col_lds<kMinLog>(logn1), r = row_lds<kMinLog>(logn2);
   const int m1 = mixed_lds_bytes(logn1), m2 = mixed_lds_bytes(logn2);
-  const int p = c > r ? c : r, m = m1 > m2 ? m1 : m2;
-  return p > m ? p : m;
+  const int a1 = adj_mixed_lds_bytes(logn1), a2 = adj_mixed_lds_bytes(logn2);
+  int most = c;
+  for (const int b : {r, m1, m2, a1, a2}) most = b > most ? b : most;
+  return most;
 }
 
 KernelLaunch col_step_kernel(int logn1, int pts, int var) {

@@ -53,6 +53,8 @@ void launch_adj_col(int logn1, int mode, int tiles, hipStream_t st, const FlameD
                     const void* state, const void* lam_in, void* lam_out);
 void launch_adj_row(int logn2, int mode, int groups, hipStream_t st, const FlameDev* fl, long long n);
 // ADJ_A / ADJ_C on the product grid (3 N1/4 rows; N1 >= 128), with ROW_ADJ reading the step's row count.
+// adj_mixed_lds_bytes: the most LDS the product-grid adjoint kernels ask for at length 2^logn.
+int adj_mixed_lds_bytes(int logn);
 void launch_adjp_col(int logn1, int mode, int tiles, hipStream_t st, const FlameDev* fl, long long n,
                      const void* state, const void* lam_in, void* lam_out);
 

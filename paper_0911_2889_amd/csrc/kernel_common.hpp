@@ -107,41 +107,6 @@ struct KernelTw {
   }
 };
 
-// Twiddles of a length 6*2^LOGP transform, cached in registers.
-template <int LOGP, int PTS>
-struct KernelTw6 {
-  using Type = ff::RegTwS<ff::Shape6<LOGP, PTS>, GlobalFetch, kTwCacheMinNs>;
-  static __device__ __forceinline__ Type make(const float2* tw, int t) { return Type(GlobalFetch{(const gf2*)tw}, t); }
-};
-
-// Transform of length 6*2^LOGP (ff::Shape6): on entry v[i] holds the input at
-// position t + G*i; on exit o[it*6 + r] holds the output at position
-// j + r*N6, j = t + G*it (zero where j >= N6). Contains workgroup barriers
-// (all threads must call it), the last one after the radix-6 pass has read
-// LDS, so the caller may write LDS at once.
-template <int LOGP, int PTS>
-using Out6 = float2[ff::Shape6<LOGP, PTS>::IT6 * 6];
-template <int PTS>
-using Regs = float2[PTS];
-
-template <int LOGP, bool INV, int PTS, class TW, int P = 0>
-__device__ __forceinline__ void fft6(Regs<PTS>& v, Out6<LOGP, PTS>& o, int t, float2* lds, int stride, const TW& tw) {
-  using S = ff::Shape6<LOGP, PTS>;
-  using F = ff::FftS<S, INV>;
-  if constexpr (P < S::NBF) {
-    F::template butterflies<P, TW, false>(v, t, lds, stride, tw);
-    __syncthreads();
-    if constexpr (P + 1 < S::NBF) {
-      F::template gather<P>(v, t, lds, stride);
-      __syncthreads();
-    }
-    fft6<LOGP, INV, PTS, TW, P + 1>(v, o, t, lds, stride, tw);
-  } else {
-    F::last6(o, t, lds, stride, tw);
-    __syncthreads();
-  }
-}
-
 struct StepScalars {
   float a;    // dt * c_n / P, multiplies the raw transform of |grad Phi|^2
   float i1;   // int_{t_n}^{t_{n+1}} dt / r0

@@ -89,8 +89,12 @@ struct MixTw {
     }
   }
 };
-// (logn, g: the transform's 2^logn and its lanes)
+// Rows (logn, g: the transform's 2^logn and its lanes): reading them late costs
+// 3 % of the row kernel at 2048x4096.
 constexpr bool mix_held(int logn, int g) { return logn < 13 || (logn == 13 && g == 512); }
+// Columns: up to 1024 points the registers are worth more as further waves
+// (32 flames of 512x1024: column kernel 25.6 -> 24.0 us).
+constexpr bool mix_held_col(int logn, int g) { return logn > 10 && mix_held(logn, g); }
 
 // Run passes P.. of a transform whose pass-P inputs are in x (every thread of
 // the workgroup calls it: it contains workgroup barriers; the last one is
@@ -140,7 +144,7 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
   constexpr int KEEP = 8 * RB;
 
   float2 sv[KEEP];
-  MixTw<I, mix_held(LOGN1, G_)> wi;
+  MixTw<I, mix_held_col(LOGN1, G_)> wi;
   if constexpr (MODE == COL_STEP) {
     gf2* const Qc = glob(f.Q) + ((((size_t)m >> QS) * L) << QS) + (m & (TQ - 1));  // column m: Qc[j1 * TQ]
     gf2* const Pc = glob(VAR >= VAR_HEUN_P ? f.S2 : f.S) + (size_t)m * f.h1 + N1 / 4;  // Heun's predictor
@@ -167,7 +171,7 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
       prd[kk] = VAR == VAR_HEUN_C ? ld(Pl + k1_of(kk)) : make_float2(0.f, 0.f);
     }
     wi.init(f.twma, t);
-    mix_fft<F, false, false>(v, my, MixTw<F, mix_held(LOGN1, G_)>(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, t));
+    mix_fft<F, false, false>(v, my, MixTw<F, mix_held_col(LOGN1, G_)>(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, t));
     const StepScalars sc = step_scalars(f, n, L, f.cols);
     const float ac = VAR == VAR_HEUN_C ? step_scalars(f, n + 1, L, f.cols).a : 0.f;  // the corrector's dt c_{n+1} / P
     const float kap2c = f.s2 * (float)m;
