@@ -103,6 +103,7 @@ struct Layout {
   size_t off_tw[flame::kMaxLog + 1];   // twiddles, 16 points per thread
   size_t off_tw8[flame::kMaxLog + 1];  // twiddles, 8 points per thread
   size_t off_twm[flame::kMaxLog + 1];  // length 3*2^l/4 (product grids)
+  size_t off_twf[flame::kMaxLog + 1];  // length 2^l <= 64, ff::FullPlan (resident kernels)
   size_t off_dev;
   size_t off_dev_full;  // device flame table whose W is the adjoint scratch (physical-grid W for diagnostics)
   size_t off_counter;  // step index read by graph replays
@@ -150,6 +151,10 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
     L->off_twm[l] = off;
     if (need_twm[l]) off = align_up(off + (size_t)ff::mix_tables_size(l) * sizeof(float2));
   }
+  for (int l = flame::kMinLog; l <= flame::kMaxLogFull; ++l) {
+    L->off_twf[l] = off;
+    if (need_tw[l]) off = align_up(off + (size_t)std::max(1, ff::mix_tables_size(l, true)) * sizeof(float2));
+  }
   L->off_dev = off;
   off = align_up(off + (size_t)nfl * sizeof(flame::FlameDev));
   L->off_dev_full = off;
@@ -195,6 +200,16 @@ struct Group {
     if (!product || col_pts != ff::kPts) return col_pts;
     return flame::split_pays(logn1, (long long)flames << (logn2 - 2), true) ? 8 : ff::kPts;
   }
+  // The kernel that steps each flame of the group on one workgroup, if there is
+  // one: for the default grid and points per thread. The store kind does not
+  // matter to it (it stores no intermediates).
+  flame::KernelLaunch resident() const {
+    if (!flame::resident_kernel || col_pts != ff::kPts || row_pts != ff::kPts ||
+        product != (logn1 >= flame::kMinLogProduct))
+      return flame::KernelLaunch{nullptr, 0, 0};
+    return flame::resident_kernel(logn1, logn2,
+                                  integrator == 1 ? flame::VAR_HEUN_P : forced ? flame::VAR_EULER_F : flame::VAR_EULER);
+  }
   int row_kernel_pts(int flames) const {
     if (logn2 < flame::kMinLogRowProduct || row_pts != ff::kPts) return row_pts;
     return flame::split_pays(logn2, (long long)flames * rows() / 2, false) ? 8 : ff::kPts;
@@ -229,6 +244,7 @@ struct flame_plan_s {
   std::vector<std::vector<float2>> tw_host;   // host copies of the tables (16 points per thread)
   std::vector<std::vector<float2>> tw_host8;  // 8 points per thread
   std::vector<std::vector<float2>> tw_hostm;  // length 3*2^l/4
+  std::vector<float2> tw_hostf[flame::kMaxLogFull + 1];  // length 2^l, ff::FullPlan
   flame::FlameDev* ddev = nullptr;
   flame::FlameDev* ddev_full = nullptr;       // same flames, W in the adjoint scratch
   std::vector<flame::FlameDev> hdev_full;
@@ -412,6 +428,47 @@ void launch_step_col(flame_plan p, const Group& gr, long long n, int pass, hipEv
                       nullptr, gr.col_pts, e0, e1, gr.col_var(pass));
 }
 
+// Steps n .. n + k - 1 of group gr (dn = 1), or k steps at index n (dn = 0,
+// for timing), on the plan's stream unless `st` is given: one launch for the
+// small flames that have a resident kernel, else a row and a column kernel per
+// pass of each step.
+void launch_resident(const flame::KernelLaunch& kl, int flames, const flame::FlameDev* fl, long long n, int k, int dn,
+                     hipStream_t st) {
+  for (int done = 0; done < k;) {
+    const int steps = std::min(k - done, flame::kResMaxSteps);
+    flame::resident_launch(kl, flames, st, fl, n + (long long)done * dn, steps, dn);
+    done += steps;
+  }
+}
+
+void launch_group_steps(flame_plan p, const Group& gr, long long n, int k, int dn, hipStream_t st = nullptr) {
+  const flame::KernelLaunch kl = gr.resident();
+  if (kl.func) {
+    launch_resident(kl, gr.count, p->ddev + gr.first, n, k, dn, st ? st : p->stream);
+    return;
+  }
+  for (int s = 0; s < k; ++s)
+    for (int pass = 0; pass < gr.passes(); ++pass) {
+      launch_step_row(p, gr, n + (long long)s * dn, nullptr, nullptr, st);
+      launch_step_col(p, gr, n + (long long)s * dn, pass, nullptr, nullptr, st);
+    }
+}
+
+// The column transforms of every flame whose intermediates are stale (a
+// resident kernel forms its own and leaves them stale).
+int rebuild_stale(flame_plan p) {
+  for (const Group& gr : p->groups) {
+    const bool own = gr.resident().func != nullptr;
+    for (int f = gr.first; f < gr.first + gr.count; ++f) {
+      if (own) p->w_valid[f] = 0;
+      if (own || p->w_valid[f]) continue;
+      const int rc = rebuild_w(p, f);
+      if (rc) return rc;
+    }
+  }
+  return FLAME_OK;
+}
+
 // Destroy the step graph. A replay may still run on the plan's stream (or
 // the runtime may still hold it), so the stream is drained first.
 void drop_graph(flame_plan p) {
@@ -490,9 +547,32 @@ int build_graph(flame_plan p) {
     const Group &ga = p->groups[a], &gb = p->groups[b];
     return (long long)ga.count << (ga.logn1 + ga.logn2) > (long long)gb.count << (gb.logn1 + gb.logn2);
   });
+  for (const size_t gi : order) {  // a resident kernel runs all its steps as one node
+    const Group& gr = p->groups[gi];
+    const flame::KernelLaunch kl = gr.resident();
+    if (!kl.func) continue;
+    const flame::FlameDev* fl = p->ddev + gr.first;
+    for (int done = 0; done < p->graph_steps;) {
+      long long n = done;
+      const long long* nb = p->counter;
+      int steps = std::min(p->graph_steps - done, flame::kResMaxSteps), dn = 1;
+      void* args[] = {&fl, &n, &nb, &steps, &dn};
+      hipKernelNodeParams kp{};
+      kp.func = const_cast<void*>(kl.func);
+      kp.gridDim = dim3(gr.count);
+      kp.blockDim = dim3(kl.threads);
+      kp.sharedMemBytes = kl.lds;
+      kp.kernelParams = args;
+      hipGraphNode_t kn;
+      e = hipGraphAddKernelNode(&kn, p->graph, last[gi] ? &last[gi] : nullptr, last[gi] ? 1 : 0, &kp);
+      if (e != hipSuccess) return hip_fail(e, "hipGraphAddKernelNode (resident)");
+      last[gi] = kn;
+      done += steps;
+    }
+  }
   for (int s = 0; s < p->graph_steps; ++s)
     for (const size_t gi : order)
-      for (int pass = 0; pass < p->groups[gi].passes(); ++pass) {
+      for (int pass = 0; !p->groups[gi].resident().func && pass < p->groups[gi].passes(); ++pass) {
         const int rc = add_pass(gi, s, pass);
         if (rc) return rc;
       }
@@ -571,9 +651,9 @@ TwSpec tw_spec_pow2(float2* out, int logn, int pts) {
   return s;
 }
 
-// One direction's plan of length 3 * 2^logn / 4 (ff::MixPlan).
-TwSpec tw_spec_mixed(float2* out, int logn, bool forward) {
-  const ff::MixPassList l = ff::mix_passes(logn, forward);
+// One direction's plan of length 3 * 2^logn / 4 (ff::MixPlan), or 2^logn (ff::FullPlan).
+TwSpec tw_spec_mixed(float2* out, int logn, bool forward, bool full) {
+  const ff::MixPassList l = ff::mix_passes(logn, forward, full);
   TwSpec s{};
   s.out = out;
   s.npass = l.npass;
@@ -689,20 +769,23 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   auto add_table = [&](const TwSpec& t, bool last) {
     tw_off[specs.ntab] = off;
     specs.t[specs.ntab++] = t;
-    off += (size_t)std::max(t.count, 1) * sizeof(float2);
+    off += (size_t)t.count * sizeof(float2);
     if (last) off = align_up(off);
   };
-  auto add_mixed = [&](int logn) {  // ff::build_mix_tables: the inverse plan's table, then the forward plan's
-    add_table(tw_spec_mixed(nullptr, logn, false), false);
-    add_table(tw_spec_mixed(nullptr, logn, true), true);
+  auto add_mixed = [&](int logn, bool full) {  // ff::build_mix_tables: the inverse plan's table, then the forward plan's
+    add_table(tw_spec_mixed(nullptr, logn, false, full), false);
+    add_table(tw_spec_mixed(nullptr, logn, true, full), true);
   };
   // pointers are filled in once the scratch address is known
   const bool product2 = s.logn2 >= flame::kMinLogRowProduct;
+  Group gr{s.logn1, s.logn2, 0, 1, s.tiles, s.rpairs};
+  gr.product = product;
+  const flame::KernelLaunch res = gr.resident();
   const size_t tw_col_off = off;
-  if (product) add_mixed(s.logn1);
+  if (product || res.func) add_mixed(s.logn1, !product);
   else add_table(tw_spec_pow2(nullptr, s.logn1, ff::kPts), true);
   const size_t tw_row_off = off;
-  if (product2) add_mixed(s.logn2);
+  if (product2 || res.func) add_mixed(s.logn2, !product2);
   else add_table(tw_spec_pow2(nullptr, s.logn2, ff::kPts), true);
   const size_t off_w = off;
   off = align_up(off + 2 * wq * sizeof(float2));
@@ -735,9 +818,9 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   fd.Q = reinterpret_cast<float2*>(base + off_q);
   const float2* tw_col = reinterpret_cast<const float2*>(base + tw_col_off);
   const float2* tw_row = reinterpret_cast<const float2*>(base + tw_row_off);
-  fd.tw1 = product ? nullptr : tw_col;
+  fd.tw1 = fd.twfa = product ? nullptr : tw_col;  // the table of whichever kernels run
   fd.twma = product ? tw_col : nullptr;
-  fd.tw2 = product2 ? nullptr : tw_row;
+  fd.tw2 = fd.twfb = product2 ? nullptr : tw_row;
   fd.twmb = product2 ? tw_row : nullptr;
   fd.n1 = desc->n1;
   fd.n2 = desc->n2;
@@ -759,9 +842,12 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   hipLaunchKernelGGL(noalloc_setup_kernel, dim3(32), dim3(256), 0, st, fd, dfl, specs);
   rc = last_launch("flame_step_noalloc setup launch");
   if (rc) return rc;
-  // W from the state, then the steps (the kernel sequence of flame_step)
-  Group gr{s.logn1, s.logn2, 0, 1, s.tiles, s.rpairs};
-  gr.product = product;
+  // the kernel sequence of flame_step: a small flame's steps in one launch, or
+  // W from the state and then the steps
+  if (res.func) {
+    if (nsteps > 0) launch_resident(res, 1, dfl, n, nsteps, 1, st);
+    return last_launch("flame_step_noalloc launch");
+  }
   if (product)
     flame::launch_colp(s.logn1, flame::COL_FIRST, s.tiles, 1, st, dfl, n, nullptr, gr.col_kernel_pts(1));
   else
@@ -886,6 +972,20 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
       return hip_fail(e, "twiddle upload");
     }
   }
+  for (int l = flame::kMinLog; l <= flame::kMaxLogFull; ++l) {
+    bool used = false;
+    for (const Sizes& s : L.sizes) used |= s.logn1 == l || s.logn2 == l;
+    if (!used) continue;
+    auto& host = p->tw_hostf[l];
+    host.assign(std::max(1, ff::mix_tables_size(l, true)), make_float2(1.f, 0.f));
+    ff::build_mix_tables(l, host.data(), true);
+    e = hipMemcpyAsync(base + L.off_twf[l], host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice,
+                       p->stream);
+    if (e != hipSuccess) {
+      delete p;
+      return hip_fail(e, "twiddle upload");
+    }
+  }
   // device flame table, ordered so that flames of one grid size are contiguous
   p->hdev.resize(n_flames);
   for (int f = 0; f < n_flames; ++f) {
@@ -908,6 +1008,8 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
     const bool p1 = s.logn1 >= flame::kMinLogProduct;
     fd.twma = p1 ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn1]) : nullptr;
     fd.twmb = s.logn2 >= flame::kMinLogRowProduct ? reinterpret_cast<const float2*>(base + L.off_twm[s.logn2]) : nullptr;
+    fd.twfa = s.logn1 <= flame::kMaxLogFull ? reinterpret_cast<const float2*>(base + L.off_twf[s.logn1]) : nullptr;
+    fd.twfb = s.logn2 <= flame::kMaxLogFull ? reinterpret_cast<const float2*>(base + L.off_twf[s.logn2]) : nullptr;
     fd.n1 = d.n1;
     fd.n2 = d.n2;
     fd.m = d.n2 / 4;
@@ -1246,11 +1348,8 @@ int flame_step(flame_plan p, int32_t nsteps) {
     if (rc) return rc;
   }
   DeviceGuard g(p->device);
-  for (int f = 0; f < p->nfl; ++f)
-    if (!p->w_valid[f]) {
-      rc = rebuild_w(p, f);
-      if (rc) return rc;
-    }
+  rc = rebuild_stale(p);
+  if (rc) return rc;
   if (p->persistent) return nsteps > 0 ? ens_steps(p, nsteps) : FLAME_OK;
   if (p->graph_steps > 0 && nsteps >= p->graph_steps) {
     if (!p->graph_exec) {
@@ -1270,17 +1369,27 @@ int flame_step(flame_plan p, int32_t nsteps) {
     }
   }
   break_chain(p);
-  int max_passes = 1;
-  for (const Group& gr : p->groups) max_passes = std::max(max_passes, gr.passes());
-  for (int s = 0; s < nsteps; ++s) {
+  int max_passes = 0;  // of the groups that step launch by launch
+  for (const Group& gr : p->groups) {
+    const flame::KernelLaunch kl = gr.resident();
+    if (!kl.func) {
+      max_passes = std::max(max_passes, gr.passes());
+    } else if (nsteps > 0) {
+      Timed tm(p, KIND_GRAPH);
+      launch_resident(kl, gr.count, p->ddev + gr.first, p->n, nsteps, 1, p->stream);
+    }
+  }
+  break_chain(p);
+  if (max_passes == 0) p->n += nsteps;
+  for (int s = 0; max_passes > 0 && s < nsteps; ++s) {
     for (int pass = 0; pass < max_passes; ++pass) {
       for (const Group& gr : p->groups) {
-        if (pass >= gr.passes()) continue;
+        if (pass >= gr.passes() || gr.resident().func) continue;
         KernelEvents ev(p, KIND_ROW);
         launch_step_row(p, gr, p->n, ev.start, ev.stop);
       }
       for (const Group& gr : p->groups) {
-        if (pass >= gr.passes()) continue;
+        if (pass >= gr.passes() || gr.resident().func) continue;
         KernelEvents ev(p, KIND_COL);
         launch_step_col(p, gr, p->n, pass, ev.start, ev.stop);
       }
@@ -1632,23 +1741,15 @@ static int autotune_jointly(flame_plan p, int steps, long long n0, hipEvent_t ev
   }
   if (e != hipSuccess) rc = hip_fail(e, "autotune streams");
   auto trial = [&](float* ms) -> int {
-    for (int f = 0; f < p->nfl; ++f)
-      if (!p->w_valid[f]) {
-        const int r = rebuild_w(p, f);
-        if (r) return r;
-      }
+    const int r = rebuild_stale(p);
+    if (r) return r;
     float best = 1e30f;
     for (int rep = 0; rep < 3; ++rep) {  // the first repetition warms up
       hipError_t e2 = hipEventRecord(ev0, p->stream);
       if (e2 == hipSuccess) e2 = hipEventRecord(fork, p->stream);
       for (size_t gi = 0; e2 == hipSuccess && gi < ng; ++gi) {
         e2 = hipStreamWaitEvent(st[gi], fork, 0);
-        const Group& gr = p->groups[gi];
-        for (int s = 0; e2 == hipSuccess && s < steps; ++s)
-          for (int pass = 0; pass < gr.passes(); ++pass) {
-            launch_step_row(p, gr, n0, nullptr, nullptr, st[gi]);
-            launch_step_col(p, gr, n0, pass, nullptr, nullptr, st[gi]);
-          }
+        if (e2 == hipSuccess) launch_group_steps(p, p->groups[gi], n0, steps, 0, st[gi]);
         if (e2 == hipSuccess) e2 = hipEventRecord(done[gi], st[gi]);
         if (e2 == hipSuccess) e2 = hipStreamWaitEvent(p->stream, done[gi], 0);
       }
@@ -1715,18 +1816,12 @@ static int autotune_alone(flame_plan p, size_t gi, int steps, long long n0, hipE
   const Group& gr = p->groups[gi];
   auto time_cfg = [&](const TuneCfg& cf, float* out) -> int {
     int rc = tune_select(p, gi, cf);
-    for (int f = gr.first; rc == FLAME_OK && f < gr.first + gr.count; ++f)
-      if (!p->w_valid[f]) rc = rebuild_w(p, f);
+    if (rc == FLAME_OK) rc = rebuild_stale(p);
     if (rc) return rc;
     // one untimed step, then `steps` timed steps of this group alone
-    hipError_t e = hipSuccess;
-    for (int s = 0; s <= steps; ++s) {
-      if (s == 1) e = hipEventRecord(ev0, p->stream);
-      for (int pass = 0; pass < gr.passes(); ++pass) {
-        launch_step_row(p, gr, n0);
-        launch_step_col(p, gr, n0, pass);
-      }
-    }
+    launch_group_steps(p, gr, n0, 1, 0);
+    hipError_t e = hipEventRecord(ev0, p->stream);
+    launch_group_steps(p, gr, n0, steps, 0);
     if (e == hipSuccess) e = hipEventRecord(ev1, p->stream);
     if (e == hipSuccess) e = hipEventSynchronize(ev1);
     float ms = 0.f;
@@ -1799,8 +1894,7 @@ int flame_autotune(flame_plan p, int32_t steps, int32_t* n_configs_tried) {
   drop_graph(p);
   p->graph_steps = 0;
   int tried = 0;
-  for (int f = 0; rc == FLAME_OK && f < p->nfl; ++f)
-    if (!p->w_valid[f]) rc = rebuild_w(p, f);
+  if (rc == FLAME_OK) rc = rebuild_stale(p);
   for (size_t gi = 0; rc == FLAME_OK && gi < p->groups.size(); ++gi)
     rc = autotune_alone(p, gi, steps, n0, ev0, ev1, &tried);
   if (rc == FLAME_OK && saved_graph > 0 && p->groups.size() > 1) rc = autotune_jointly(p, steps, n0, ev0, ev1);

@@ -39,6 +39,8 @@ struct FlameDev {
   const float2* tw2_8;
   const float2* twma;  // twiddles of the length-3N1/4 transforms (ff::MixTables), or null
   const float2* twmb;  // the same for length 3N2/4
+  const float2* twfa;  // twiddles of the length-N1 transforms of ff::FullPlan (N1 <= 64), or null
+  const float2* twfb;  // the same for length N2
   double* part;        // per-workgroup partial sums of the diagnostics
   const double* r0tab; // reference-radius table {r0(t_n), I1_n, I2_n} (r0_law = 1), or null for r0 = t
   long long r0n;       // its entries
@@ -110,6 +112,14 @@ struct ColCfg {
 // kernel forms the term on 3 N2/4 points for N2 >= 64 (mixed_bodies.hpp).
 constexpr int kMinLogProduct = 7;
 constexpr int kMinLogRowProduct = 6;
+
+// Resident kernels (resident_kernel.hip) exist for N1 N2 <= 2^kResMaxLogs and
+// where a flame's intermediates fit one workgroup's LDS.
+constexpr int kResMaxLogs = 14;
+// Steps per resident launch at most.
+constexpr int kResMaxSteps = 2000;
+// FullPlan twiddles exist for lengths up to 2^kMaxLogFull.
+constexpr int kMaxLogFull = 6;
 
 // Whether a step kernel on a product grid runs the bodies for few transforms
 // (mixed_bodies.hpp, "few transforms"): `transforms` columns or row pairs of

@@ -27,6 +27,15 @@ void launch_set_step(hipStream_t st, long long* counter, long long value);
 // asks for (row, column, product-grid and adjoint kernels, every variant).
 int lds_bytes_needed(int logn1, int logn2);
 
+// The kernel that runs every step of a call on one workgroup per flame (grid:
+// flames; arguments: fls, n, nbase, steps, dn), for a flame of the default
+// configuration; var: VAR_EULER, VAR_EULER_F or VAR_HEUN_P. func is null
+// where there is none. Set by resident_kernel.hip as it is loaded.
+inline KernelLaunch (*resident_kernel)(int logn1, int logn2, int var) = nullptr;
+// Launches it for `flames` flames (steps at most kResMaxSteps).
+inline void (*resident_launch)(const KernelLaunch& kl, int flames, hipStream_t st, const FlameDev* fl, long long n,
+                               int steps, int dn) = nullptr;
+
 // Column kernel over `tiles` tiles of T columns for `nfl` flames of one size
 // (fl points at their consecutive FlameDev entries in device memory). src,
 // if not null, replaces the state read by COL_FIRST and COL_SYNTH.
