@@ -91,8 +91,8 @@ int check_desc(const flame_desc* d, Sizes* s) {
     const int qcols = (m + s->tq - 1) / s->tq * s->tq;
     s->wq_elems = (size_t)std::max(s->tiles * s->tcol, qcols) * d->n1;
     const long long spec = (long long)m * (d->n1 / 2);
-    s->n_spec = (int)std::min<long long>(1024, (spec + flame::kDiagThreads - 1) / flame::kDiagThreads);
-    s->part_elems = (size_t)s->rgroups + 2 * (size_t)s->n_spec;
+    s->n_spec = (int)std::min<long long>(256, (spec + 1023) / 1024);
+    s->part_elems = (size_t)(d->n1 / 2) + 2 * (size_t)s->n_spec;  // at most one area workgroup per row pair
   }
   return FLAME_OK;
 }
@@ -104,8 +104,10 @@ struct Layout {
   size_t off_tw8[flame::kMaxLog + 1];  // twiddles, 8 points per thread
   size_t off_twm[flame::kMaxLog + 1];  // length 3*2^l/4 (product grids)
   size_t off_twf[flame::kMaxLog + 1];  // length 2^l <= 64, ff::FullPlan (resident kernels)
+  size_t off_tables;   // start of what flame_init uploads: the tables, the flame tables and the tickets, to off_counter
   size_t off_dev;
   size_t off_dev_full;  // device flame table whose W is the adjoint scratch (physical-grid W for diagnostics)
+  size_t off_ticket;   // the diagnostics' counters (FlameDev::ticket)
   size_t off_counter;  // step index read by graph replays
   size_t off_diag;     // 4 doubles per flame: flame_diagnostics_host's device copy
   size_t off_ens_items, off_ens_arrive, off_ens_err;  // persistent ensemble launch
@@ -137,6 +139,7 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
     L->off_part.push_back(off);
     off = align_up(off + s.part_elems * sizeof(double));
   }
+  L->off_tables = off;
   for (int l = 0; l <= flame::kMaxLog; ++l) {
     L->off_tw[l] = off;
     if (need_tw[l]) {
@@ -159,6 +162,8 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
   off = align_up(off + (size_t)nfl * sizeof(flame::FlameDev));
   L->off_dev_full = off;
   off = align_up(off + (size_t)nfl * sizeof(flame::FlameDev));
+  L->off_ticket = off;
+  off = align_up(off + (size_t)(flame::kTickets + 1) * flame::kTicketStride * sizeof(unsigned));
   L->off_counter = off;
   off = align_up(off + sizeof(long long));
   L->off_diag = off;
@@ -241,10 +246,6 @@ struct flame_plan_s {
   std::vector<flame_desc> descs;
   Layout layout;
   std::vector<flame::FlameDev> hdev;
-  std::vector<std::vector<float2>> tw_host;   // host copies of the tables (16 points per thread)
-  std::vector<std::vector<float2>> tw_host8;  // 8 points per thread
-  std::vector<std::vector<float2>> tw_hostm;  // length 3*2^l/4
-  std::vector<float2> tw_hostf[flame::kMaxLogFull + 1];  // length 2^l, ff::FullPlan
   flame::FlameDev* ddev = nullptr;
   flame::FlameDev* ddev_full = nullptr;       // same flames, W in the adjoint scratch
   std::vector<flame::FlameDev> hdev_full;
@@ -936,55 +937,23 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
   p->w_valid.assign(n_flames, 0);
   char* base = static_cast<char*>(ws);
   const Layout& L = p->layout;
-  // twiddle tables, built in double precision and rounded once
-  p->tw_host.resize(flame::kMaxLog + 1);
-  p->tw_host8.resize(flame::kMaxLog + 1);
+  // everything flame_init uploads, as one host image and one copy: the twiddle
+  // tables (built in double precision and rounded once), the flame tables and
+  // the tickets (zero)
+  std::vector<char> image(L.off_counter - L.off_tables, 0);
+  auto at = [&](size_t off) { return reinterpret_cast<float2*>(image.data() + (off - L.off_tables)); };
   for (int l = flame::kMinLog; l <= flame::kMaxLog; ++l) {
-    bool used = false;
-    for (const Sizes& s : L.sizes) used |= (s.logn1 == l || s.logn2 == l);
-    if (!used) continue;
-    for (int pts : {16, 8}) {
-      auto& host = pts == 16 ? p->tw_host[l] : p->tw_host8[l];
-      const ff::PassPlan pp = ff::make_pass_plan(l, pts);
-      host.assign(pp.tw_size > 0 ? pp.tw_size : 1, make_float2(1.f, 0.f));
-      ff::build_twiddles(l, host.data(), pts);
-      e = hipMemcpyAsync(base + (pts == 16 ? L.off_tw[l] : L.off_tw8[l]), host.data(), host.size() * sizeof(float2),
-                         hipMemcpyHostToDevice, p->stream);
-      if (e != hipSuccess) {
-        delete p;
-        return hip_fail(e, "twiddle upload");
-      }
+    bool axis1 = false, axis2 = false;
+    for (const Sizes& s : L.sizes) {
+      axis1 |= s.logn1 == l;
+      axis2 |= s.logn2 == l;
     }
-  }
-  p->tw_hostm.resize(flame::kMaxLog + 1);
-  for (int l = flame::kMinLogRowProduct; l <= flame::kMaxLog; ++l) {
-    bool used = false;
-    for (const Sizes& s : L.sizes)
-      used |= (s.logn1 == l && l >= flame::kMinLogProduct) || s.logn2 == l;
-    if (!used) continue;
-    auto& host = p->tw_hostm[l];
-    host.assign(ff::mix_tables_size(l), make_float2(1.f, 0.f));
-    ff::build_mix_tables(l, host.data());
-    e = hipMemcpyAsync(base + L.off_twm[l], host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice,
-                       p->stream);
-    if (e != hipSuccess) {
-      delete p;
-      return hip_fail(e, "twiddle upload");
-    }
-  }
-  for (int l = flame::kMinLog; l <= flame::kMaxLogFull; ++l) {
-    bool used = false;
-    for (const Sizes& s : L.sizes) used |= s.logn1 == l || s.logn2 == l;
-    if (!used) continue;
-    auto& host = p->tw_hostf[l];
-    host.assign(std::max(1, ff::mix_tables_size(l, true)), make_float2(1.f, 0.f));
-    ff::build_mix_tables(l, host.data(), true);
-    e = hipMemcpyAsync(base + L.off_twf[l], host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice,
-                       p->stream);
-    if (e != hipSuccess) {
-      delete p;
-      return hip_fail(e, "twiddle upload");
-    }
+    if (!axis1 && !axis2) continue;
+    ff::build_twiddles(l, at(L.off_tw[l]), 16);
+    ff::build_twiddles(l, at(L.off_tw8[l]), 8);
+    if ((axis1 && l >= flame::kMinLogProduct) || (axis2 && l >= flame::kMinLogRowProduct))
+      ff::build_mix_tables(l, at(L.off_twm[l]));
+    if (l <= flame::kMaxLogFull) ff::build_mix_tables(l, at(L.off_twf[l]), true);
   }
   // device flame table, ordered so that flames of one grid size are contiguous
   p->hdev.resize(n_flames);
@@ -1001,6 +970,7 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
     fd.A2 = reinterpret_cast<float2*>(base + L.off_a2[f]);
     fd.S2 = fd.A2;  // Heun's predictor: A2 is free between the calls that use it
     fd.part = reinterpret_cast<double*>(base + L.off_part[f]);
+    fd.ticket = reinterpret_cast<unsigned*>(base + L.off_ticket);
     fd.tw1 = reinterpret_cast<const float2*>(base + L.off_tw[s.logn1]);
     fd.tw2 = reinterpret_cast<const float2*>(base + L.off_tw[s.logn2]);
     fd.tw1_8 = reinterpret_cast<const float2*>(base + L.off_tw8[s.logn1]);
@@ -1057,15 +1027,14 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
   p->d_items = reinterpret_cast<flame::EnsembleItem*>(base + L.off_ens_items);
   p->d_arrive = reinterpret_cast<unsigned*>(base + L.off_ens_arrive);
   p->d_err = reinterpret_cast<int*>(base + L.off_ens_err);
-  e = hipMemcpyAsync(p->ddev, p->hdev.data(), sizeof(flame::FlameDev) * n_flames, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(p->ddev_full, p->hdev_full.data(), sizeof(flame::FlameDev) * n_flames, hipMemcpyHostToDevice,
-                       p->stream);
+  std::memcpy(image.data() + (L.off_dev - L.off_tables), p->hdev.data(), sizeof(flame::FlameDev) * n_flames);
+  std::memcpy(image.data() + (L.off_dev_full - L.off_tables), p->hdev_full.data(), sizeof(flame::FlameDev) * n_flames);
+  e = hipMemcpyAsync(base + L.off_tables, image.data(), image.size(), hipMemcpyHostToDevice, p->stream);
   if (e != hipSuccess) {
     delete p;
-    return hip_fail(e, "flame table upload");
+    return hip_fail(e, "table upload");
   }
-  // the host copies must outlive the asynchronous uploads
+  // the image must outlive the asynchronous upload
   e = hipStreamSynchronize(p->stream);
   if (e != hipSuccess) {
     delete p;
@@ -1418,10 +1387,8 @@ int flame_diagnostics(flame_plan p, int32_t flame, double* out4, void* dJ_dstate
     Timed tm(p, KIND_OTHER);
     flame::FlameDev* fd = product ? p->ddev_full + flame : p->ddev + flame;
     if (product) flame::launch_col(s.logn1, flame::COL_FIRST, s.tiles, 1, p->stream, fd, p->n);
-    flame::launch_row(s.logn2, flame::ROW_DIAG, s.rgroups, 1, p->stream, fd, p->n, nullptr, nullptr);
-    double* part = p->hdev[flame].part;
-    flame::launch_diag_spectral(p->stream, p->ddev, flame, s.n_spec, part + s.rgroups);
-    flame::launch_diag_final(p->stream, p->ddev, flame, p->n, s.rgroups, s.n_spec, out4);
+    flame::launch_row(s.logn2, flame::ROW_DIAG, s.rgroups, 1, p->stream, fd, p->n, nullptr,
+                      reinterpret_cast<float*>(out4), s.n_spec);
   }
   break_chain(p);
   rc = last_launch("diagnostics launch");

@@ -42,6 +42,8 @@ struct FlameDev {
   const float2* twfa;  // twiddles of the length-N1 transforms of ff::FullPlan (N1 <= 64), or null
   const float2* twfb;  // the same for length N2
   double* part;        // per-workgroup partial sums of the diagnostics
+  unsigned* ticket;    // counters of the workgroups of a diagnostics launch that have finished: a
+                       // master and kTickets others, kTicketStride apart, zero between launches
   const double* r0tab; // reference-radius table {r0(t_n), I1_n, I2_n} (r0_law = 1), or null for r0 = t
   long long r0n;       // its entries
   const float2* F;     // forcing f~ of Eq. (1) in the state layout [M][H1], or null (f~ = 0)
@@ -112,6 +114,9 @@ struct ColCfg {
 // kernel forms the term on 3 N2/4 points for N2 >= 64 (mixed_bodies.hpp).
 constexpr int kMinLogProduct = 7;
 constexpr int kMinLogRowProduct = 6;
+
+// One set of counters per plan (its launches follow each other on one stream).
+constexpr unsigned kTickets = 32, kTicketStride = 32;
 
 // Resident kernels (resident_kernel.hip) exist for N1 N2 <= 2^kResMaxLogs and
 // where a flame's intermediates fit one workgroup's LDS.
@@ -200,7 +205,6 @@ constexpr int kMaxLog = 14;
 // Lengths up to 2^kMaxLog8 have the 8-points-per-thread kernels (beyond it
 // they would need more than 1024 threads per workgroup).
 constexpr int kMaxLog8 = 13;
-constexpr int kDiagThreads = 256;
 
 // Persistent ensemble kernel: one co-resident grid of workgroups steps every
 // flame of a plan for all steps of a launch. A workgroup's share is either

@@ -45,108 +45,7 @@ __global__ void __launch_bounds__((RowCfg<LOGN2, PTS>::THREADS)) __attribute__((
                const float* __restrict__ phys_in, float* __restrict__ phys_out) {
   if (nbase) n += *nbase;
   row_body<LOGN2, MODE, PTS, NT>(fls[blockIdx.y], n, phys_in, phys_out, xcd_swizzle(blockIdx.x, gridDim.x),
-                                 blockIdx.x, threadIdx.x);
-}
-
-// Canonical half spectrum -> state, with the k2 = 0 symmetrisation.
-__global__ void set_spectrum_kernel(const FlameDev* __restrict__ fls, int flame, const float2* __restrict__ half) {
-  const FlameDev f = fls[flame];
-  const int total = f.m * f.h1;
-  const int k1max = f.n1 / 4 - 1;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int m = e / f.h1, s = e % f.h1;
-    const int k1 = s - f.n1 / 4;
-    float2 val = make_float2(0.f, 0.f);
-    if (s > 0) {
-      if (m == 0 && k1 < 0) {
-        val = ff::cconj(half[(size_t)(-k1 + k1max) * f.m]);
-      } else {
-        val = half[(size_t)(k1 + k1max) * f.m + m];
-        if (m == 0 && k1 == 0) val.y = 0.f;
-      }
-    }
-    f.S[e] = val;
-  }
-}
-
-__global__ void get_spectrum_kernel(const FlameDev* __restrict__ fls, int flame, float2* __restrict__ half) {
-  const FlameDev f = fls[flame];
-  const int rows = f.n1 / 2 - 1;
-  const int total = rows * f.m;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int r = e / f.m, m = e % f.m;
-    half[e] = f.S[(size_t)m * f.h1 + r + 1];
-  }
-}
-
-// Spectral sums: per workgroup partial of sum_k w_k |kappa|^2 |Phi~_k|^2 (w = 1 on
-// k2 = 0, 2 elsewhere) and a count of non-finite entries.
-__global__ void __launch_bounds__(kDiagThreads)
-    diag_spectral_kernel(const FlameDev* __restrict__ fls, int flame, double* __restrict__ part) {
-  const FlameDev f = fls[flame];
-  __shared__ double red[kDiagThreads];
-  __shared__ double bad[kDiagThreads];
-  const int total = f.m * f.h1;
-  double acc = 0.0, nb = 0.0;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
-    const int m = e / f.h1, s = e % f.h1;
-    const float2 v = f.S[e];
-    if (!isfinite(v.x) || !isfinite(v.y)) {
-      nb += 1.0;
-      continue;
-    }
-    const double k1 = (double)f.s1 * (double)(s - f.n1 / 4), k2 = (double)f.s2 * (double)m;
-    const double w = m == 0 ? 1.0 : 2.0;
-    acc += w * (k1 * k1 + k2 * k2) * ((double)v.x * v.x + (double)v.y * v.y);
-  }
-  red[threadIdx.x] = acc;
-  bad[threadIdx.x] = nb;
-  __syncthreads();
-  for (int w = kDiagThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      red[threadIdx.x] += red[threadIdx.x + w];
-      bad[threadIdx.x] += bad[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = red[0];
-    part[2 * blockIdx.x + 1] = bad[0];
-  }
-}
-
-__global__ void __launch_bounds__(kDiagThreads)
-    diag_final_kernel(const FlameDev* __restrict__ fls, int flame, long long n, int n_area, int n_spec,
-                      double* __restrict__ out) {
-  const FlameDev f = fls[flame];
-  __shared__ double ra[kDiagThreads], rs[kDiagThreads], rb[kDiagThreads];
-  double a = 0.0, s = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < n_area; i += blockDim.x) a += f.part[i];
-  const double* sp = f.part + n_area;
-  for (int i = threadIdx.x; i < n_spec; i += blockDim.x) {
-    s += sp[2 * i];
-    b += sp[2 * i + 1];
-  }
-  ra[threadIdx.x] = a;
-  rs[threadIdx.x] = s;
-  rb[threadIdx.x] = b;
-  __syncthreads();
-  for (int w = kDiagThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      ra[threadIdx.x] += ra[threadIdx.x + w];
-      rs[threadIdx.x] += rs[threadIdx.x + w];
-      rb[threadIdx.x] += rb[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double r = r0_at(f, n);
-    const float2 s00 = f.S[f.n1 / 4];
-    out[0] = r + (double)s00.x;
-    out[1] = rs[0] / (2.0 * r * r);
-    out[2] = ra[0] / ((double)f.n1 * (double)f.n2);
-    out[3] = (rb[0] == 0.0 && isfinite(out[2])) ? 1.0 : 0.0;
-  }
+                                 threadIdx.x);
 }
 
 // ------------------------------------------------------------------ dispatch
@@ -209,10 +108,7 @@ struct RowTable {
       case ROW_FORWARD:
         hipLaunchKernelGGL((row_kernel<LOGN, ROW_FORWARD>), grid, dim3(th), lds, st, fl, n, nb, in, out);
         break;
-      case ROW_SYNTH:
-        hipLaunchKernelGGL((row_kernel<LOGN, ROW_SYNTH>), grid, dim3(th), lds, st, fl, n, nb, in, out);
-        break;
-      default: hipLaunchKernelGGL((row_kernel<LOGN, ROW_DIAG>), grid, dim3(th), lds, st, fl, n, nb, in, out); break;
+      default: hipLaunchKernelGGL((row_kernel<LOGN, ROW_SYNTH>), grid, dim3(th), lds, st, fl, n, nb, in, out); break;
     }
   }
   template <bool NT>
@@ -269,6 +165,9 @@ void launch_col(int logn1, int mode, int tiles, int nfl, hipStream_t st, const F
       (void)hipLaunchKernel(kl.func, dim3(tiles * kl.mult, nfl), dim3(kl.threads), args, kl.lds, st);
     return;
   }
+  if (mode == COL_FIRST && nfl == 1 &&
+      launch_first_side(logn1, tiles * col_tile(logn1), st, fl, static_cast<const float2*>(src)))
+    return;
   dispatch_log<ColTable, kMinLog>(logn1, mode, dim3(tiles, nfl), st, fl, n, static_cast<const float2*>(src));
 }
 
@@ -283,6 +182,10 @@ void launch_row(int logn2, int mode, int groups, int nfl, hipStream_t st, const 
       (void)hipExtLaunchKernel(kl.func, dim3(groups * kl.mult, nfl), dim3(kl.threads), args, kl.lds, st, ev_start, ev_stop, 0);
     else
       (void)hipLaunchKernel(kl.func, dim3(groups * kl.mult, nfl), dim3(kl.threads), args, kl.lds, st);
+    return;
+  }
+  if (mode == ROW_DIAG) {
+    launch_diag(logn2, groups, pts, st, fl, n, reinterpret_cast<double*>(out));
     return;
   }
   dispatch_log<RowTable, kMinLog>(logn2, mode, dim3(groups, nfl), st, fl, n, in, out);
@@ -348,26 +251,5 @@ __global__ void set_step_kernel(long long* __restrict__ counter, long long value
 void launch_set_step(hipStream_t st, long long* counter, long long value) {
   hipLaunchKernelGGL(set_step_kernel, dim3(1), dim3(64), 0, st, counter, value);
 }
-
-void launch_set_spectrum(hipStream_t st, const FlameDev* fl, int flame, int total, const void* half) {
-  const int blocks = (total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096;
-  hipLaunchKernelGGL(set_spectrum_kernel, dim3(blocks), dim3(256), 0, st, fl, flame,
-                     static_cast<const float2*>(half));
-}
-
-void launch_get_spectrum(hipStream_t st, const FlameDev* fl, int flame, int total, void* half) {
-  const int blocks = (total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096;
-  hipLaunchKernelGGL(get_spectrum_kernel, dim3(blocks), dim3(256), 0, st, fl, flame, static_cast<float2*>(half));
-}
-
-void launch_diag_spectral(hipStream_t st, const FlameDev* fl, int flame, int blocks, double* part) {
-  hipLaunchKernelGGL(diag_spectral_kernel, dim3(blocks), dim3(kDiagThreads), 0, st, fl, flame, part);
-}
-
-void launch_diag_final(hipStream_t st, const FlameDev* fl, int flame, long long n, int n_area, int n_spec,
-                       double* out) {
-  hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(kDiagThreads), 0, st, fl, flame, n, n_area, n_spec, out);
-}
-
 
 }  // namespace flame

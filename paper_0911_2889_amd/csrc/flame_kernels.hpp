@@ -68,6 +68,8 @@ void launch_adjp_col(int logn1, int mode, int tiles, hipStream_t st, const Flame
                      const void* state, const void* lam_in, void* lam_out);
 
 // Row kernel over `groups` groups of B row pairs for `nfl` flames of one size.
+// ROW_DIAG: `out` takes the flame's four averages (doubles), and `pts` is the
+// number of workgroups for the spectral sums; fl->part and fl->ticket are used.
 void launch_row(int logn2, int mode, int groups, int nfl, hipStream_t st, const FlameDev* fl, long long n,
                 const float* in, float* out, int pts = ff::kPts, hipEvent_t ev_start = nullptr,
                 hipEvent_t ev_stop = nullptr, bool nt = false);
@@ -96,10 +98,10 @@ hipError_t launch_ensemble(hipStream_t st, const FlameDev* fls, const EnsembleIt
                            unsigned* arrive, int narrive, int* err, long long n0, int steps,
                            unsigned long long limit);
 
+// physical_kernels.hip: the averages (launch_row's ROW_DIAG), COL_FIRST with its
+// transforms side by side (false: not for this launch), and the canonical spectrum.
+void launch_diag(int logn2, int groups, int n_spec, hipStream_t st, const FlameDev* fl, long long n, double* out);
+bool launch_first_side(int logn1, int columns, hipStream_t st, const FlameDev* fl, const float2* src);
 void launch_set_spectrum(hipStream_t st, const FlameDev* fl, int flame, int total, const void* half);
 void launch_get_spectrum(hipStream_t st, const FlameDev* fl, int flame, int total, void* half);
-void launch_diag_spectral(hipStream_t st, const FlameDev* fl, int flame, int blocks, double* part);
-void launch_diag_final(hipStream_t st, const FlameDev* fl, int flame, long long n, int n_area, int n_spec,
-                       double* out);
-
 }  // namespace flame

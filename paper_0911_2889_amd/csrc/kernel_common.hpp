@@ -212,6 +212,46 @@ __device__ __forceinline__ float2 forcing_at(const FlameDev& f, int m, int k1) {
   return f.F ? v : make_float2(0.f, 0.f);
 }
 
+// Sum of sqrt(1 + x) - 1 = x / (1 + sqrt(1 + x)), x = q[i] inv_r2, in double.
+// The square root and the reciprocal start from single precision (2^-22) and
+// are refined in double by Newton steps, two for the root and two for the
+// quotient (2^-44, then beyond the last bit): fewer instructions than the
+// library's square root and division, and no branch between the elements. Where
+// an x is above 1e30, out of the single-precision seeds' reach, or not a
+// number, the plain form for all of them.
+template <int N>
+__device__ __forceinline__ double excess_sum(const float (&q)[N], float inv_r2) {
+  double sum = 0.0;
+  bool plain = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const double x = (double)q[i] * (double)inv_r2, y = 1.0 + x;
+    plain = plain || !(x <= 1e30);
+    const float r0 = __builtin_amdgcn_rsqf((float)y);
+    const double hr = 0.5 * (double)r0;
+    double s = y * (double)r0;
+    s = __builtin_fma(hr, __builtin_fma(-s, s, y), s);
+    s = __builtin_fma(hr, __builtin_fma(-s, s, y), s);
+    const double den = 1.0 + s, d0 = (double)__builtin_amdgcn_rcpf((float)den);
+    double e = x * d0;
+    e = __builtin_fma(__builtin_fma(-e, den, x), d0, e);
+    e = __builtin_fma(__builtin_fma(-e, den, x), d0, e);
+    sum += e;
+  }
+  if (plain) {
+    sum = 0.0;
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+      float qi = q[0];
+#pragma unroll
+      for (int k = 1; k < N; ++k) qi = k == i ? q[k] : qi;
+      const double x = (double)qi * (double)inv_r2;
+      sum += x / (1.0 + sqrt(1.0 + x));
+    }
+  }
+  return sum;
+}
+
 // Offset of element (j1, m) of Wp from f.Wp, and of Wm from f.Wm (Wp and Wm
 // fill the two halves of the W buffer): [j1/4][m][j1%4], so that the two rows
 // of a row pair are adjacent (the row kernel reads both with one 16-byte load

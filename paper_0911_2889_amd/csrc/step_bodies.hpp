@@ -134,6 +134,8 @@ __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const f
     }
   }
 
+  // a projected field's W is wanted only where the step runs on the N1 rows
+  if (MODE == COL_PROJECT && f.rows != N1) return;
   if constexpr (MODE == COL_SYNTH) {
 #pragma unroll
     for (int i = 0; i < PTS; ++i) v[i] = make_float2(0.f, 0.f);
@@ -153,7 +155,7 @@ __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const f
     for (int kk = 0; kk < KEEP; ++kk) {
       const int i = kept_reg<LOGN1, PTS>(kk);
       const float kap1 = f.s1 * (float)(t + G * i - (i >= HIGH ? L : 0));
-      v[i] = make_float2(-kap1 * sv[kk].y - kap2 * sv[kk].x, kap1 * sv[kk].x - kap2 * sv[kk].y);
+      v[i] = slope(kap1, -kap2, sv[kk]);
     }
     fft_s<S, true, kPrune>(v, t, my, T, tw1);
     if (live) {
@@ -167,7 +169,7 @@ __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const f
     for (int kk = 0; kk < KEEP; ++kk) {
       const int i = kept_reg<LOGN1, PTS>(kk);
       const float kap1 = f.s1 * (float)(t + G * i - (i >= HIGH ? L : 0));
-      v[i] = make_float2(-kap1 * sv[kk].y + kap2 * sv[kk].x, kap1 * sv[kk].x + kap2 * sv[kk].y);
+      v[i] = slope(kap1, kap2, sv[kk]);
     }
     fft_s<S, true, kPrune>(v, t, my, T, tw1);
     if (live) {
@@ -179,10 +181,10 @@ __device__ __forceinline__ void col_body(const FlameDev& f, long long n, const f
 
 // The row transforms have length N2, with PTS (16 or 8) points per thread.
 // row_body is the work of thread tid of a workgroup on row-pair group `group`
-// of flame f (ROW_DIAG writes its partial sum to f.part[slot]).
+// of flame f. ROW_DIAG returns the thread's part of the area sum.
 template <int LOGN2, int MODE, int PTS = ff::kPts, bool NT = false>
-__device__ __forceinline__ void row_body(const FlameDev& f, long long n, const float* __restrict__ phys_in,
-                                         float* __restrict__ phys_out, int group, int slot, int tid) {
+__device__ __forceinline__ double row_body(const FlameDev& f, long long n, const float* __restrict__ phys_in,
+                                           float* __restrict__ phys_out, int group, int tid) {
   using TS = TfShape<LOGN2, PTS>;
   using S = typename TS::S;
   constexpr int G = S::G, B = RowCfg<LOGN2, PTS>::B, N2 = 1 << LOGN2, L2 = S::N;
@@ -240,8 +242,7 @@ __device__ __forceinline__ void row_body(const FlameDev& f, long long n, const f
       for (int i = 0; i < PTS; ++i) {
         const float q = vr[half][i].x * vr[half][i].x + vr[half][i].y * vr[half][i].y;
         if constexpr (MODE == ROW_DIAG) {
-          const double x = (double)q * (double)inv_r2;
-          area += x / (1.0 + sqrt(1.0 + x));
+          qa[i] = q;
         } else {
           if (half == 0)
             qa[i] = q;
@@ -249,20 +250,9 @@ __device__ __forceinline__ void row_body(const FlameDev& f, long long n, const f
             y[i] = make_float2(qa[i], q);
         }
       }
+      if constexpr (MODE == ROW_DIAG) area += excess_sum(qa, inv_r2);
     }
-    if constexpr (MODE == ROW_DIAG) {
-      // deterministic workgroup reduction of the area sums
-      __syncthreads();
-      double* red = reinterpret_cast<double*>(lds);
-      red[tid] = live ? area : 0.0;
-      __syncthreads();
-      for (int w = RowCfg<LOGN2, PTS>::THREADS / 2; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-      }
-      if (tid == 0) f.part[slot] = red[0];
-      return;
-    }
+    if constexpr (MODE == ROW_DIAG) return live ? area : 0.0;
   } else if constexpr (MODE == ROW_FORWARD) {
 #pragma unroll
     for (int i = 0; i < PTS; ++i) {
@@ -299,7 +289,7 @@ __device__ __forceinline__ void row_body(const FlameDev& f, long long n, const f
         glob(phys_out)[(size_t)jb * N2 + idx] = y[i].y;
       }
     }
-    return;
+    return 0.0;
   }
 
   // forward transform of the two packed real rows, then split:
@@ -320,6 +310,7 @@ __device__ __forceinline__ void row_body(const FlameDev& f, long long n, const f
       st_nt<NT>(Q + tiled(jb, k, n1, ts), qb);
     }
   }
+  return 0.0;
 }
 
 }  // namespace flame
