@@ -16,6 +16,13 @@
 // i < 4), so HBM is touched only to load them at the start and store them
 // at the end. The twiddles are computed in double precision at the start
 // and rounded once, so the kernels need no table or workspace.
+//
+// What bounds the step is the vector ALU. From N = 64 on the squares are
+// formed on 3 N/4 points, on which a product of two spectra |k| <= K = N/4 - 1
+// has no alias in |k| <= K either (ff::MixPlan), in shorter circles and in the
+// averages on the N points. 2048 circles of 4096 points, 50 steps: 466 us for
+// 498 on N points; 511 of 16384, 10 steps: 488 for 669; 301 of 64, 20 steps:
+// 43 for 55.
 
 #include <hip/hip_runtime.h>
 
@@ -23,6 +30,7 @@
 #include "flame_dev.hpp"
 #include "flame_kernels.hpp"
 #include "kernel_common.hpp"
+#include "mixed_bodies.hpp"
 
 namespace flame {
 
@@ -87,6 +95,129 @@ __device__ __forceinline__ void gradient_spectrum(const float2 (&sa)[4], const f
   __syncthreads();  // the transform reuses the LDS
 }
 
+// The step on 3 N/4 points: lane t holds the modes t + G i (i < 4) of both
+// circles, which are inputs i of its radix-12 butterfly; inputs 8..11 are the
+// mirror images of other lanes' modes, which come through LDS, and outputs
+// 8..11 of the forward transform go back the same way.
+template <int LOGN>
+struct CircleMix {
+  static constexpr int N = 1 << LOGN, G = N / 16, L = 3 * N / 4;
+  static constexpr int B = G >= 256 ? 1 : 256 / G;
+  using I = ff::Mix<typename ff::MixPlan<LOGN>::I, G, B>;
+  using F = ff::Mix<typename ff::MixPlan<LOGN>::F, G, B>;
+  static constexpr int THREADS = B * G;
+  static constexpr int LDS_BYTES = 8 * (I::LDS > F::LDS ? I::LDS : F::LDS);
+};
+
+// Twiddles of every pass in registers, computed (ComputedTw).
+template <class M>
+struct MixComputed {
+  static constexpr int first(int p) { return p <= 1 ? 0 : first(p - 1) + M::tw_count(p - 1); }
+  int t;
+  float2 w[M::NPASS > 1 ? first(M::NPASS) : 1];
+  __device__ __forceinline__ explicit MixComputed(int t_) : t(t_) { load<1>(); }
+  template <int P>
+  __device__ __forceinline__ void load() {
+    if constexpr (P < M::NPASS) {
+      constexpr int R = M::radix(P);
+#pragma unroll
+      for (int b = 0; b < M::rounds(P); ++b)
+        ff::tw_butterfly<R>(M::ns(P), ff::mod_ns<M::ns(P)>(t + M::G * b),
+                            [&](int r, float2 e) { w[first(P) + b * (R - 1) + r - 1] = e; });
+      load<P + 1>();
+    }
+  }
+  template <int P>
+  __device__ __forceinline__ void pass(float2 (&v)[M::tw_count(P)]) const {
+#pragma unroll
+    for (int i = 0; i < M::tw_count(P); ++i) v[i] = w[first(P) + i];
+  }
+};
+
+template <int LOGN>
+__global__ void __launch_bounds__(CircleMix<LOGN>::THREADS)
+    circle_mix_kernel(CircleDev d, long long n0, int nsteps) {
+  using C = CircleMix<LOGN>;
+  using I = typename C::I;
+  using F = typename C::F;
+  constexpr int G = C::G, B = C::B, H = C::N / 4;
+  extern __shared__ float2 lds[];
+  const int tid = threadIdx.x;
+  const int p = tid % B, t = tid / B;
+  const int pair = blockIdx.x * B + p;
+  const int ca = 2 * pair, cb = 2 * pair + 1;
+  const bool live_a = ca < d.n_circles, live_b = cb < d.n_circles;
+  float2* const my = lds + p;
+  const MixComputed<I> wi(t);
+  const MixComputed<F> wf(t);
+  gf2* const sg = glob(d.S);
+  // loads without conditions; a circle past the batch is zero and stays zero
+  // (circle 0 is another workgroup's to store)
+  const size_t oa = (size_t)(live_a ? ca : 0) * H, ob = (size_t)(live_b ? cb : 0) * H;
+  float2 sa[4], sb[4];
+  float kap[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float2 la = ld(sg + oa + t + G * i), lb = ld(sg + ob + t + G * i);
+    sa[i] = make_float2(live_a ? la.x : 0.f, live_a ? la.y : 0.f);
+    sb[i] = make_float2(live_b ? lb.x : 0.f, live_b ? lb.y : 0.f);
+    kap[i] = d.seg * (float)(t + G * i);
+  }
+  for (int s = 0; s < nsteps; ++s) {
+    const CircleScalars sc = circle_scalars(d, n0 + s, C::L);
+    const float a_a = live_a ? sc.a : 0.f, a_b = live_b ? sc.a : 0.f;
+    // i kappa (Phi~_a + i Phi~_b) at k = t + G i, and its mirror image to lane
+    // G - t: position L - k = (G - t) + G (11 - i)
+    float2 v[I::REGS];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float2 pa = sa[i], pb = sb[i];
+      v[i] = make_float2(-kap[i] * (pa.y + pb.x), kap[i] * (pa.x - pb.y));
+      my[(t + G * i) * B] = make_float2(kap[i] * (pb.x - pa.y), -kap[i] * (pa.x + pb.y));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 8; r < 12; ++r) {
+      const bool past = r == 8 && t == 0;  // k = -N/4 lies outside the box
+      const float2 w = my[(G * (12 - r) - t - (past ? 1 : 0)) * B];
+      v[r] = past ? make_float2(0.f, 0.f) : w;
+    }
+    __syncthreads();  // the transform reuses the LDS
+    mix_fft<I, true, true>(v, my, wi);
+    // q_a + i q_b: the squared gradients of the two circles
+    constexpr int P = I::NPASS - 1, NV = I::rounds(P) * I::radix(P);
+    float2 y[F::REGS];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) y[i] = make_float2(v[i].x * v[i].x, v[i].y * v[i].y);
+    mix_fft<F, false, false>(y, my, wf);
+#pragma unroll
+    for (int r = 8; r < 12; ++r) my[(t + G * (r - 8)) * B] = y[r];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = t + G * i;
+      const float2 yk = y[i];
+      const float2 yo = my[(G * (4 - i) - t - (k == 0 ? 1 : 0)) * B];
+      float2 na, nb;
+      split_pair(yk, k == 0 ? yk : yo, na, nb);
+      const float kk = kap[i] * kap[i];
+      const float e = __expf(-kk * sc.i2 + 0.5f * d.gamma * fabsf(kap[i]) * sc.i1);
+      sa[i] = make_float2(e * (sa[i].x + a_a * na.x), e * (sa[i].y + a_a * na.y));
+      sb[i] = make_float2(e * (sb[i].x + a_b * nb.x), e * (sb[i].y + a_b * nb.y));
+    }
+    if (t == 0) {  // Im Phi~_0 = 0 (symmetrisation)
+      sa[0].y = 0.f;
+      sb[0].y = 0.f;
+    }
+    __syncthreads();  // the next step writes the LDS
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (live_a) st(sg + oa + t + G * i, sa[i]);
+    if (live_b) st(sg + ob + t + G * i, sb[i]);
+  }
+}
+
 template <int LOGN>
 __global__ void __launch_bounds__(CircleCfg<LOGN>::THREADS)
     circle_step_kernel(CircleDev d, long long n0, int nsteps) {
@@ -102,19 +233,22 @@ __global__ void __launch_bounds__(CircleCfg<LOGN>::THREADS)
   float2* my = lds + p;
   const ff::RegTwS<S, ComputedTw, 2> tw(ComputedTw{}, t);
   gf2* const sg = glob(d.S);
-  // loads without conditions: a circle past the batch reads circle 0 (never stored)
+  // loads without conditions; a circle past the batch is zero and stays zero
+  // (circle 0 is another workgroup's to store)
   const size_t oa = (size_t)(live_a ? ca : 0) * H, ob = (size_t)(live_b ? cb : 0) * H;
   float2 sa[4], sb[4];
   float kap[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int k = t + G * i;
-    sa[i] = ld(sg + oa + k);
-    sb[i] = ld(sg + ob + k);
+    const float2 la = ld(sg + oa + k), lb = ld(sg + ob + k);
+    sa[i] = make_float2(live_a ? la.x : 0.f, live_a ? la.y : 0.f);
+    sb[i] = make_float2(live_b ? lb.x : 0.f, live_b ? lb.y : 0.f);
     kap[i] = d.seg * (float)k;
   }
   for (int s = 0; s < nsteps; ++s) {
     const CircleScalars sc = circle_scalars(d, n0 + s, N);
+    const float a_a = live_a ? sc.a : 0.f, a_b = live_b ? sc.a : 0.f;
     float2 v[16];
     gradient_spectrum<S>(sa, sb, kap, t, my, B, v);
     fft_s<S, true, kPrune>(v, t, my, B, tw);
@@ -134,8 +268,8 @@ __global__ void __launch_bounds__(CircleCfg<LOGN>::THREADS)
       const float2 nb = make_float2(0.5f * (yk.y + ym.y), 0.5f * (ym.x - yk.x));
       const float kk = kap[i] * kap[i];
       const float e = __expf(-kk * sc.i2 + 0.5f * d.gamma * fabsf(kap[i]) * sc.i1);
-      sa[i] = make_float2(e * (sa[i].x + sc.a * na.x), e * (sa[i].y + sc.a * na.y));
-      sb[i] = make_float2(e * (sb[i].x + sc.a * nb.x), e * (sb[i].y + sc.a * nb.y));
+      sa[i] = make_float2(e * (sa[i].x + a_a * na.x), e * (sa[i].y + a_a * na.y));
+      sb[i] = make_float2(e * (sb[i].x + a_b * nb.x), e * (sb[i].y + a_b * nb.y));
     }
     if (t == 0) {  // Im Phi~_0 = 0 (symmetrisation)
       sa[0].y = 0.f;
@@ -230,6 +364,9 @@ __global__ void __launch_bounds__(CircleCfg<LOGN>::THREADS)
   }
 }
 
+// Steps run on 3 N/4 points from N = 64 on (MixPlan): faster at every length
+// and batch tried (32 and 16 points have no shorter plan).
+constexpr int kMinLogCircleMix = 6;
 template <int L>
 bool circle_dispatch(int logn, bool diag, const CircleDev& d, long long n, int nsteps, double* out, hipStream_t st) {
   if constexpr (L > kMaxLog) {
@@ -239,10 +376,15 @@ bool circle_dispatch(int logn, bool diag, const CircleDev& d, long long n, int n
     using Cfg = CircleCfg<L>;
     const int pairs = (d.n_circles + 1) / 2;
     const int blocks = (pairs + Cfg::B - 1) / Cfg::B;
-    if (diag)
+    if (diag) {
       hipLaunchKernelGGL(circle_diag_kernel<L>, dim3(blocks), dim3(Cfg::THREADS), Cfg::LDS_BYTES, st, d, n, out);
-    else
+    } else if constexpr (L >= kMinLogCircleMix) {
+      using Mix = CircleMix<L>;
+      static_assert(Mix::B == Cfg::B, "one grid for both");
+      hipLaunchKernelGGL(circle_mix_kernel<L>, dim3(blocks), dim3(Mix::THREADS), Mix::LDS_BYTES, st, d, n, nsteps);
+    } else {
       hipLaunchKernelGGL(circle_step_kernel<L>, dim3(blocks), dim3(Cfg::THREADS), Cfg::LDS_BYTES, st, d, n, nsteps);
+    }
     return true;
   }
 }

@@ -142,3 +142,24 @@ def test_circle_errors(flame):
     ok = flame.native.make_circle_desc(32)
     assert lib.flame_circle_step(ctypes.byref(ok), 1, ctypes.c_void_p(st.data_ptr()), 0, -1, None) == -1
     assert lib.flame_circle_step(ctypes.byref(ok), 1, None, 0, 1, None) == -1
+
+
+@pytest.mark.parametrize("n,count", [(32, 35), (64, 131), (128, 65), (512, 17), (2048, 5), (8192, 2), (16384, 1)])
+def test_circle_steps_on_every_plan(flame, n, count):
+    """Both ends of the product plans' range and one length below it, batches
+    that leave a workgroup or a pair part empty, and 40 steps in one call or
+    in three (bit for bit)."""
+    amp, t0, dt = 0.3, 5.0, 0.1
+    spec = circle_spectra(n, count, seed=n + 2 * count, amp=amp)
+    p = oracle.CircleParams(n, gamma=0.8, seg=1.0, t0=t0, dt=dt)
+    batch = flame.CircleBatch(n, count, gamma=0.8, seg=1.0, t0=t0, dt=dt)
+    batch.set_spectra(spec)
+    batch.step(40)
+    got = batch.states.cpu().numpy()
+    for c in sorted({0, count // 2, count - 1}):
+        # the bound of the 50-step comparison above
+        assert rel_l2_circle(got[c], oracle_circle(spec[c], p, 40)) < 1e-5, c
+    batch.set_spectra(spec)
+    for k in (1, 2, 37):
+        batch.step(k)
+    assert np.array_equal(batch.states.cpu().numpy(), got)
