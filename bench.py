@@ -25,9 +25,12 @@ HBM_PEAK_GBS = 8000.0
 # for packed FP32 x 2.4 GHz); without packed FP32 instructions half of it
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 CIRCLE_SOURCES = ("paper_0911_2889_amd/csrc/circle_kernels.hip", "paper_0911_2889_amd/csrc/fft_engine.hpp",
+                  "paper_0911_2889_amd/csrc/mixed_fft.hpp", "paper_0911_2889_amd/csrc/mixed_bodies.hpp",
                   "paper_0911_2889_amd/csrc/flame_dev.hpp",
                   "paper_0911_2889_amd/csrc/kernel_common.hpp")
 KERNEL_SOURCES = ("paper_0911_2889_amd/csrc/flame_kernels.hip", "paper_0911_2889_amd/csrc/step_bodies.hpp",
+                  "paper_0911_2889_amd/csrc/mixed_kernels.hip", "paper_0911_2889_amd/csrc/mixed_bodies.hpp",
+                  "paper_0911_2889_amd/csrc/mixed_fft.hpp",
                   "paper_0911_2889_amd/csrc/fft_engine.hpp", "paper_0911_2889_amd/csrc/flame_dev.hpp",
                   "paper_0911_2889_amd/csrc/kernel_common.hpp")
 
@@ -445,8 +448,9 @@ def circle_leg(n=4096, count=2048, steps=200, valu_per_wave_step=None):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     pairs = (count + 1) // 2
-    # nominal FFT flops: one inverse and one forward complex transform of n points per pair and step
-    flops = pairs * steps * 2 * 5.0 * n * math.log2(n)
+    # nominal FFT flops: one inverse and one forward complex transform per pair and step, of 3 n/4 points from n = 64 on
+    m = 3 * n // 4 if n >= 64 else n
+    flops = pairs * steps * 2 * 5.0 * m * math.log2(m)
     out = {"circles": count, "points": n, "steps": steps, "ms": ms, "us_per_step": ms * 1e3 / steps,
            "point_steps_per_s": n * count * steps / (ms * 1e-3),
            "nominal_fft_tflops": flops / (ms * 1e-3) / 1e12,
@@ -751,7 +755,7 @@ def main():
     dom = "col"
     achieved = nbytes[dom] / (per_launch[dom] * 1e-3) / 1e9
     traffic = measured_traffic(dom, w.name, pts[0] if dom == "col" else pts[1], rows, streaming)
-    row_cols = 3 * w.n2 // 4 if pts[1] == 12 else w.n2
+    row_cols = 3 * w.n2 // 4 if w.n2 >= 64 else w.n2
     row_flops = row_pass_flops(rows, row_cols)
     row_tflops = row_flops / (per_launch["row"] * 1e-3) / 1e12
     result = {
@@ -770,7 +774,7 @@ def main():
         "config": {"workload": w.name, "grid": [w.n1, w.n2], "dt": w.dt, "t0": w.t0, "gamma": w.gamma,
                    "diagnostics_every": args.diag_every, "ic": f"{w.rule} modes, amp {w.amp}, seed {w.seed}",
                    "points_per_thread": {"col": pts[0], "row": pts[1]}, "product_rows": rows,
-                   "product_cols": 3 * w.n2 // 4 if pts[1] == 12 else w.n2,
+                   "product_cols": row_cols,
                    "streaming_stores": streaming, "graph_steps": graph_steps,
                    # what the timed region ran: graph replays of graph_steps steps, steps
                    # launched directly, and diagnostics (due every diagnostics_every steps)

@@ -228,25 +228,28 @@ int flame_timing_begin(flame_plan plan);
 /* Stop timing, synchronise the plan's stream and report the summed
  * durations in milliseconds and the counts, per kind: [0] row step kernels,
  * [1] column step kernels, [2] diagnostics and other kernels, [3] graph
- * launches (each covering steps_per_graph steps) and persistent launches
- * (each covering the steps of one flame_step call, up to 1000). Bracketed launches that
+ * launches (each covering steps_per_graph steps), persistent launches (each
+ * covering the steps of one flame_step call, up to 1000) and the launches of
+ * small flames, n1 n2 <= 2^14, that run up to 2000 steps at once. Bracketed launches that
  * follow each other share their boundary event, so their intervals include
  * the launch gap. ms4 and counts4 are host arrays of 4 entries. */
 int flame_timing_end(flame_plan plan, double* ms4, int64_t* counts4);
 
-/* Points per thread of the step kernels for the flames of grid n1 x n2: each
- * length-N transform is owned by N/pts threads holding pts points, with
- * radix-pts passes (col_pts for the column kernel, row_pts for the row
- * kernel; 8 or 16, default 16; 8 only for lengths up to 8192,
- * FLAME_ERR_UNSUPPORTED_SIZE beyond). pts = 12 selects the 12-point plan (a
- * radix-12 pass, then radix 4 and 2) for transforms of 3/4 of the grid on
- * N/16 threads: col_pts = 12 runs the column transforms of the product grid
- * (it needs flame_set_product_grid enabled, FLAME_ERR_INVALID_ARG
- * otherwise), row_pts = 12 forms the quadratic term on 3 N2/4 phi points
- * instead of N2 (n2 >= 64, FLAME_ERR_UNSUPPORTED_SIZE otherwise); for a
- * product of two box-limited fields that grid is also alias-free, as the
- * theta product grid is. Results agree to rounding, not bit for bit; the
- * choice trades registers per thread for waves per transform. */
+/* Points per thread of the step kernels for the flames of grid n1 x n2
+ * (col_pts for the column kernel, row_pts for the row kernel; default 16).
+ * Rows of n2 >= 64 and, on the product grid (flame_set_product_grid), columns
+ * are transforms of 3/4 of the grid's length (the phi axis is alias-free on
+ * 3 N2/4 points as the theta axis is on 3 N1/4), which have kernels for many
+ * and for few transforms in a launch: 12 selects those for many (12 points
+ * per thread), 8 those for few (a pair's two inverse transforms side by side
+ * on twice the threads, or at length 8192 one after the other on all of
+ * them), and 16 lets the library choose by the number of transforms. The
+ * results are the same bit for bit. On N1 rows, and for rows of n2 < 64, a
+ * length-N transform is owned by N/pts threads holding pts points, pts 8 or
+ * 16, with radix-pts passes (results agree to rounding); col_pts = 12 needs
+ * the product grid (FLAME_ERR_INVALID_ARG otherwise) and row_pts = 12 n2 >= 64
+ * (FLAME_ERR_UNSUPPORTED_SIZE otherwise). 8 stops at length 8192
+ * (FLAME_ERR_UNSUPPORTED_SIZE beyond). */
 int flame_set_points_per_thread(flame_plan plan, int32_t n1, int32_t n2, int32_t col_pts, int32_t row_pts);
 int flame_get_points_per_thread(flame_plan plan, int32_t n1, int32_t n2, int32_t* col_pts, int32_t* row_pts);
 
@@ -258,10 +261,8 @@ int flame_get_points_per_thread(flame_plan plan, int32_t n1, int32_t n2, int32_t
  * its aliases falls inside |k1| <= K1, so the truncated term, and the step,
  * are the same as on N1 rows up to rounding. It moves 3/4 of the
  * intermediate data and does 3/4 of the row transforms. The column
- * transforms then have length 3 N1/4 (radix-16 passes and a radix-6 pass;
- * col_pts = 8 selects the variant whose forward transform runs on twice the
- * threads with 8 points each and whose Wp and Wm transforms run side by
- * side). Diagnostics,
+ * transforms then have length 3 N1/4 (mixed radices, a radix-12 pass among
+ * them). Diagnostics,
  * state I/O, synthesis and the adjoint always use the N1 x N2 grid. Default:
  * enabled for n1 >= 128. Disabling it while col_pts = 12 fails with
  * FLAME_ERR_INVALID_ARG. Changing it synchronises the stream. */
@@ -416,7 +417,8 @@ int flame_circle_diagnostics(const flame_circle_desc* desc, int32_t n_circles, c
  * the kernel sequence flame_step runs on a fresh plan in its default
  * configuration (product grid for n1 >= 128, 16 points per thread, plain
  * stores, direct launches): the column transforms of the state, then a row
- * and a column kernel per step. `state` (dev, flame_state_bytes, 16-byte
+ * and a column kernel per step, or for small flames (n1 n2 <= 2^14) launches
+ * of many steps. `state` (dev, flame_state_bytes, 16-byte
  * aligned, the state layout above) holds the state at step index n
  * (time t0 + n dt) and is updated in place; the work is queued on
  * hip_stream (a hipStream_t, 0 for the null stream) of the current device.

@@ -1,4 +1,6 @@
-// HIP kernels of the spectral flame step (gfx950).
+// HIP kernels of the spectral flame step on N1 rows and on rows of fewer than
+// 64 points, and of the physical grid's transforms (gfx950); on the product
+// grids the step runs the kernels of mixed_kernels.hip, in the same two parts.
 //
 // One step of Eq. (1) is two kernels:
 //  * row_kernel<ROW_STEP>: for each pair of grid rows j1, load the column-

@@ -162,7 +162,9 @@ class FlameEnsemble:
         return out
 
     def set_points_per_thread(self, n1, n2, col_pts, row_pts):
-        """Points per thread (8 or 16) of the step kernels for the grid n1 x n2."""
+        """Points per thread (8, 12 or 16) of the step kernels for the grid n1 x n2: on
+        the product grids 12 selects the kernels for many transforms, 8 those for
+        few, 16 leaves the choice to the library."""
         native.check(self.lib.flame_set_points_per_thread(self.plan, int(n1), int(n2), int(col_pts), int(row_pts)))
 
     def points_per_thread(self, n1, n2):
