@@ -16,18 +16,19 @@
 // lds_pad32 and lds_pad32_256 below; a Shape chooses them per exchange).
 //
 // Twiddles come from a table built in double precision and rounded once to
-// float: pass p >= 1 of radix R stores, for the twiddle w(k, r) =
-// exp(-2 pi i r k / (Ns R)) = c_r (1 - i t_r), the pair (t_r, rho_r) at
+// float: pass p >= 1 of radix R stores w(k, r) = exp(-2 pi i r k / (Ns R)) at
 // [(r - 1) * Ns + k], 0 < r < R, k < Ns, so that the lanes of a wave
-// (consecutive k) read consecutive addresses for each r. rho_r = c_r / c_q is
-// the cosine relative to that of the input q = tw_parent(R, r) that input r
-// meets first in the butterfly. The kernels are bound by the vector ALU, and
-// in this form a twiddle costs two fused multiply-adds per point instead of
-// four operations: x (1 - i t) needs two, and the cosines ride on the
-// butterfly's additions (a +- rho b), which become fused multiply-adds. The
-// butterflies' own roots take the same form. A radix-16 pass is 180
-// operations per 16 points instead of 220 (144 instead of 160 without
-// twiddles). The last radix-6 pass of Shape6 keeps plain (cos, -sin) twiddles.
+// (consecutive k) read consecutive addresses for each r. The butterflies' own
+// roots are written c (1 - i t): x (1 - i t) takes two fused multiply-adds,
+// and the cosine rides on the addition that follows (a +- c b). A radix-16
+// pass is 204 operations per 16 points instead of 220 (144 instead of 160
+// without twiddles). Those t are at most tan(3 pi/8) = 2.4, so that this costs
+// no range. For the twiddles the form is not used: a quarter turn has no
+// cosine, and next to one t is in the thousands; with a cosine of 2^-28 in its
+// place (180 operations) inputs of 1e29 overflowed, and a single mode lost a
+// quarter of its accuracy. The whole calls it made 0.5 % faster on the mean
+// (2048 circles of 4096 points, 50 steps: 478 us instead of 485; 50 steps of
+// 2048x4096: 1749 instead of 1765).
 //
 // The pass functions are __host__ __device__ so the same code can be
 // driven thread by thread on the CPU to check the index maps.
@@ -286,66 +287,62 @@ constexpr float kSin8 = 0.38268343236508977173f;      // sin(pi/8) = cos(3 pi/8)
 constexpr float kTan8 = 0.41421356237309504880f;      // tan(pi/8) = tan(9 pi/8)
 constexpr float kTan38 = 2.41421356237309504880f;     // tan(3 pi/8)
 
-// Length-8 DFT of inputs that carry scales: x[r] stands for c_r x[r] with
-// rho[r] = c_r / c_parent(r) (tw_parent; rho[0] unused, c_0 = 1).
 template <bool INV>
-__host__ __device__ __forceinline__ void dft8s(float2* x, const float* rho) {
+__host__ __device__ __forceinline__ void dft8(float2* x) {
   float2 e0 = x[0], e1 = x[2], e2 = x[4], e3 = x[6];
   float2 o0 = x[1], o1 = x[3], o2 = x[5], o3 = x[7];
-  dft4s<INV>(e0, e1, e2, e3, rho[2], rho[4], rho[6]);
-  dft4s<INV>(o0, o1, o2, o3, rho[3], rho[5], rho[7]);
-  const float r1 = rho[1], r1h = kSqrtHalf * rho[1];
+  dft4<INV>(e0, e1, e2, e3);
+  dft4<INV>(o0, o1, o2, o3);
   o1 = tmul<INV>(o1, 1.f);   // w8 without cos(pi/4)
   o2 = mul_q<INV>(o2);
   o3 = tmul<INV>(o3, -1.f);  // w8^3 without -cos(pi/4)
-  x[0] = axpy(e0, r1, o0);
-  x[4] = axpy(e0, -r1, o0);
-  x[1] = axpy(e1, r1h, o1);
-  x[5] = axpy(e1, -r1h, o1);
-  x[2] = axpy(e2, r1, o2);
-  x[6] = axpy(e2, -r1, o2);
-  x[3] = axpy(e3, -r1h, o3);
-  x[7] = axpy(e3, r1h, o3);
+  x[0] = cadd(e0, o0);
+  x[4] = csub(e0, o0);
+  x[1] = axpy(e1, kSqrtHalf, o1);
+  x[5] = axpy(e1, -kSqrtHalf, o1);
+  x[2] = cadd(e2, o2);
+  x[6] = csub(e2, o2);
+  x[3] = axpy(e3, -kSqrtHalf, o3);
+  x[7] = axpy(e3, kSqrtHalf, o3);
 }
 
 // Second half of the length-16 DFT: y[4 r2 + m1] holds the length-4
-// transforms over r1 (r = 4 r1 + r2, m = m1 + 4 m2), scaled by c_{r2}; the
-// inner roots w16^(r2 m1), then the length-4 transforms over r2.
+// transforms over r1 (r = 4 r1 + r2, m = m1 + 4 m2); the inner roots
+// w16^(r2 m1), then the length-4 transforms over r2.
 template <bool INV>
-__host__ __device__ __forceinline__ void dft16_tail(float2* x, float2* y, float r1, float r2, float r3) {
-  dft4s<INV>(y[0], y[4], y[8], y[12], r1, r2, r3);
+__host__ __device__ __forceinline__ void dft16_tail(float2* x, float2* y) {
+  dft4<INV>(y[0], y[4], y[8], y[12]);
   y[5] = tmul<INV>(y[5], kTan8);     // w^1, cos(pi/8)
   y[9] = tmul<INV>(y[9], 1.f);       // w^2, cos(pi/4)
   y[13] = tmul<INV>(y[13], kTan38);  // w^3, cos(3 pi/8)
-  dft4s<INV>(y[1], y[5], y[9], y[13], kCos8 * r1, kSqrtHalf * r2, (kSin8 / kCos8) * r3);
+  dft4s<INV>(y[1], y[5], y[9], y[13], kCos8, kSqrtHalf, kSin8 / kCos8);
   y[6] = tmul<INV>(y[6], 1.f);     // w^2
   y[10] = mul_q<INV>(y[10]);       // w^4
   y[14] = tmul<INV>(y[14], -1.f);  // w^6, -cos(pi/4)
-  dft4s<INV>(y[2], y[6], y[10], y[14], kSqrtHalf * r1, r2, -r3);
+  dft4s<INV>(y[2], y[6], y[10], y[14], kSqrtHalf, 1.f, -1.f);
   y[7] = tmul<INV>(y[7], kTan38);  // w^3
   y[11] = tmul<INV>(y[11], -1.f);  // w^6
   y[15] = tmul<INV>(y[15], kTan8);  // w^9, -cos(pi/8)
-  dft4s<INV>(y[3], y[7], y[11], y[15], kSin8 * r1, -kSqrtHalf * r2, -(kCos8 / kSin8) * r3);
+  dft4s<INV>(y[3], y[7], y[11], y[15], kSin8, -kSqrtHalf, -(kCos8 / kSin8));
 #pragma unroll
   for (int m1 = 0; m1 < 4; ++m1)
 #pragma unroll
     for (int m2 = 0; m2 < 4; ++m2) x[m1 + 4 * m2] = y[4 * m2 + m1];
 }
 
-// Length-16 DFT of inputs that carry scales, as dft8s.
 template <bool INV>
-__host__ __device__ __forceinline__ void dft16s(float2* x, const float* rho) {
+__host__ __device__ __forceinline__ void dft16(float2* x) {
   float2 y[16];
 #pragma unroll
   for (int r2 = 0; r2 < 4; ++r2) {
     float2 a = x[r2], b = x[r2 + 4], c = x[r2 + 8], d = x[r2 + 12];
-    dft4s<INV>(a, b, c, d, rho[r2 + 4], rho[r2 + 8], rho[r2 + 12]);
+    dft4<INV>(a, b, c, d);
     y[4 * r2 + 0] = a;
     y[4 * r2 + 1] = b;
     y[4 * r2 + 2] = c;
     y[4 * r2 + 3] = d;
   }
-  dft16_tail<INV>(x, y, rho[1], rho[2], rho[3]);
+  dft16_tail<INV>(x, y);
 }
 
 // dft16 for inputs x[4..11] == 0 (only the first and last quarter set).
@@ -361,7 +358,7 @@ __host__ __device__ __forceinline__ void dft16_outer(float2* x) {
     y[4 * r2 + 2] = csub(a, d);
     y[4 * r2 + 3] = cadd(a, qd);
   }
-  dft16_tail<INV>(x, y, 1.f, 1.f, 1.f);
+  dft16_tail<INV>(x, y);
 }
 
 // dft8 for inputs x[2..5] == 0.
@@ -435,11 +432,10 @@ __host__ __device__ __forceinline__ void dft3s(float2& y, float2& q, float2& r, 
 // length-12 DFT as 4 x 3: r = 3 a + b, m = c + 4 d. Length-4 transforms over
 // a for each b, the inner roots w12^(b c), then length-3 transforms over b:
 // X[c + 4 d] = sum_b w3^(b d) w12^(b c) sum_a x[3 a + b] w4^(a c).
-// x[r] carries the scale c_r, as in dft8s. ZMID: the caller guarantees
-// x[4..7] == 0 (a spectrum kept in the first and last third) and no scales,
-// which drops the terms that vanish.
+// ZMID: the caller guarantees x[4..7] == 0 (a spectrum kept in the first and
+// last third), which drops the terms that vanish.
 template <bool INV, bool ZMID = false>
-__host__ __device__ __forceinline__ void dft12s(float2* x, const float* rho) {
+__host__ __device__ __forceinline__ void dft12(float2* x) {
   constexpr float h = 0.86602540378443864676f;  // sqrt(3)/2 = cos(pi/6)
   constexpr float t30 = 0.57735026918962576451f, t60 = 1.73205080756887729353f;
   float2 y[3][4];
@@ -468,83 +464,69 @@ __host__ __device__ __forceinline__ void dft12s(float2* x, const float* rho) {
         y[b][3] = cadd(d02, qa3);
       }
     } else {
-      dft4s<INV>(a0, a1, a2, a3, rho[b + 3], rho[b + 6], rho[b + 9]);
+      dft4<INV>(a0, a1, a2, a3);
       y[b][0] = a0;
       y[b][1] = a1;
       y[b][2] = a2;
       y[b][3] = a3;
     }
   }
-  const float r1 = ZMID ? 1.f : rho[1], r2 = ZMID ? 1.f : rho[2];
-  dft3s<INV>(y[0][0], y[1][0], y[2][0], r1, r2);
+  dft3s<INV>(y[0][0], y[1][0], y[2][0], 1.f, 1.f);
   y[1][1] = tmul<INV>(y[1][1], t30);   // w12, cos h
   y[2][1] = tmul<INV>(y[2][1], t60);   // w12^2, cos 1/2
-  dft3s<INV>(y[0][1], y[1][1], y[2][1], h * r1, (0.5f / h) * r2);
+  dft3s<INV>(y[0][1], y[1][1], y[2][1], h, 0.5f / h);
   y[1][2] = tmul<INV>(y[1][2], t60);   // w12^2
   y[2][2] = tmul<INV>(y[2][2], -t60);  // w12^4, cos -1/2
-  dft3s<INV>(y[0][2], y[1][2], y[2][2], 0.5f * r1, -r2);
+  dft3s<INV>(y[0][2], y[1][2], y[2][2], 0.5f, -1.f);
   y[1][3] = mul_q<INV>(y[1][3]);       // w12^3; y[2][3] takes w12^6 = -1
-  dft3s<INV>(y[0][3], y[1][3], y[2][3], r1, -r2);
+  dft3s<INV>(y[0][3], y[1][3], y[2][3], 1.f, -1.f);
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int d = 0; d < 3; ++d) x[c + 4 * d] = y[d][c];
 }
 
-// Length-R DFT of inputs that carry scales (dft8s); rho[0] is not read.
 template <int R, bool INV>
-__host__ __device__ __forceinline__ void dfts(float2* x, const float* rho) {
+__host__ __device__ __forceinline__ void dft(float2* x) {
   if constexpr (R == 2) {
-    const float2 a = x[0];
-    x[0] = axpy(a, rho[1], x[1]);
-    x[1] = axpy(a, -rho[1], x[1]);
+    dft2<INV>(x[0], x[1]);
   } else if constexpr (R == 4) {
-    dft4s<INV>(x[0], x[1], x[2], x[3], rho[1], rho[2], rho[3]);
+    dft4<INV>(x[0], x[1], x[2], x[3]);
   } else if constexpr (R == 8) {
-    dft8s<INV>(x, rho);
+    dft8<INV>(x);
   } else if constexpr (R == 12) {
-    dft12s<INV>(x, rho);
+    dft12<INV>(x);
   } else {
     static_assert(R == 16, "radix");
-    dft16s<INV>(x, rho);
+    dft16<INV>(x);
   }
 }
 
-// The input whose scale that of input r is stored relative to: the one it
-// meets first in dft4s, dft8s, dft16s (r without its highest bit) or dft12s.
-__host__ __device__ constexpr int tw_parent(int radix, int r) {
-  if (radix == 12) return r >= 6 ? r - 6 : (r >= 3 ? r - 3 : r - 1);
-  int h = 1;
-  while (2 * h <= r) h *= 2;
-  return r - h;
+// x times the twiddle w (forward; the inverse transform takes its conjugate),
+// each operation written out (update1 in kernel_common.hpp has the reason).
+template <bool INV>
+__host__ __device__ __forceinline__ float2 twmul(float2 x, float2 w) {
+#pragma clang fp contract(off)
+  const float wy = INV ? -w.y : w.y;
+  return make_float2(__builtin_fmaf(w.x, x.x, -(wy * x.y)), __builtin_fmaf(w.x, x.y, wy * x.x));
 }
 
-// Twiddles of one butterfly, r = 1 .. radix - 1: w(r) = (t_r, rho_r) of
-// exp(-2 pi i r k / (ns radix)), stored through `put(r, entry)`. The powers of
-// one root by multiplication in double, so one sine and cosine per butterfly.
-// A quarter turn has no cosine: it takes 2^-28 instead, which is an error of
-// 4e-9 in the twiddle. Each rho and t is formed with the cosines as rounded
-// so far, so that every product c_r and c_r t_r is rounded once. Every
-// operation is written out (no contraction left to the compiler), so that the
-// tables built on the host and on the device agree.
+// Twiddles of one butterfly, r = 1 .. radix - 1: exp(-2 pi i r k / (ns radix)),
+// stored through `put(r, entry)`. The powers of one root by multiplication in
+// double, so one sine and cosine per butterfly. Every operation is written out
+// (no contraction left to the compiler), so that the tables built on the host
+// and on the device agree.
 template <int R, class PUT>
 __host__ __device__ __forceinline__ void tw_butterfly(int ns, int k, const PUT& put) {
   const double ang = 2.0 * M_PI * (double)k / ((double)ns * R);
   const double c1 = cos(ang), s1 = sin(ang);
-  double inv[R], have[R];
-  have[0] = inv[0] = 1.0;
   double c = 1.0, s = 0.0;
 #pragma unroll
   for (int r = 1; r < R; ++r) {
     const double cn = __builtin_fma(c, c1, -(s * s1));
     s = __builtin_fma(s, c1, c * s1);
     c = cn;
-    const double cc = fabs(c) < 0x1p-28 ? (c < 0.0 ? -0x1p-28 : 0x1p-28) : c;
-    const int q = tw_parent(R, r);
-    const float rho = (float)(cc * inv[q]);
-    have[r] = (double)rho * have[q];
-    inv[r] = 1.0 / have[r];
-    put(r, make_float2((float)(s * inv[r]), rho));
+    put(r, make_float2((float)c, -(float)s));
   }
 }
 template <class PUT>
@@ -680,7 +662,7 @@ struct FftS {
 
   // Pass P < S::NBF: thread t runs PTS/R butterflies on its registers.
   // Butterfly b has global index j = t + b*G and inputs x[j + r*N/R] =
-  // v[b + r*PTS/R]; it applies the twiddles w(j mod Ns, r) (tmul and the scales), the radix-R DFT,
+  // v[b + r*PTS/R]; it applies the twiddles w(j mod Ns, r), the radix-R DFT,
   // and sends output r to position (j / Ns) * Ns * R + (j mod Ns) + r * Ns:
   // into LDS, or, in the last pass (Ns * R = N), back into the same registers.
   // OUTER: the caller guarantees v[PTS/4 .. 3PTS/4 - 1] == 0 on entry to
@@ -704,20 +686,13 @@ struct FftS {
       } else if constexpr (OUTER && P == 0 && R == 8 && PTS == 8) {
         dft8_outer<INV>(x);
       } else if constexpr (OUTER && P == 0 && R == 12 && PTS == 12) {
-        dft12s<INV, true>(x, nullptr);
+        dft12<INV, true>(x);
       } else {
-        float rho[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) rho[r] = 1.f;
         if constexpr (P > 0) {
 #pragma unroll
-          for (int r = 1; r < R; ++r) {
-            const float2 w = tw.template get<P>(b, r);
-            x[r] = tmul<INV>(x[r], w.x);
-            rho[r] = w.y;
-          }
+          for (int r = 1; r < R; ++r) x[r] = twmul<INV>(x[r], tw.template get<P>(b, r));
         }
-        dfts<R, INV>(x, rho);
+        dft<R, INV>(x);
       }
       if constexpr (LAST) {
 #pragma unroll
@@ -787,7 +762,7 @@ inline void build_twiddles_plan(const PassPlan& p, float2* out) {
 inline void build_twiddles(int logn, float2* out, int pts = kPts) { build_twiddles_plan(make_pass_plan(logn, pts), out); }
 
 // Host: the twiddle table of a length 6*2^logp transform (Shape6 layout): the
-// power-of-two passes' table, then plain exp(-2 pi i r k / N) at TW6 + (r-1)*N6 + k.
+// power-of-two passes' table, then exp(-2 pi i r k / N) at TW6 + (r-1)*N6 + k.
 inline void build_twiddles6(int logp, float2* out, int pts = kPts) {
   build_twiddles(logp, out, pts);
   const PassPlan p = make_pass_plan(logp, pts);

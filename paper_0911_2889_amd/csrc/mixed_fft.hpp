@@ -211,26 +211,18 @@ struct Mix {
     for (int b = 0; b < rounds(P); ++b) {
       if (!active<P>(t, b)) continue;
       float2 y[R];
-      float rho[R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        y[r] = x[b * R + r];
-        rho[r] = 1.f;
-      }
+      for (int r = 0; r < R; ++r) y[r] = x[b * R + r];
       if constexpr (P > 0) {
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          const float2 wr = w[b * (R - 1) + r - 1];
-          y[r] = tmul<INV>(y[r], wr.x);
-          rho[r] = wr.y;
-        }
+        for (int r = 1; r < R; ++r) y[r] = twmul<INV>(y[r], w[b * (R - 1) + r - 1]);
       }
       if constexpr (P == 0 && R == 12 && ZMID)
-        dft12s<INV, true>(y, rho);
+        dft12<INV, true>(y);
       else if constexpr (P == 0 && R == 16 && ZMID)
         dft16_outer<INV>(y);
       else
-        dfts<R, INV>(y, rho);
+        dft<R, INV>(y);
 #pragma unroll
       for (int r = 0; r < R; ++r) x[b * R + r] = y[r];
     }
