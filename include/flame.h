@@ -338,8 +338,8 @@ int flame_set_graph_steps(flame_plan plan, int32_t steps);
  * so the results are the same bit for bit. Shares are sized so that every
  * workgroup has about the same number of tiles per step.
  *
- * workgroups: the grid size (0: every workgroup that fits on the device,
- * two per compute unit). wait_limit_us: the bound of each wait at a counter,
+ * workgroups: the grid size, at most what fits on the device at once (0: two
+ * per compute unit, or one where no more fit). wait_limit_us: the bound of each wait at a counter,
  * in microseconds (0: 2 s); a wait that runs out makes every workgroup stop,
  * and flame_step returns FLAME_ERR_TIMEOUT with the states undefined. In
  * this mode flame_step waits for the plan's stream before it returns (to

@@ -1186,8 +1186,10 @@ int ens_prepare(flame_plan p) {
   if (per_cu <= 0) return fail(FLAME_ERR_HIP, "occupancy query of the persistent kernel failed");
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute(multiprocessor count)");
-  int wgs = std::min(per_cu * cus, kMaxEnsItems);
-  if (p->ens_wgs > 0) wgs = std::min(wgs, p->ens_wgs);
+  // Two a compute unit unless the caller says otherwise, also where three fit:
+  // the arrivals at the flames' counters grow with the workgroups that share
+  // one (256 flames of three grids, us a step: 256 workgroups 148, 512 119, 736 133).
+  const int wgs = std::min({per_cu * cus, kMaxEnsItems, p->ens_wgs > 0 ? p->ens_wgs : 2 * cus});
   const std::vector<int> sig = ens_signature(p, wgs);
   if (!p->ens_items.empty() && sig == p->ens_sig) return FLAME_OK;
   // an earlier upload may still read the host table; the graph holds the old grid
