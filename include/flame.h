@@ -134,7 +134,10 @@ int flame_step_index(flame_plan plan, int64_t* n);
  * Phi* (symmetrised, kept in the workspace), and
  *   Phi~ <- (Phi* + E_k Phi~ + dt (f~_k + N_k(Phi*, t_{n+1}))) / 2,
  * symmetrised; it runs the row and column kernels twice per step, and with
- * r0_law = 1 it also reads table entry n + 1. nsteps >= 0. */
+ * r0_law = 1 it also reads table entry n + 1. nsteps >= 0. Small flames run
+ * up to 2000 steps in one launch, a workgroup per flame, where their
+ * intermediates fit one workgroup's LDS: n1 n2 <= 2^14, but not 16x1024,
+ * 32x512 and 64x256, with the default grid and points per thread. */
 int flame_step(flame_plan plan, int32_t nsteps);
 
 /* Integral diagnostics of flame `flame` at the current step (the averages of
@@ -230,7 +233,7 @@ int flame_timing_begin(flame_plan plan);
  * [1] column step kernels, [2] diagnostics and other kernels, [3] graph
  * launches (each covering steps_per_graph steps), persistent launches (each
  * covering the steps of one flame_step call, up to 1000) and the launches of
- * small flames, n1 n2 <= 2^14, that run up to 2000 steps at once. Bracketed launches that
+ * small flames that run up to 2000 steps at once (flame_step). Bracketed launches that
  * follow each other share their boundary event, so their intervals include
  * the launch gap. ms4 and counts4 are host arrays of 4 entries. */
 int flame_timing_end(flame_plan plan, double* ms4, int64_t* counts4);
@@ -417,8 +420,7 @@ int flame_circle_diagnostics(const flame_circle_desc* desc, int32_t n_circles, c
  * the kernel sequence flame_step runs on a fresh plan in its default
  * configuration (product grid for n1 >= 128, 16 points per thread, plain
  * stores, direct launches): the column transforms of the state, then a row
- * and a column kernel per step, or for small flames (n1 n2 <= 2^14) launches
- * of many steps. `state` (dev, flame_state_bytes, 16-byte
+ * and a column kernel per step, or for small flames launches of many steps. `state` (dev, flame_state_bytes, 16-byte
  * aligned, the state layout above) holds the state at step index n
  * (time t0 + n dt) and is updated in place; the work is queued on
  * hip_stream (a hipStream_t, 0 for the null stream) of the current device.

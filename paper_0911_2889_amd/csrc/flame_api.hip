@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <algorithm>
 #include <mutex>
 #include <new>
@@ -185,6 +186,7 @@ struct Group {
   int nt = 0;                                  // non-temporal stores: 0 none, 1 Q and W, 2 W, 3 Q
   bool forced = false;                         // some flame of the group has a forcing bound
   int integrator = 0;                          // 0: IF-Euler (one pass per step); 1: IF-Heun (two passes)
+  int max_lds = 0;                             // the device's LDS per workgroup
   int passes() const { return integrator == 1 ? 2 : 1; }
   // the column kernel's variant in pass 0 or 1 of a step
   int col_var(int pass) const {
@@ -206,14 +208,16 @@ struct Group {
     return flame::split_pays(logn1, (long long)flames << (logn2 - 2), true) ? 8 : ff::kPts;
   }
   // The kernel that steps each flame of the group on one workgroup, if there is
-  // one: for the default grid and points per thread. The store kind does not
-  // matter to it (it stores no intermediates).
+  // one and the device has the LDS for it: for the default grid and points per
+  // thread. The store kind does not matter to it (it stores no intermediates).
   flame::KernelLaunch resident() const {
+    const flame::KernelLaunch none{nullptr, 0, 0};
     if (!flame::resident_kernel || col_pts != ff::kPts || row_pts != ff::kPts ||
         product != (logn1 >= flame::kMinLogProduct))
-      return flame::KernelLaunch{nullptr, 0, 0};
-    return flame::resident_kernel(logn1, logn2,
-                                  integrator == 1 ? flame::VAR_HEUN_P : forced ? flame::VAR_EULER_F : flame::VAR_EULER);
+      return none;
+    const flame::KernelLaunch kl = flame::resident_kernel(
+        logn1, logn2, integrator == 1 ? flame::VAR_HEUN_P : forced ? flame::VAR_EULER_F : flame::VAR_EULER);
+    return kl.lds <= max_lds ? kl : none;
   }
   int row_kernel_pts(int flames) const {
     if (logn2 < flame::kMinLogRowProduct || row_pts != ff::kPts) return row_pts;
@@ -781,12 +785,15 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   const bool product2 = s.logn2 >= flame::kMinLogRowProduct;
   Group gr{s.logn1, s.logn2, 0, 1, s.tiles, s.rpairs};
   gr.product = product;
-  const flame::KernelLaunch res = gr.resident();
+  // a resident kernel's tables, where the grid has one; they begin with those
+  // of the row and column kernels (ff::FullPlan's inverse plan is theirs)
+  gr.max_lds = std::numeric_limits<int>::max();
+  const bool small = gr.resident().func != nullptr;
   const size_t tw_col_off = off;
-  if (product || res.func) add_mixed(s.logn1, !product);
+  if (product || small) add_mixed(s.logn1, !product);
   else add_table(tw_spec_pow2(nullptr, s.logn1, ff::kPts), true);
   const size_t tw_row_off = off;
-  if (product2 || res.func) add_mixed(s.logn2, !product2);
+  if (product2 || small) add_mixed(s.logn2, !product2);
   else add_table(tw_spec_pow2(nullptr, s.logn2, ff::kPts), true);
   const size_t off_w = off;
   off = align_up(off + 2 * wq * sizeof(float2));
@@ -806,6 +813,8 @@ int flame_step_noalloc(const flame_desc* desc, void* state, int64_t n, int32_t n
   if (need_lds > max_lds)
     return fail(FLAME_ERR_UNSUPPORTED_SIZE, "grid %d x %d needs %d bytes of LDS per workgroup, the device has %d",
                 desc->n1, desc->n2, need_lds, max_lds);
+  gr.max_lds = max_lds;
+  const flame::KernelLaunch res = gr.resident();
   void* base_v = nullptr;
   rc = scratch_address(dev, &base_v);
   if (rc) return rc;
@@ -1004,6 +1013,7 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
       Group gr{s.logn1, s.logn2, f, 1, s.tiles, s.rpairs};
       gr.product = s.logn1 >= flame::kMinLogProduct;
       gr.integrator = descs[f].integrator;
+      gr.max_lds = max_lds;
       p->groups.push_back(gr);
     }
     p->group_of[f] = (int)p->groups.size() - 1;

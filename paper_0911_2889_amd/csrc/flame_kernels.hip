@@ -221,8 +221,9 @@ int lds_bytes_needed(int logn1, int logn2) {
   const int c = col_lds<kMinLog>(logn1), r = row_lds<kMinLog>(logn2);
   const int m1 = mixed_lds_bytes(logn1), m2 = mixed_lds_bytes(logn2);
   const int a1 = adj_mixed_lds_bytes(logn1), a2 = adj_mixed_lds_bytes(logn2);
+  const int p1 = phys_lds_bytes(logn1), p2 = phys_lds_bytes(logn2);
   int most = c;
-  for (const int b : {r, m1, m2, a1, a2}) most = b > most ? b : most;
+  for (const int b : {r, m1, m2, a1, a2, p1, p2}) most = b > most ? b : most;
   return most;
 }
 

@@ -24,7 +24,8 @@ KernelLaunch col_step_kernel(int logn1, int pts, int var = VAR_EULER);
 KernelLaunch row_step_kernel(int logn2, int pts, bool nt = false);
 void launch_set_step(hipStream_t st, long long* counter, long long value);
 // Largest dynamic LDS (bytes per workgroup) any kernel of an N1 x N2 flame
-// asks for (row, column, product-grid and adjoint kernels, every variant).
+// asks for (row, column, product-grid, adjoint and averages kernels, every
+// variant), but for the resident kernels: those are used only where they fit.
 int lds_bytes_needed(int logn1, int logn2);
 
 // The kernel that runs every step of a call on one workgroup per flame (grid:
@@ -101,6 +102,8 @@ hipError_t launch_ensemble(hipStream_t st, const FlameDev* fls, const EnsembleIt
 // physical_kernels.hip: the averages (launch_row's ROW_DIAG), COL_FIRST with its
 // transforms side by side (false: not for this launch), and the canonical spectrum.
 void launch_diag(int logn2, int groups, int n_spec, hipStream_t st, const FlameDev* fl, long long n, double* out);
+// phys_lds_bytes: the most LDS that those side by side ask for at length 2^logn.
+int phys_lds_bytes(int logn);
 bool launch_first_side(int logn1, int columns, hipStream_t st, const FlameDev* fl, const float2* src);
 void launch_set_spectrum(hipStream_t st, const FlameDev* fl, int flame, int total, const void* half);
 void launch_get_spectrum(hipStream_t st, const FlameDev* fl, int flame, int total, void* half);

@@ -341,7 +341,16 @@ bool first_dispatch(int logn1, int columns, hipStream_t st, const FlameDev* fl, 
   return false;
 }
 
+template <int L>
+int phys_lds(int logn) {
+  if constexpr (L <= kMaxLogSide)
+    return logn == L ? PhysSplit<L>::LDS_BYTES : phys_lds<L + 1>(logn);
+  return 0;
+}
+
 }  // namespace
+
+int phys_lds_bytes(int logn) { return phys_lds<kMinLog>(logn); }
 
 void launch_diag(int logn2, int groups, int n_spec, hipStream_t st, const FlameDev* fl, long long n, double* out) {
   diag_dispatch<kMinLog>(logn2, groups, n_spec, st, fl, n, out);

@@ -85,6 +85,20 @@ struct Res {
   static constexpr bool OK = THREADS <= kResMaxThreads && LDS_BYTES <= kResMaxLds;
 };
 
+// Resident: every grid of N1 N2 <= 2^kResMaxLogs but three, which need 162 to 189 KB.
+template <int L1, int L2>
+constexpr bool resident_as_documented() {
+  if constexpr (L1 + L2 <= kResMaxLogs) {
+    constexpr bool out = (L1 == 4 && L2 == 10) || (L1 == 5 && L2 == 9) || (L1 == 6 && L2 == 8);
+    return Res<L1, L2>::OK != out && resident_as_documented<L1, L2 + 1>();
+  } else if constexpr (L1 + 1 + kMinLog <= kResMaxLogs) {
+    return resident_as_documented<L1 + 1, kMinLog>();
+  } else {
+    return true;
+  }
+}
+static_assert(resident_as_documented<kMinLog, kMinLog>(), "the grids that flame_step's description names");
+
 // A value the compiler cannot see through: what a phase derives from the
 // thread index (addresses, wavenumbers) is then formed in that phase, instead
 // of being kept, and spilled, across all the phases of all the steps.

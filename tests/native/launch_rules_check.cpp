@@ -11,18 +11,50 @@
 #include <hip/hip_runtime.h>
 
 #define ensemble_blocks_per_cu stub_blocks_per_cu
+#define hipDeviceGetAttribute stub_device_attribute
 #include "hipstub/hip_stub.cpp"
+#undef hipDeviceGetAttribute
 #undef ensemble_blocks_per_cu
 
 #include "flame.h"
 
 namespace {
 int g_blocks_per_cu = 2;
+int g_max_lds = 160 * 1024;
+}  // namespace
+
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int dev) {
+  if (a != hipDeviceAttributeMaxSharedMemoryPerBlock) return stub_device_attribute(v, a, dev);
+  *v = g_max_lds;
+  return hipSuccess;
 }
 
 namespace flame {
 int ensemble_blocks_per_cu() { return g_blocks_per_cu; }
 }  // namespace flame
+
+// Resident kernels of 100 KB for n1 n2 <= 2^14, as resident_kernel.hip
+// registers its own; the launches are counted.
+namespace {
+constexpr int kResidentLds = 100 * 1024;
+long g_resident_launches = 0, g_resident_steps = 0;
+
+flame::KernelLaunch resident_info(int logn1, int logn2, int) {
+  if (logn1 + logn2 > flame::kResMaxLogs) return flame::KernelLaunch{nullptr, 0, 0};
+  return flame::KernelLaunch{flame::kDummyKernel, 256, kResidentLds};
+}
+void resident_run(const flame::KernelLaunch& kl, int flames, hipStream_t st, const flame::FlameDev* fl, long long,
+                  int steps, int) {
+  if (kl.func != flame::kDummyKernel || kl.lds > g_max_lds) violation("resident launch past the device's LDS");
+  if (flames < 1 || steps < 1 || steps > flame::kResMaxSteps) violation("resident launch out of range");
+  flame::touch(fl, flames);
+  ++g_resident_launches;
+  g_resident_steps += steps;
+  hip_stub_launch(kl.func, st);
+}
+const bool g_registered =
+    (flame::resident_kernel = &resident_info, flame::resident_launch = &resident_run, true);
+}  // namespace
 
 namespace {
 
@@ -103,12 +135,66 @@ void persistent_default() {
   }
 }
 
+// Where a device has less LDS than a resident kernel asks for, the small
+// flames take the two launches a step, here and in the allocation-free call.
+void resident_lds() {
+  for (int lds : {160 * 1024, 64 * 1024}) {
+    g_max_lds = lds;
+    g_resident_launches = g_resident_steps = 0;
+    Plan pl({desc(64, 128), desc(32, 64, 1)});
+    CHECK(flame_step(pl.p, 3));
+    CHECK(flame_set_graph_steps(pl.p, 2));
+    CHECK(flame_step(pl.p, 4));
+    flame_desc d = desc(64, 128);
+    std::vector<float> s(64 * 128 / 4, 0.f);
+    CHECK(flame_step_noalloc(&d, s.data(), 0, 5, nullptr));
+    EXPECT(lds >= kResidentLds ? g_resident_steps == 3 + 3 + 5 : g_resident_launches == 0);
+  }
+}
+
+// The resident paths of flame_step, its graphs, timing, autotuning and the
+// settings that enter and leave them, in a plan that has other groups too.
+void resident_paths() {
+  for (int graph : {0, 1, 7, 2001}) {
+    Plan pl({desc(64, 128), desc(64, 128), desc(32, 64, 1), desc(128, 128), desc(256, 512)});
+    flame_plan p = pl.p;
+    std::vector<float> spec(256 * 512 / 4, 0.f);
+    for (int f = 0; f < 5; ++f) CHECK(flame_set_spectrum(p, f, spec.data(), 0));
+    g_resident_steps = 0;
+    CHECK(flame_set_graph_steps(p, graph));
+    int64_t n = 0;
+    CHECK(flame_step(p, 2003));
+    CHECK(flame_step_index(p, &n));
+    EXPECT(n == 2003);
+    EXPECT(g_resident_steps == 3 * (graph ? 2003 % graph : 2003));  // three groups; the others are in the graphs
+    for (int it = 0; it < 24; ++it) {
+      CHECK(flame_set_points_per_thread(p, 64, 128, it % 3 == 1 ? 8 : 16, 16));
+      CHECK(flame_set_product_grid(p, 128, 128, it % 2));
+      CHECK(flame_set_forcing(p, 0, it % 4 == 1 ? spec.data() : nullptr));
+      if (it % 5 == 0) CHECK(flame_set_graph_steps(p, it % 10 ? 0 : graph));
+      CHECK(flame_timing_begin(p));
+      CHECK(flame_step(p, it % 3));
+      double ms[4];
+      int64_t cnt[4];
+      CHECK(flame_timing_end(p, ms, cnt));
+    }
+    CHECK(flame_autotune(p, 1, nullptr));
+    CHECK(flame_step(p, 9));
+    CHECK(flame_step_index(p, &n));
+    EXPECT(n == 2003 + 8 * 3 + 9);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "persistent_default")
     persistent_default();
+  else if (what == "resident_lds")
+    resident_lds();
+  else if (what == "resident_paths")
+    resident_paths();
   else
     return 2;
   std::printf("OK\n");

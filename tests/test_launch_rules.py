@@ -36,3 +36,11 @@ def drive(tmp_path_factory):
 
 def test_persistent_grid_is_two_workgroups_per_compute_unit(drive):
     drive("persistent_default")
+
+
+def test_resident_kernels_need_the_lds_they_ask_for(drive):
+    drive("resident_lds")
+
+
+def test_resident_paths_are_clean_under_sanitizers(drive):
+    drive("resident_paths")
