@@ -105,10 +105,10 @@ struct Layout {
   size_t off_tw8[flame::kMaxLog + 1];  // twiddles, 8 points per thread
   size_t off_twm[flame::kMaxLog + 1];  // length 3*2^l/4 (product grids)
   size_t off_twf[flame::kMaxLog + 1];  // length 2^l <= 64, ff::FullPlan (resident kernels)
-  size_t off_tables;   // start of what flame_init uploads: the tables, the flame tables and the tickets, to off_counter
+  size_t off_tables;   // start of what flame_init uploads: the tables and the flame tables, to off_counter
   size_t off_dev;
   size_t off_dev_full;  // device flame table whose W is the adjoint scratch (physical-grid W for diagnostics)
-  size_t off_ticket;   // the diagnostics' counters (FlameDev::ticket)
+  size_t off_ticket;   // the diagnostics' counters, kTicketWords per flame (FlameDev::ticket)
   size_t off_counter;  // step index read by graph replays
   size_t off_diag;     // 4 doubles per flame: flame_diagnostics_host's device copy
   size_t off_ens_items, off_ens_arrive, off_ens_err;  // persistent ensemble launch
@@ -163,12 +163,12 @@ int plan_layout(const flame_desc* descs, int nfl, Layout* L) {
   off = align_up(off + (size_t)nfl * sizeof(flame::FlameDev));
   L->off_dev_full = off;
   off = align_up(off + (size_t)nfl * sizeof(flame::FlameDev));
-  L->off_ticket = off;
-  off = align_up(off + (size_t)(flame::kTickets + 1) * flame::kTicketStride * sizeof(unsigned));
   L->off_counter = off;
   off = align_up(off + sizeof(long long));
   L->off_diag = off;
   off = align_up(off + 4 * sizeof(double) * (size_t)nfl);
+  L->off_ticket = off;
+  off = align_up(off + (size_t)nfl * flame::kTicketWords * sizeof(unsigned));
   L->off_ens_items = off;
   off = align_up(off + sizeof(flame::EnsembleItem) * (size_t)kMaxEnsItems);
   L->off_ens_arrive = off;
@@ -947,8 +947,7 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
   char* base = static_cast<char*>(ws);
   const Layout& L = p->layout;
   // everything flame_init uploads, as one host image and one copy: the twiddle
-  // tables (built in double precision and rounded once), the flame tables and
-  // the tickets (zero)
+  // tables (built in double precision and rounded once) and the flame tables
   std::vector<char> image(L.off_counter - L.off_tables, 0);
   auto at = [&](size_t off) { return reinterpret_cast<float2*>(image.data() + (off - L.off_tables)); };
   for (int l = flame::kMinLog; l <= flame::kMaxLog; ++l) {
@@ -979,7 +978,7 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
     fd.A2 = reinterpret_cast<float2*>(base + L.off_a2[f]);
     fd.S2 = fd.A2;  // Heun's predictor: A2 is free between the calls that use it
     fd.part = reinterpret_cast<double*>(base + L.off_part[f]);
-    fd.ticket = reinterpret_cast<unsigned*>(base + L.off_ticket);
+    fd.ticket = reinterpret_cast<unsigned*>(base + L.off_ticket) + (size_t)f * flame::kTicketWords;
     fd.tw1 = reinterpret_cast<const float2*>(base + L.off_tw[s.logn1]);
     fd.tw2 = reinterpret_cast<const float2*>(base + L.off_tw[s.logn2]);
     fd.tw1_8 = reinterpret_cast<const float2*>(base + L.off_tw8[s.logn1]);
@@ -1043,6 +1042,13 @@ int flame_init(const flame_desc* descs, int32_t n_flames, void* const* states, v
   if (e != hipSuccess) {
     delete p;
     return hip_fail(e, "table upload");
+  }
+  flame::launch_ensemble_reset(p->stream, reinterpret_cast<unsigned*>(base + L.off_ticket),
+                               n_flames * (int)flame::kTicketWords, p->d_err, false);
+  rc = last_launch("ticket reset");
+  if (rc) {
+    delete p;
+    return rc;
   }
   // the image must outlive the asynchronous upload
   e = hipStreamSynchronize(p->stream);

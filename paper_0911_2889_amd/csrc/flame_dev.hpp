@@ -115,8 +115,9 @@ struct ColCfg {
 constexpr int kMinLogProduct = 7;
 constexpr int kMinLogRowProduct = 6;
 
-// One set of counters per plan (its launches follow each other on one stream).
-constexpr unsigned kTickets = 32, kTicketStride = 32;
+// One set of counters per flame, as of partial sums: the averages of two flames
+// of a plan, captured apart, may be replayed at the same time.
+constexpr unsigned kTickets = 32, kTicketStride = 32, kTicketWords = (kTickets + 1) * kTicketStride;
 
 // Resident kernels (resident_kernel.hip) exist for N1 N2 <= 2^kResMaxLogs and
 // where a flame's intermediates fit one workgroup's LDS.

@@ -10,11 +10,15 @@
 
 #include <hip/hip_runtime.h>
 
+#include "flame_kernels.hpp"
+
+#define launch_row stub_launch_row
 #define ensemble_blocks_per_cu stub_blocks_per_cu
 #define hipDeviceGetAttribute stub_device_attribute
 #include "hipstub/hip_stub.cpp"
 #undef hipDeviceGetAttribute
 #undef ensemble_blocks_per_cu
+#undef launch_row
 
 #include "flame.h"
 
@@ -29,8 +33,17 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int dev) {
   return hipSuccess;
 }
 
+namespace {
+flame::FlameDev g_diag;  // the flame of the last launch of averages
+}
+
 namespace flame {
 int ensemble_blocks_per_cu() { return g_blocks_per_cu; }
+void launch_row(int logn2, int mode, int groups, int nfl, hipStream_t st, const FlameDev* fl, long long n,
+                const float* in, float* out, int pts, hipEvent_t e0, hipEvent_t e1, bool nt) {
+  if (mode == ROW_DIAG) g_diag = *fl;
+  stub_launch_row(logn2, mode, groups, nfl, st, fl, n, in, out, pts, e0, e1, nt);
+}
 }  // namespace flame
 
 // Resident kernels of 100 KB for n1 n2 <= 2^14, as resident_kernel.hip
@@ -185,6 +198,23 @@ void resident_paths() {
   }
 }
 
+// Two flames' averages share nothing that a launch writes.
+void averages_apart() {
+  Plan pl({desc(64, 128), desc(64, 128), desc(256, 512)});
+  std::vector<flame::FlameDev> seen;
+  for (int f = 0; f < 3; ++f) {
+    double out[4];
+    CHECK(flame_diagnostics(pl.p, f, out, nullptr));
+    for (unsigned i = 0; i < (flame::kTickets + 1) * flame::kTicketStride; ++i) EXPECT(g_diag.ticket[i] == 0);
+    for (const flame::FlameDev& d : seen) {
+      const long long apart = g_diag.ticket - d.ticket;
+      EXPECT(std::llabs(apart) >= (long long)((flame::kTickets + 1) * flame::kTicketStride));
+      EXPECT(d.part != g_diag.part && d.Wp != g_diag.Wp);
+    }
+    seen.push_back(g_diag);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -195,6 +225,8 @@ int main(int argc, char** argv) {
     resident_lds();
   else if (what == "resident_paths")
     resident_paths();
+  else if (what == "averages_apart")
+    averages_apart();
   else
     return 2;
   std::printf("OK\n");

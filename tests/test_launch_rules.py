@@ -44,3 +44,7 @@ def test_resident_kernels_need_the_lds_they_ask_for(drive):
 
 def test_resident_paths_are_clean_under_sanitizers(drive):
     drive("resident_paths")
+
+
+def test_averages_of_two_flames_share_no_counters(drive):
+    drive("averages_apart")
