@@ -755,7 +755,9 @@ def main():
     dom = "col"
     achieved = nbytes[dom] / (per_launch[dom] * 1e-3) / 1e9
     traffic = measured_traffic(dom, w.name, pts[0] if dom == "col" else pts[1], rows, streaming)
-    row_cols = 3 * w.n2 // 4 if w.n2 >= 64 else w.n2
+    # phi points: 3 N2/4, but N2 where the paper's grid was chosen (rows of 12 points per thread have no other length)
+    full = rows == w.n1 and w.n1 >= 128 and pts[1] != 12
+    row_cols = 3 * w.n2 // 4 if w.n2 >= 64 and not full else w.n2
     row_flops = row_pass_flops(rows, row_cols)
     row_tflops = row_flops / (per_launch["row"] * 1e-3) / 1e12
     result = {

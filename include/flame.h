@@ -240,35 +240,39 @@ int flame_timing_end(flame_plan plan, double* ms4, int64_t* counts4);
 
 /* Points per thread of the step kernels for the flames of grid n1 x n2
  * (col_pts for the column kernel, row_pts for the row kernel; default 16).
- * Rows of n2 >= 64 and, on the product grid (flame_set_product_grid), columns
+ * Columns on the product grid (flame_set_product_grid) and rows of n2 >= 64
  * are transforms of 3/4 of the grid's length (the phi axis is alias-free on
  * 3 N2/4 points as the theta axis is on 3 N1/4), which have kernels for many
  * and for few transforms in a launch: 12 selects those for many (12 points
  * per thread), 8 those for few (a pair's two inverse transforms side by side
  * on twice the threads, or at length 8192 one after the other on all of
  * them), and 16 lets the library choose by the number of transforms. The
- * results are the same bit for bit. On N1 rows, and for rows of n2 < 64, a
- * length-N transform is owned by N/pts threads holding pts points, pts 8 or
- * 16, with radix-pts passes (results agree to rounding); col_pts = 12 needs
- * the product grid (FLAME_ERR_INVALID_ARG otherwise) and row_pts = 12 n2 >= 64
- * (FLAME_ERR_UNSUPPORTED_SIZE otherwise). 8 stops at length 8192
+ * results are the same bit for bit. On N1 rows, for rows of n2 < 64, and for
+ * rows where the product grid was disabled (there row_pts = 12 still selects
+ * 3 N2/4 points), a length-N transform is owned by N/pts threads holding pts
+ * points, pts 8 or 16, with radix-pts passes (results agree to rounding);
+ * col_pts = 12 needs the product grid (FLAME_ERR_INVALID_ARG otherwise) and
+ * row_pts = 12 n2 >= 64 (FLAME_ERR_UNSUPPORTED_SIZE otherwise). 8 stops at length 8192
  * (FLAME_ERR_UNSUPPORTED_SIZE beyond). */
 int flame_set_points_per_thread(flame_plan plan, int32_t n1, int32_t n2, int32_t col_pts, int32_t row_pts);
 int flame_get_points_per_thread(flame_plan plan, int32_t n1, int32_t n2, int32_t* col_pts, int32_t* row_pts);
 
 /* Grid on which flame_step (and its graphs) forms the quadratic term of
  * Eq. (1) for the flames of grid n1 x n2: enable = 0, the N1 x N2 grid of the
- * paper's augmented array (Section 3); enable = 1, a product grid of
- * M1 = 3 N1/4 theta rows (n1 >= 128). The product of two fields truncated to
+ * paper's augmented array (Section 3; with row_pts = 12, 3 N2/4 of its phi
+ * points); enable = 1, a product grid of M1 = 3 N1/4 theta rows (n1 >= 128) and
+ * M2 = 3 N2/4 phi points (n2 >= 64). The product of two fields truncated to
  * |k1| <= K1 = N1/4 - 1 reaches |k1| <= 2 K1; on M1 >= 3 K1 + 1 rows none of
  * its aliases falls inside |k1| <= K1, so the truncated term, and the step,
- * are the same as on N1 rows up to rounding. It moves 3/4 of the
- * intermediate data and does 3/4 of the row transforms. The column
- * transforms then have length 3 N1/4 (mixed radices, a radix-12 pass among
- * them). Diagnostics,
- * state I/O, synthesis and the adjoint always use the N1 x N2 grid. Default:
- * enabled for n1 >= 128. Disabling it while col_pts = 12 fails with
- * FLAME_ERR_INVALID_ARG. Changing it synchronises the stream. */
+ * are the same as on N1 rows up to rounding; the same holds along phi. It moves
+ * 3/4 of the intermediate data and does 3/4 of the row transforms. Its
+ * transforms have lengths 3 N/4 (mixed radices, a radix-12 pass among them).
+ * The adjoint step uses the step's grid; diagnostics, state I/O, synthesis and
+ * the area gradient always use the N1 x N2 grid. Default: enabled for
+ * n1 >= 128; shorter columns have N1 rows, and 3 N2/4 phi points where
+ * n2 >= 64 unless the call is made with enable = 0. Disabling it while
+ * col_pts = 12 fails with FLAME_ERR_INVALID_ARG. Changing it synchronises the
+ * stream. */
 int flame_set_product_grid(flame_plan plan, int32_t n1, int32_t n2, int32_t enable);
 int flame_get_product_grid(flame_plan plan, int32_t n1, int32_t n2, int32_t* enabled);
 

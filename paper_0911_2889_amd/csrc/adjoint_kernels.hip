@@ -13,7 +13,7 @@
 //     dJ/dPhi = -Pi div( grad Phi / (P r0^2 sqrt(1 + |grad Phi|^2/r0^2)) ).
 //
 // One adjoint step is three kernels on the step's grid: adjm_col (3 N1/4 rows)
-// or adj_col (N1 rows), and adjm_row (3 N2/4 phi points) or adj_row (N2 < 64):
+// or adj_col (N1 rows), and adjm_row (3 N2/4 phi points) or adj_row (N2):
 //  * adj_col<ADJ_A>: mu = E lambda per column; column inverse transforms of mu
 //    (-> Q) and of (i kappa1 -+ kappa2) Phi~^n (-> Wp, Wm, as the forward step);
 //  * adj_row<ROW_ADJ>: per row pair, m (one packed real synthesis for two
@@ -606,14 +606,10 @@ template <int LOGN>
 struct AdjRowTable {
   static void launch(int mode, dim3 grid, hipStream_t st, const FlameDev* fl, long long n) {
     constexpr int th = RowCfg<LOGN>::THREADS, lds = RowCfg<LOGN>::LDS_BYTES;
-    if constexpr (LOGN < kMinLogRowProduct) {
-      if (mode == ROW_ADJ) {
-        hipLaunchKernelGGL((adj_row_kernel<LOGN, ROW_ADJ>), grid, dim3(th), lds, st, fl, n);
-        return;
-      }
-    }
     if (mode == ROW_SEED)
       hipLaunchKernelGGL((adj_row_kernel<LOGN, ROW_SEED>), grid, dim3(th), lds, st, fl, n);
+    else
+      hipLaunchKernelGGL((adj_row_kernel<LOGN, ROW_ADJ>), grid, dim3(th), lds, st, fl, n);
   }
 };
 

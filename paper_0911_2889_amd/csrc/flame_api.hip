@@ -183,6 +183,7 @@ struct Group {
   int logn1, logn2, first, count, tiles, rpairs;
   int col_pts = ff::kPts, row_pts = ff::kPts;  // points per thread of the step kernels
   bool product = false;                        // step on the 3N1/4-row product grid
+  bool full = false;                           // the paper's N1 x N2 grid was asked for: N2 phi points too
   int nt = 0;                                  // non-temporal stores: 0 none, 1 Q and W, 2 W, 3 Q
   bool forced = false;                         // some flame of the group has a forcing bound
   int integrator = 0;                          // 0: IF-Euler (one pass per step); 1: IF-Heun (two passes)
@@ -197,8 +198,11 @@ struct Group {
   bool nt_q() const { return nt == 1 || nt == 3; }  // the row kernel's stores of Q
   bool nt_w() const { return nt == 1 || nt == 2; }  // the column kernel's stores of Wp and Wm
   int rows() const { return product ? 3 * (1 << logn1) / 4 : (1 << logn1); }
-  // phi points of the quadratic term's grid: 3 N2/4 where the row kernel has that length
-  int cols() const { return logn2 >= flame::kMinLogRowProduct ? 3 * (1 << logn2) / 4 : (1 << logn2); }
+  // phi points of the quadratic term's grid: 3 N2/4 where the row kernel has
+  // that length, but N2 on the full grid (whose 12 row points per thread are
+  // those of 3 N2/4 points)
+  bool row_product() const { return logn2 >= flame::kMinLogRowProduct && (!full || row_pts == 12); }
+  int cols() const { return row_product() ? 3 * (1 << logn2) / 4 : (1 << logn2); }
   int rgroups() const { return (rows() / 2 + rpairs - 1) / rpairs; }
   // Points per thread that the kernels are asked for: on a product grid 8
   // selects the bodies for few transforms, 12 the others, and 16 (the default)
@@ -213,14 +217,15 @@ struct Group {
   flame::KernelLaunch resident() const {
     const flame::KernelLaunch none{nullptr, 0, 0};
     if (!flame::resident_kernel || col_pts != ff::kPts || row_pts != ff::kPts ||
-        product != (logn1 >= flame::kMinLogProduct))
+        product != (logn1 >= flame::kMinLogProduct) || row_product() != (logn2 >= flame::kMinLogRowProduct))
       return none;
     const flame::KernelLaunch kl = flame::resident_kernel(
         logn1, logn2, integrator == 1 ? flame::VAR_HEUN_P : forced ? flame::VAR_EULER_F : flame::VAR_EULER);
     return kl.lds <= max_lds ? kl : none;
   }
   int row_kernel_pts(int flames) const {
-    if (logn2 < flame::kMinLogRowProduct || row_pts != ff::kPts) return row_pts;
+    if (!row_product()) return row_pts | flame::kRowFull;
+    if (row_pts != ff::kPts) return row_pts;
     return flame::split_pays(logn2, (long long)flames * rows() / 2, false) ? 8 : ff::kPts;
   }
 };
@@ -1445,13 +1450,15 @@ int flame_adjoint_step(flame_plan p, int32_t flame, int64_t n, const void* state
   const Sizes& s = p->layout.sizes[flame];
   flame::FlameDev* fd = p->ddev + flame;
   const Group& gr = p->groups[p->group_of[flame]];
-  if (gr.product) {  // the transpose of the step on its product grid
+  // the transpose of the step on its grid
+  const int row_mode = gr.row_product() ? flame::ROW_ADJ : flame::ROW_ADJ_FULL;
+  if (gr.product) {
     flame::launch_adjp_col(s.logn1, flame::ADJ_A, s.tiles, p->stream, fd, n, state_n, lam_in, nullptr);
-    flame::launch_adj_row(s.logn2, flame::ROW_ADJ, gr.rgroups(), p->stream, fd, n);
+    flame::launch_adj_row(s.logn2, row_mode, gr.rgroups(), p->stream, fd, n);
     flame::launch_adjp_col(s.logn1, flame::ADJ_C, s.tiles, p->stream, fd, n, nullptr, lam_in, lam_out);
   } else {
     flame::launch_adj_col(s.logn1, flame::ADJ_A, s.tiles, p->stream, fd, n, state_n, lam_in, nullptr);
-    flame::launch_adj_row(s.logn2, flame::ROW_ADJ, s.rgroups, p->stream, fd, n);
+    flame::launch_adj_row(s.logn2, row_mode, s.rgroups, p->stream, fd, n);
     flame::launch_adj_col(s.logn1, flame::ADJ_C, s.tiles, p->stream, fd, n, nullptr, lam_in, lam_out);
   }
   p->w_valid[flame] = 0;
@@ -1572,8 +1579,13 @@ int flame_set_points_per_thread(flame_plan p, int32_t n1, int32_t n2, int32_t co
   for (size_t gi = 0; gi < p->groups.size(); ++gi) {
     Group& gr = p->groups[gi];
     if ((1 << gr.logn1) != n1 || (1 << gr.logn2) != n2) continue;
+    const int cols = gr.cols();
     gr.col_pts = col_pts;
     gr.row_pts = row_pts;
+    if (gr.cols() != cols) {
+      rc = apply_rows(p, (int)gi);
+      if (rc) return rc;
+    }
   }
   drop_graph(p);
   return FLAME_OK;
@@ -1606,8 +1618,10 @@ int flame_set_product_grid(flame_plan p, int32_t n1, int32_t n2, int32_t enable)
       return fail(FLAME_ERR_UNSUPPORTED_SIZE, "the product grid needs n1 >= %d", 1 << flame::kMinLogProduct);
     if (!enable && gr.col_pts == 12)
       return fail(FLAME_ERR_INVALID_ARG, "col_pts = 12 runs on the product grid: choose 8 or 16 points first");
-    if (gr.product != (enable != 0)) {
-      gr.product = enable != 0;
+    const bool change = gr.product != (enable != 0) || gr.full != (enable == 0);
+    gr.product = enable != 0;
+    gr.full = enable == 0;
+    if (change) {
       rc = apply_rows(p, (int)gi);
       if (rc) return rc;
     }
@@ -1697,12 +1711,13 @@ static std::vector<TuneCfg> tune_cfgs(const Group& gr) {
 
 static int tune_select(flame_plan p, size_t gi, const TuneCfg& cf) {
   Group& gr = p->groups[gi];
-  const bool grid_change = gr.product != cf.product;
+  const int rows = gr.rows(), cols = gr.cols();
   gr.col_pts = cf.c;
   gr.row_pts = cf.r;
   gr.nt = cf.nt;
   gr.product = cf.product;
-  if (grid_change) return apply_rows(p, (int)gi);
+  gr.full = !cf.product && gr.logn1 >= flame::kMinLogProduct;  // N1 rows by choice: the paper's grid
+  if (gr.rows() != rows || gr.cols() != cols) return apply_rows(p, (int)gi);
   return FLAME_OK;
 }
 

@@ -114,6 +114,8 @@ struct ColCfg {
 // kernel forms the term on 3 N2/4 points for N2 >= 64 (mixed_bodies.hpp).
 constexpr int kMinLogProduct = 7;
 constexpr int kMinLogRowProduct = 6;
+// Added to the row kernel's points per thread: on all N2 phi points.
+constexpr int kRowFull = 64;
 
 // One set of counters per flame, as of partial sums: the averages of two flames
 // of a plan, captured apart, may be replayed at the same time.
@@ -177,10 +179,11 @@ enum RowMode : int { ROW_STEP = 0, ROW_FORWARD = 1, ROW_SYNTH = 2, ROW_DIAG = 3 
 // of mu and of the state's packed gradient; ADJ_C / SEED_C form the
 // divergence from the row transforms in A1, A2 and write the cotangent.
 enum AdjColMode : int { ADJ_A = 0, ADJ_C = 1, SEED_C = 2 };
-// Adjoint row kernel: ROW_ADJ forms w = m grad Phi, ROW_SEED forms
-// w = grad Phi / (r0^2 sqrt(1 + |grad Phi|^2 / r0^2)); both write the row
+// Adjoint row kernel: ROW_ADJ forms w = m grad Phi (on 3 N2/4 phi points where
+// there is a transform of that length; ROW_ADJ_FULL: on N2), ROW_SEED forms
+// w = grad Phi / (r0^2 sqrt(1 + |grad Phi|^2 / r0^2)); all write the row
 // transforms of w1 and i kappa2 w2 to A1, A2.
-enum AdjRowMode : int { ROW_ADJ = 0, ROW_SEED = 1 };
+enum AdjRowMode : int { ROW_ADJ = 0, ROW_SEED = 1, ROW_ADJ_FULL = 2 };
 
 // Keep each thread's twiddles in registers for a kernel's lifetime (the
 // alternative reads the table in every pass).

@@ -1,6 +1,6 @@
-// HIP kernels of the spectral flame step on N1 rows and on rows of fewer than
-// 64 points, and of the physical grid's transforms (gfx950); on the product
-// grids the step runs the kernels of mixed_kernels.hip, in the same two parts.
+// HIP kernels of the spectral flame step on N1 rows and on N2 phi points, and
+// of the physical grid's transforms (gfx950); on the product grids the step
+// runs the kernels of mixed_kernels.hip, in the same two parts.
 //
 // One step of Eq. (1) is two kernels:
 //  * row_kernel<ROW_STEP>: for each pair of grid rows j1, load the column-
@@ -104,9 +104,6 @@ struct RowTable {
     constexpr int th = RowCfg<LOGN>::THREADS, lds = RowCfg<LOGN>::LDS_BYTES;
     const long long* nb = nullptr;
     switch (mode) {
-      case ROW_STEP:
-        hipLaunchKernelGGL((row_kernel<LOGN, ROW_STEP>), grid, dim3(th), lds, st, fl, n, nb, in, out);
-        break;
       case ROW_FORWARD:
         hipLaunchKernelGGL((row_kernel<LOGN, ROW_FORWARD>), grid, dim3(th), lds, st, fl, n, nb, in, out);
         break;
@@ -234,12 +231,13 @@ KernelLaunch col_step_kernel(int logn1, int pts, int var) {
 }
 
 // The row kernel forms the quadratic term on 3 N2/4 phi points where it has a
-// transform of that length (N2 >= 64): three quarters of the butterflies of
-// N2 points in as many passes or fewer.
+// transform of that length (N2 >= 64) and the caller did not ask for all N2
+// (kRowFull): three quarters of the butterflies of N2 points in as many passes
+// or fewer.
 KernelLaunch row_step_kernel(int logn2, int pts, bool nt) {
-  if (logn2 >= kMinLogRowProduct) return rowp_kernel_info(logn2, pts, nt);
+  if (logn2 >= kMinLogRowProduct && !(pts & kRowFull)) return rowp_kernel_info(logn2, pts, nt);
   KernelLaunch out{nullptr, 0, 0};
-  dispatch_info<RowTable, kMinLog>(logn2, &out, pts, nt);
+  dispatch_info<RowTable, kMinLog>(logn2, &out, pts & ~kRowFull, nt);
   return out;
 }
 

@@ -35,6 +35,8 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int dev) {
 
 namespace {
 flame::FlameDev g_diag;  // the flame of the last launch of averages
+flame::FlameDev g_step;  // and of the last row kernel of a step, with its points per thread
+int g_step_pts = 0;
 }
 
 namespace flame {
@@ -42,6 +44,10 @@ int ensemble_blocks_per_cu() { return g_blocks_per_cu; }
 void launch_row(int logn2, int mode, int groups, int nfl, hipStream_t st, const FlameDev* fl, long long n,
                 const float* in, float* out, int pts, hipEvent_t e0, hipEvent_t e1, bool nt) {
   if (mode == ROW_DIAG) g_diag = *fl;
+  if (mode == ROW_STEP) {
+    g_step = *fl;
+    g_step_pts = pts;
+  }
   stub_launch_row(logn2, mode, groups, nfl, st, fl, n, in, out, pts, e0, e1, nt);
 }
 }  // namespace flame
@@ -215,6 +221,36 @@ void averages_apart() {
   }
 }
 
+// The step's grid: the product grid by default, the paper's N1 x N2 where the
+// product grid is disabled, with 3 N2/4 of its phi points at 12 row points.
+void step_grids() {
+  for (const auto& g : {std::pair<int, int>{256, 512}, {64, 512}, {128, 32}}) {
+    const int n1 = g.first, n2 = g.second;
+    const int m1 = n1 >= 128 ? 3 * n1 / 4 : n1, m2 = n2 >= 64 ? 3 * n2 / 4 : n2;
+    Plan pl({desc(n1, n2), desc(n1, n2, 1)});
+    auto grid = [&](int rows, int cols) {
+      CHECK(flame_step(pl.p, 1));
+      EXPECT(g_step.rows == rows && g_step.cols == cols);
+      EXPECT(((g_step_pts & flame::kRowFull) != 0) == (cols == n2));
+      EXPECT((g_step_pts & ~flame::kRowFull) != 12 || cols == m2);
+    };
+    CHECK(flame_set_points_per_thread(pl.p, n1, n2, 8, 16));  // no resident kernel
+    grid(m1, m2);
+    CHECK(flame_set_product_grid(pl.p, n1, n2, 0));
+    for (int pts : {8, 16, 12}) {
+      if (pts == 12 && n2 < 64) continue;
+      CHECK(flame_set_points_per_thread(pl.p, n1, n2, 16, pts));
+      grid(n1, pts == 12 ? m2 : n2);
+    }
+    CHECK(flame_set_points_per_thread(pl.p, n1, n2, 8, 8));
+    grid(n1, n2);
+    if (n1 >= 128) {
+      CHECK(flame_set_product_grid(pl.p, n1, n2, 1));
+      grid(m1, m2);
+    }
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -227,6 +263,8 @@ int main(int argc, char** argv) {
     resident_paths();
   else if (what == "averages_apart")
     averages_apart();
+  else if (what == "step_grids")
+    step_grids();
   else
     return 2;
   std::printf("OK\n");

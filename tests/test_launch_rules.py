@@ -48,3 +48,7 @@ def test_resident_paths_are_clean_under_sanitizers(drive):
 
 def test_averages_of_two_flames_share_no_counters(drive):
     drive("averages_apart")
+
+
+def test_disabling_the_product_grid_gives_the_papers_grid(drive):
+    drive("step_grids")
