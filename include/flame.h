@@ -305,7 +305,8 @@ int flame_get_streaming_stores(flame_plan plan, int32_t n1, int32_t n2, int32_t*
  * The configurations are (col_pts, row_pts) in {16, 8} x {16, 8, 12} on the
  * N1-row grid and, for n1 >= 128, {16, 8, 12}^2 on the product grid (row_pts
  * 12 only where n2 >= 64), each with plain and with non-temporal stores
- * (flame_set_streaming_stores). If a group's choice has both Q and W
+ * (flame_set_streaming_stores); those that come to the same kernels are timed
+ * once, and the default is taken among equals. If a group's choice has both Q and W
  * non-temporal, the same kernels with only W and with only Q non-temporal are
  * timed as well, and the faster of the two replaces it if it runs in at most
  * 1/0.98 of its time (it moves fewer bytes). When graphs are in use
@@ -319,7 +320,7 @@ int flame_get_streaming_stores(flame_plan plan, int32_t n1, int32_t n2, int32_t*
  * synchronises the stream. With the persistent launch enabled
  * (flame_set_persistent), whose kernels are fixed, it fails with
  * FLAME_ERR_INVALID_ARG.
- * *n_configs_tried (nullable) receives the number of timed configurations. */
+ * *n_configs_tried (nullable) receives the number of configurations compared. */
 int flame_autotune(flame_plan plan, int32_t steps, int32_t* n_configs_tried);
 
 /* Run flame_step in graphs of `steps` steps (0: direct launches, the default).

@@ -1709,14 +1709,41 @@ static std::vector<TuneCfg> tune_cfgs(const Group& gr) {
   return cfgs;
 }
 
-static int tune_select(flame_plan p, size_t gi, const TuneCfg& cf) {
-  Group& gr = p->groups[gi];
-  const int rows = gr.rows(), cols = gr.cols();
+static void tune_apply(Group& gr, const TuneCfg& cf) {
   gr.col_pts = cf.c;
   gr.row_pts = cf.r;
   gr.nt = cf.nt;
   gr.product = cf.product;
   gr.full = !cf.product && gr.logn1 >= flame::kMinLogProduct;  // N1 rows by choice: the paper's grid
+}
+
+// What a configuration launches. Several come to the same kernels (on the
+// product grid 16 points per thread are 8 or 12, and the bodies for few
+// transforms have plain stores only): those share one time, so that none is
+// chosen over an equal one by noise.
+struct TuneKernels {
+  bool product;
+  int cols;
+  const void *resident, *row, *col;
+  TuneKernels(Group gr, const TuneCfg& cf) {
+    tune_apply(gr, cf);
+    product = gr.product;
+    cols = gr.cols();
+    resident = gr.resident().func;
+    row = flame::row_step_kernel(gr.logn2, gr.row_kernel_pts(gr.count), gr.nt_q()).func;
+    col = gr.product ? flame::colp_kernel_info(gr.logn1, flame::COL_STEP, gr.col_kernel_pts(gr.count), gr.col_var(0)).func
+                     : flame::col_step_kernel(gr.logn1, gr.col_pts, gr.col_var(0)).func;
+  }
+  bool operator==(const TuneKernels& o) const {
+    if (resident || o.resident) return resident == o.resident;
+    return product == o.product && cols == o.cols && row == o.row && col == o.col;
+  }
+};
+
+static int tune_select(flame_plan p, size_t gi, const TuneCfg& cf) {
+  Group& gr = p->groups[gi];
+  const int rows = gr.rows(), cols = gr.cols();
+  tune_apply(gr, cf);
   if (gr.rows() != rows || gr.cols() != cols) return apply_rows(p, (int)gi);
   return FLAME_OK;
 }
@@ -1771,8 +1798,11 @@ static int autotune_jointly(flame_plan p, int steps, long long n0, hipEvent_t ev
       const Group& gr = p->groups[gi];
       const TuneCfg cur{gr.product, gr.col_pts, gr.row_pts, gr.nt};
       TuneCfg keep = cur;
+      std::vector<TuneKernels> timed{TuneKernels(gr, cur)};
       for (const TuneCfg& cf : tune_cfgs(gr)) {
-        if (cf == cur) continue;
+        const TuneKernels k(gr, cf);
+        if (std::find(timed.begin(), timed.end(), k) != timed.end()) continue;
+        timed.push_back(k);
         rc = tune_select(p, gi, cf);
         float t = 0.f;
         if (rc == FLAME_OK) rc = trial(&t);
@@ -1834,30 +1864,44 @@ static int autotune_alone(flame_plan p, size_t gi, int steps, long long n0, hipE
   };
   const std::vector<TuneCfg> cfgs = tune_cfgs(gr);
   const TuneCfg default_cfg{gr.logn1 >= flame::kMinLogProduct, ff::kPts, ff::kPts, 0};
+  std::vector<TuneKernels> kernels;
+  std::vector<size_t> first;  // the first configuration of the same kernels: it is the one timed
+  for (const TuneCfg& cf : cfgs) {
+    kernels.push_back(TuneKernels(gr, cf));
+    first.push_back(std::find(kernels.begin(), kernels.end(), kernels.back()) - kernels.begin());
+  }
   std::vector<float> t_best(cfgs.size(), 1e30f);
   for (int round = 0; round < kAutotuneRounds; ++round) {
     for (size_t ci = 0; ci < cfgs.size(); ++ci) {
+      if (first[ci] != ci) continue;
       const int rc = time_cfg(cfgs[ci], &t_best[ci]);
       if (rc) return rc;
-      if (round == 0) ++*tried;
     }
   }
+  *tried += (int)cfgs.size();
   size_t best = 0, dflt = 0;
   for (size_t ci = 0; ci < cfgs.size(); ++ci) {
+    t_best[ci] = t_best[first[ci]];
     if (t_best[ci] < t_best[best]) best = ci;
     if (cfgs[ci] == default_cfg) dflt = ci;
   }
-  if (t_best[best] > kAutotuneMargin * t_best[dflt]) best = dflt;
+  if (first[best] == first[dflt] || t_best[best] > kAutotuneMargin * t_best[dflt]) best = dflt;
   TuneCfg pick = cfgs[best];
   if (pick.nt == 1) {
     const TuneCfg alt[2] = {TuneCfg{pick.product, pick.c, pick.r, 2}, TuneCfg{pick.product, pick.c, pick.r, 3}};
     float t_alt[2] = {1e30f, 1e30f};
+    for (int k = 0; k < 2; ++k) {
+      const size_t known = std::find(kernels.begin(), kernels.end(), TuneKernels(gr, alt[k])) - kernels.begin();
+      if (known < kernels.size()) t_alt[k] = t_best[known];
+    }
+    const bool timed[2] = {t_alt[0] < 1e30f, t_alt[1] < 1e30f};
     for (int round = 0; round < kAutotuneRounds; ++round)
       for (int k = 0; k < 2; ++k) {
+        if (timed[k]) continue;
         const int rc = time_cfg(alt[k], &t_alt[k]);
         if (rc) return rc;
-        if (round == 0) ++*tried;
       }
+    *tried += 2;
     const int k = t_alt[0] <= t_alt[1] ? 0 : 1;
     if (kAutotuneMargin * t_alt[k] <= t_best[best]) pick = alt[k];
   }

@@ -13,12 +13,18 @@
 #include "flame_kernels.hpp"
 
 #define launch_row stub_launch_row
+#define col_step_kernel stub_col_step_kernel
+#define row_step_kernel stub_row_step_kernel
+#define colp_kernel_info stub_colp_kernel_info
 #define ensemble_blocks_per_cu stub_blocks_per_cu
 #define hipDeviceGetAttribute stub_device_attribute
 #include "hipstub/hip_stub.cpp"
 #undef hipDeviceGetAttribute
 #undef ensemble_blocks_per_cu
 #undef launch_row
+#undef col_step_kernel
+#undef row_step_kernel
+#undef colp_kernel_info
 
 #include "flame.h"
 
@@ -37,16 +43,36 @@ namespace {
 flame::FlameDev g_diag;  // the flame of the last launch of averages
 flame::FlameDev g_step;  // and of the last row kernel of a step, with its points per thread
 int g_step_pts = 0;
+long g_row_steps = 0;
+
+// A kernel for each choice, as the library has them: on a product grid 8
+// points are the bodies for few transforms, which have plain stores only.
+const char g_kernels[4][128] = {};
+flame::KernelLaunch a_kernel(int kind, int pts, int var) {
+  return flame::KernelLaunch{&g_kernels[kind][(pts & 31) * 4 + (var & 3)], 256, 0};
+}
 }
 
 namespace flame {
 int ensemble_blocks_per_cu() { return g_blocks_per_cu; }
+KernelLaunch col_step_kernel(int, int pts, int var) {
+  return pts == 12 ? KernelLaunch{nullptr, 0, 0} : a_kernel(0, pts, (var & VAR_NT) != 0);
+}
+KernelLaunch colp_kernel_info(int logn1, int, int pts, int var) {
+  if (logn1 < kMinLogProduct) return KernelLaunch{nullptr, 0, 0};
+  return a_kernel(1, pts == 8 ? 8 : 12, pts != 8 && (var & VAR_NT) != 0);
+}
+KernelLaunch row_step_kernel(int logn2, int pts, bool nt) {
+  if (logn2 < kMinLogRowProduct || (pts & kRowFull)) return a_kernel(2, pts, nt);
+  return a_kernel(3, pts == 8 ? 8 : 12, pts != 8 && nt);
+}
 void launch_row(int logn2, int mode, int groups, int nfl, hipStream_t st, const FlameDev* fl, long long n,
                 const float* in, float* out, int pts, hipEvent_t e0, hipEvent_t e1, bool nt) {
   if (mode == ROW_DIAG) g_diag = *fl;
   if (mode == ROW_STEP) {
     g_step = *fl;
     g_step_pts = pts;
+    ++g_row_steps;
   }
   stub_launch_row(logn2, mode, groups, nfl, st, fl, n, in, out, pts, e0, e1, nt);
 }
@@ -251,6 +277,33 @@ void step_grids() {
   }
 }
 
+// Configurations of the same kernels are timed once, and equal times leave the default.
+void autotune_equals() {
+  for (int joint : {0, 1}) {
+    std::vector<flame_desc> ds{desc(256, 512)};
+    if (joint) ds.push_back(desc(512, 512));
+    Plan pl(ds);
+    CHECK(flame_set_points_per_thread(pl.p, 256, 512, 8, 8));
+    if (joint) CHECK(flame_set_graph_steps(pl.p, 2));
+    g_row_steps = 0;
+    int32_t tried = 0, cp = 0, rp = 0, product = 0, nt = -1;
+    CHECK(flame_autotune(pl.p, 1, &tried));
+    EXPECT(tried == 30 * (int)ds.size());
+    // 12 kernel pairs on N1 rows; on the product grid three column and three
+    // row kernels (few; many; many, non-temporal), without the two pairs that
+    // mix the bodies for many transforms with different store kinds. Each
+    // pair takes two launches in each of three rounds; jointly, three
+    // repetitions of one step for the other 18 pairs of each group (and the
+    // first trial), with the other group beside it.
+    const long alone = 6 * (12 + 7);
+    EXPECT(g_row_steps == (joint ? 2 * alone + 2 * 3 * (1 + 2 * 18) : alone));
+    CHECK(flame_get_points_per_thread(pl.p, 256, 512, &cp, &rp));
+    CHECK(flame_get_product_grid(pl.p, 256, 512, &product));
+    CHECK(flame_get_streaming_stores(pl.p, 256, 512, &nt));
+    EXPECT(cp == 16 && rp == 16 && product == 1 && nt == 0);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -265,6 +318,8 @@ int main(int argc, char** argv) {
     averages_apart();
   else if (what == "step_grids")
     step_grids();
+  else if (what == "autotune_equals")
+    autotune_equals();
   else
     return 2;
   std::printf("OK\n");

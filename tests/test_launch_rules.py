@@ -52,3 +52,7 @@ def test_averages_of_two_flames_share_no_counters(drive):
 
 def test_disabling_the_product_grid_gives_the_papers_grid(drive):
     drive("step_grids")
+
+
+def test_autotuner_times_equal_kernels_once(drive):
+    drive("autotune_equals")
