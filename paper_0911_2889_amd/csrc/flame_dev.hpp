@@ -138,9 +138,10 @@ constexpr int kMaxLogFull = 6;
 // for the rows (768 waves: 8.8 against 9.3 us). At 4096 points a workgroup of
 // either kind is one transform and fills its compute unit's issue slots, and
 // side by side is slower (9.5 against 8.5 us for 96 row pairs). At 8192 points
-// the variant is 512 lanes instead of 256: faster while every compute unit
-// has at most one transform (128x8192 14.0 against 16.5 us), slower where two
-// workgroups of 256 threads can share one (8192x8192: 196 against 161 us).
+// the variant is 768 lanes instead of 256: faster while every compute unit
+// has at most one transform (128x8192 12.9 against 16.5 us), slower where two
+// workgroups of 256 threads can share one (8192x8192: 196, with 512 lanes,
+// against 161 us).
 constexpr bool split_pays(int logn, long long transforms, bool columns) {
   const long long waves = transforms * ((1 << logn) / 16) / 64;
   return logn <= 11 ? waves <= (columns ? 512 : 1024) : logn == 13 && transforms <= 256;

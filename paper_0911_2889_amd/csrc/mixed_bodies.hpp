@@ -20,17 +20,25 @@ namespace flame {
 // workgroups of 256 threads share a compute unit instead of one of 512.
 constexpr int mix_lanes(int logn) { return (1 << logn) / (logn == 13 ? 32 : 16); }
 
+// Lanes per transform of 8192 points where there are few: one butterfly each
+// in the radix-8 passes (the radix-12 pass leaves 4 of the 12 waves idle). A
+// compute unit has one transform at a time, of 768 lanes rather than 512: 8192x16
+// column kernel 16.0 -> 15.6 us, 16x8192 row kernel 13.3 -> 12.6. (Plans of
+// 16, 16, 4 and 6 points took 15.1 and 12.6. Both inverse transforms of a
+// column pass by pass, in the same waits: 16.0.)
+constexpr int kFewLanes13 = 768;
+
 // Whether a transform's exchanges alternate between two areas, so that each
-// needs one workgroup barrier instead of two: for the workgroup of 512 lanes
-// that has its compute unit to itself, where the barriers are idle time.
-// Measured: 8192x16 column kernel 16.9 -> 15.9 us, 16x8192 row kernel 14.0 -> 13.6.
-constexpr bool mix_two_areas(int logn, int g) { return logn == 13 && g == 512; }
+// needs one workgroup barrier instead of two: for that workgroup, whose
+// barriers are idle time. Measured: 8192x16 column kernel 17.0 -> 15.6 us,
+// 16x8192 row kernel 13.9 -> 12.8.
+constexpr bool mix_two_areas(int logn, int g) { return logn == 13 && g == kFewLanes13; }
 
 // Column kernel: G lanes and T columns as the N1-row kernels (ColCfg).
 template <int LOGN1, int G_ = mix_lanes(LOGN1)>
 struct ColMix {
   static constexpr int N1 = 1 << LOGN1, NB = N1 / 16;
-  static constexpr int G = G_, RB = NB / G;  // RB: radix-12 butterflies per lane
+  static constexpr int G = G_, RB = G > NB ? 1 : NB / G;  // RB: radix-12 butterflies per lane (lanes t >= NB: none)
   static constexpr int T = col_tile_for(NB), TQ = q_tile_for(NB), QS = ff::ilog2c(TQ);
   using F = ff::Mix<typename ff::MixPlan<LOGN1>::F, G, T>;
   using I = ff::Mix<typename ff::MixPlan<LOGN1>::I, G, T>;
@@ -46,7 +54,7 @@ struct ColMix {
 template <int LOGN2, int G_ = mix_lanes(LOGN2)>
 struct RowMix {
   static constexpr int N2 = 1 << LOGN2, NB = N2 / 16;
-  static constexpr int G = G_, RB = NB / G;
+  static constexpr int G = G_, RB = G > NB ? 1 : NB / G;
   static constexpr int B = NB >= 256 ? 1 : 256 / NB;
   using F = ff::Mix<typename ff::MixPlan<LOGN2>::F, G, B>;
   using I = ff::Mix<typename ff::MixPlan<LOGN2>::I, G, B>;
@@ -101,7 +109,7 @@ struct MixTw {
 };
 // Rows (logn, g: the transform's 2^logn and its lanes): reading them late costs
 // 3 % of the row kernel at 2048x4096.
-constexpr bool mix_held(int logn, int g) { return logn < 13 || (logn == 13 && g == 512); }
+constexpr bool mix_held(int logn, int g) { return logn < 13 || (logn == 13 && g == kFewLanes13); }
 // Columns: up to 1024 points the registers are worth more as further waves
 // (32 flames of 512x1024: column kernel 25.6 -> 24.0 us).
 constexpr bool mix_held_col(int logn, int g) { return logn > 10 && mix_held(logn, g); }
@@ -170,6 +178,8 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
   constexpr int T = C::T, G = C::G, NB = C::NB, RB = C::RB, L = C::L, N1 = C::N1, TQ = C::TQ, QS = C::QS;
   extern __shared__ float2 lds[];
   const int c = tid % T, t = tid / T;
+  const bool act = G <= NB || t < NB;  // lanes of the radix-12 pass; the others read lane 0's modes (unused)
+  const int jt = act ? t : 0;
   const int m = tile * T + c;
   const bool live = m < f.m;
   float2* const my = lds + c;
@@ -178,7 +188,7 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
   // kept mode i = 8 b + kk of this lane, in butterfly t + G b of the radix-12
   // pass: k1 = t + G b + NB kk >= 0 for kk < 4, then t + G b - NB (8 - kk) < 0;
   // it is input or output kk, or kk + 4, of that butterfly
-  auto k1_of = [&](int i) { return t + G * (i >> 3) + NB * ((i & 7) < 4 ? (i & 7) : (i & 7) - 8); };
+  auto k1_of = [&](int i) { return jt + G * (i >> 3) + NB * ((i & 7) < 4 ? (i & 7) : (i & 7) - 8); };
   auto reg_of = [](int i) { return 12 * (i >> 3) + ((i & 7) < 4 ? (i & 7) : (i & 7) + 4); };
   constexpr int KEEP = 8 * RB;
 
@@ -223,18 +233,18 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
       const float kap1 = f.s1 * (float)k1;
       const float e = growth_factor(norm2(kap1, kap2c), sc, f.gamma);
       float2 val = update_mode<VAR>(e, old[kk], q, frc[kk], prd[kk], sc.a, ac, dtf);
-      if (kk == 4 && t == 0) val = make_float2(0.f, 0.f);  // k1 = -N1/4 lies outside the box
+      if (kk == 4 && jt == 0) val = make_float2(0.f, 0.f);  // k1 = -N1/4 lies outside the box
       sv[kk] = val;
     }
     if (tile == 0) {
       // symmetrise column k2 = 0 (group c == 0): copy k1 > 0 conjugated onto -k1
-      if (c == 0) {
+      if (c == 0 && act) {
 #pragma unroll
         for (int kk = 0; kk < KEEP; ++kk)
           if ((kk & 7) < 4) my2[k1_of(kk)] = sv[kk];
       }
       __syncthreads();
-      if (c == 0) {
+      if (c == 0 && act) {
 #pragma unroll
         for (int kk = 0; kk < KEEP; ++kk)
           if ((kk & 7) >= 4 && k1_of(kk) > -N1 / 4) sv[kk] = ff::cconj(my2[-k1_of(kk)]);
@@ -242,7 +252,7 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
       }
       __syncthreads();
     }
-    if (live) {
+    if (live && act) {
       gf2* const Dc = VAR == VAR_HEUN_P ? Pc : Sc;  // the predictor goes to S2
 #pragma unroll
       for (int kk = 0; kk < KEEP; ++kk) st(Dc + k1_of(kk), sv[kk]);
@@ -294,6 +304,8 @@ __device__ __forceinline__ void rowm_body(const FlameDev& f, int group, int tid)
   constexpr int B = C::B, G = C::G, NB = C::NB, RB = C::RB;
   extern __shared__ float2 lds[];
   const int p = tid % B, t = tid / B;
+  const bool act = G <= NB || t < NB;  // as colm_body
+  const int jt = act ? t : 0;
   const int pair = group * B + p;
   const int n1 = f.rows, ts = f.tshift, mcols = f.m;
   const bool live = pair < n1 / 2;
@@ -312,18 +324,18 @@ __device__ __forceinline__ void rowm_body(const FlameDev& f, int group, int tid)
   const int pbase4 = (pl >> 1) * mcols, poff = (pl & 1) << 1;
 #pragma unroll
   for (int b = 0; b < RB; ++b) {
-    const int j = t + G * b;
+    const int j = jt + G * b;
 #pragma unroll
     for (int r = 0; r < 4; ++r) ld_pair(Wp + (((pbase4 + j + NB * r) << 2) + poff), v[0][12 * b + r], v[1][12 * b + r]);
 #pragma unroll
     for (int r = 8; r < 12; ++r) {
       const int mm = NB * (12 - r) - j;  // k2 = -mm; mm = mcols at r = 8, j = 0
-      ld_pair(Wm + (((pbase4 + (r > 8 || b > 0 || t > 0 ? mm : 0)) << 2) + poff), v[0][12 * b + r], v[1][12 * b + r]);
+      ld_pair(Wm + (((pbase4 + (r > 8 || b > 0 || jt > 0 ? mm : 0)) << 2) + poff), v[0][12 * b + r], v[1][12 * b + r]);
     }
   }
   const MixTw<I, mix_held(LOGN2, G_)> wi(f.twmb, t);
-  v[0][8] = t > 0 ? v[0][8] : make_float2(0.f, 0.f);  // b = 0, r = 8
-  v[1][8] = t > 0 ? v[1][8] : make_float2(0.f, 0.f);
+  v[0][8] = jt > 0 ? v[0][8] : make_float2(0.f, 0.f);  // b = 0, r = 8
+  v[1][8] = jt > 0 ? v[1][8] : make_float2(0.f, 0.f);
   constexpr int PL = I::NPASS - 1;  // an inverse's last pass and the forward's first share their register map
   static_assert(I::radix(PL) == F::radix(0) && I::rounds(PL) == F::rounds(0), "forward plan = inverse plan reversed");
   constexpr int NV = I::rounds(PL) * I::radix(PL);
@@ -349,12 +361,14 @@ __device__ __forceinline__ void rowm_body(const FlameDev& f, int group, int tid)
   // k = j + NB r in [0, K2] (r < 4): Y(-k) is output 11 - r of butterfly NB - j
   // (of this one, output 12 - r, for j = 0). Only those four go through LDS.
   static_assert(F::bf(F::NPASS - 1) == NB, "radix-12 last pass");
+  if (act) {
 #pragma unroll
-  for (int b = 0; b < RB; ++b)
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
-    for (int r = 8; r < 12; ++r) my2[(t + G * b + NB * (r - 8)) * B] = y[12 * b + r];
+      for (int r = 8; r < 12; ++r) my2[(t + G * b + NB * (r - 8)) * B] = y[12 * b + r];
+  }
   __syncthreads();
-  if (live) {
+  if (live && act) {
 #pragma unroll
     for (int b = 0; b < RB; ++b)
 #pragma unroll

@@ -84,9 +84,9 @@ KernelLaunch rowm_dispatch(int logn2, bool nt) {
 template <int L, int VAR>
 KernelLaunch cols_info(int mode) {
   if constexpr (L > 12) {  // side by side would take 1024 threads of 128 registers: one after the other on all lanes
-    using C = ColMix<L, ColMix<L>::NB>;
-    const void* fn = mode == COL_FIRST ? reinterpret_cast<const void*>(&colm_kernel<L, COL_FIRST, VAR_EULER, C::NB>)
-                                       : reinterpret_cast<const void*>(&colm_kernel<L, COL_STEP, VAR, C::NB>);
+    using C = ColMix<L, kFewLanes13>;
+    const void* fn = mode == COL_FIRST ? reinterpret_cast<const void*>(&colm_kernel<L, COL_FIRST, VAR_EULER, kFewLanes13>)
+                                       : reinterpret_cast<const void*>(&colm_kernel<L, COL_STEP, VAR, kFewLanes13>);
     return KernelLaunch{fn, C::THREADS, C::LDS_BYTES};
   } else {
     using C = ColSplit<L>;
@@ -124,8 +124,8 @@ KernelLaunch rows_dispatch(int logn2) {
   } else {
     if (logn2 != L) return rows_dispatch<L + 1>(logn2);
     if constexpr (L > 12) {
-      using C = RowMix<L, RowMix<L>::NB>;
-      return KernelLaunch{reinterpret_cast<const void*>(&rowm_kernel<L, false, C::NB>), C::THREADS, C::LDS_BYTES};
+      using C = RowMix<L, kFewLanes13>;
+      return KernelLaunch{reinterpret_cast<const void*>(&rowm_kernel<L, false, kFewLanes13>), C::THREADS, C::LDS_BYTES};
     } else {
       using C = RowSplit<L>;
       return KernelLaunch{reinterpret_cast<const void*>(&rows_kernel<L>), C::THREADS, C::LDS_BYTES,
@@ -168,11 +168,11 @@ int mixed_lds(int logn) {
     if (logn != L) return mixed_lds<L + 1>(logn);
     int b = RowMix<L>::LDS_BYTES;
     if constexpr (L < 12) b = RowSplit<L>::LDS_BYTES > b ? RowSplit<L>::LDS_BYTES : b;
-    if constexpr (L == 13) b = RowMix<L, 512>::LDS_BYTES > b ? RowMix<L, 512>::LDS_BYTES : b;
+    if constexpr (L == 13) b = RowMix<L, kFewLanes13>::LDS_BYTES > b ? RowMix<L, kFewLanes13>::LDS_BYTES : b;
     if constexpr (L >= kMinLogProduct) {
       b = ColMix<L>::LDS_BYTES > b ? ColMix<L>::LDS_BYTES : b;
       if constexpr (L < 12) b = ColSplit<L>::LDS_BYTES > b ? ColSplit<L>::LDS_BYTES : b;
-      if constexpr (L == 13) b = ColMix<L, 512>::LDS_BYTES > b ? ColMix<L, 512>::LDS_BYTES : b;
+      if constexpr (L == 13) b = ColMix<L, kFewLanes13>::LDS_BYTES > b ? ColMix<L, kFewLanes13>::LDS_BYTES : b;
     }
     return b;
   }
