@@ -226,7 +226,7 @@ struct Group {
   int row_kernel_pts(int flames) const {
     if (!row_product()) return row_pts | flame::kRowFull;
     if (row_pts != ff::kPts) return row_pts;
-    return flame::split_pays(logn2, (long long)flames * rows() / 2, false) ? 8 : ff::kPts;
+    return flame::split_pays_rows(logn2, (long long)flames * rows() / 2) ? 8 : ff::kPts;
   }
 };
 

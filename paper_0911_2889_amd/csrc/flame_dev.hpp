@@ -146,6 +146,13 @@ constexpr bool split_pays(int logn, long long transforms, bool columns) {
   const long long waves = transforms * ((1 << logn) / 16) / 64;
   return logn <= 11 ? waves <= (columns ? 512 : 1024) : logn == 13 && transforms <= 256;
 }
+// The step's row kernel. Rows of at most 256 points have two passes and one
+// exchange, little to wait for, and half as many waves are enough for them: at
+// 768 waves 8192x256 takes 7.5 us side by side and 6.6 one after the other,
+// 16384x128 6.6 and 6.1 (4096x512 7.8 and 8.0); at 384, 4096x256, 5.3 and 5.7.
+constexpr bool split_pays_rows(int logn, long long pairs) {
+  return split_pays(logn, pairs, false) && (logn > 8 || pairs * ((1 << logn) / 16) / 64 <= 512);
+}
 
 // Row kernel: B = max(1, 16*256/N2) row pairs per workgroup, interleaved.
 // WPE: the minimum waves per SIMD it is compiled for; at N2 = 8192 with 16
