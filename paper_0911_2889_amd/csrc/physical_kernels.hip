@@ -35,6 +35,17 @@ FLAME_POW_PLAN(11, 16, 16, 8);
 #undef FLAME_POW_PLAN
 constexpr int kMaxLogSide = 11;  // longer transforms run one after another (split_pays)
 
+// Whether a row pair's two transforms of the averages run side by side: as the
+// step's (split_pays), but short rows less long, because the spectral sums
+// fill part of the chip beside them. Averages one after the other and side by
+// side, us: rows of at most 512 points, at 1024 waves 8192x256 25.4 and 31.4,
+// 4096x512 23.6 and 27.8, at 512 waves 4096x256 19.2 and 20.8; 1024 points, at
+// 1024 waves 23.7 and 24.0, at 512 17.6 and 16.5; 2048 points, at 1024 21.7 and 20.8.
+constexpr bool diag_split_pays(int logn, long long pairs) {
+  const long long waves = pairs * ((1 << logn) / 16) / 64;
+  return split_pays(logn, pairs, false) && waves <= (logn <= 9 ? 256 : logn == 10 ? 512 : 1024);
+}
+
 // Two inverse transforms side by side on two groups of G lanes (ColSplit, RowSplit).
 template <int LOGN>
 struct PhysSplit {
@@ -316,7 +327,7 @@ void diag_dispatch(int logn2, int groups, int n_spec, hipStream_t st, const Flam
     if constexpr (L <= kMaxLogSide) {
       using C = PhysSplit<L>;
       const int pairs = groups * RowCfg<L>::B;
-      if (split_pays(L, pairs, false)) {
+      if (diag_split_pays(L, pairs)) {
         const int n_area = (pairs + C::T - 1) / C::T;
         hipLaunchKernelGGL(diag_side_kernel<L>, dim3(n_area + n_spec), dim3(C::THREADS), C::LDS_BYTES, st, fl, n,
                            n_area, n_spec, out);
