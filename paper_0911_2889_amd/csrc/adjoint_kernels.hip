@@ -189,10 +189,16 @@ __global__ void __launch_bounds__(ColCfg<LOGN1>::THREADS) __attribute__((amdgpu_
 // column or row pair; NG = 2: the two forward ones of a column), or run them
 // one after another on N/16 lanes (NG = 1). As for the step's kernels
 // (split_pays), side by side is for launches that leave most of the chip idle.
+// At 8192 points one after another means 768 lanes and two exchange areas, for
+// the reasons at kFewLanes13 and mix_two_areas; here for many transforms too,
+// since three transforms' data leave no registers for a second workgroup
+// (adjoint steps: 16x8192 33.1 -> 30.3 us, 8192x64 31.8 -> 29.0, 8192x8192 682
+// -> 641; 512 lanes with two areas 31.6, 30.7 and 659, 768 with one 32.1, 31.1
+// and 675).
 template <int LOGN, int NG>
 struct AdjMix {
   static constexpr int N = 1 << LOGN, NB = N / 16;
-  static constexpr int G = NG > 1 ? split_lanes(LOGN) : NB;
+  static constexpr int G = NG > 1 ? split_lanes(LOGN) : (LOGN == 13 ? kFewLanes13 : NB);
   static constexpr int T = NG > 1 ? (G >= 64 ? 1 : 64 / G) : (G >= 256 ? 1 : 256 / G);
   // twiddles in registers (MixTw); one after another, a row kernel holds both
   // rows' inputs and m beside its transform, and from 2048 points on spills
@@ -201,7 +207,8 @@ struct AdjMix {
   using I = ff::Mix<typename ff::MixPlan<LOGN>::I, G, T>;
   static constexpr int L = F::N, AREA = F::LDS > I::LDS ? F::LDS : I::LDS;
   static constexpr int THREADS = NG * G * T;
-  static constexpr int LDS_BYTES = 8 * NG * AREA;
+  static constexpr bool TWO = NG == 1 && LOGN == 13;  // two exchange areas (mix_two_areas)
+  static constexpr int LDS_BYTES = 8 * NG * (TWO ? 2 : 1) * AREA;
 };
 
 template <int LOGN1, int MODE, int NG>
@@ -225,6 +232,7 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
   const bool live = m < f.m;
   const bool act = G == NB || t < NB;  // lanes of the radix-12 pass
   float2* const my = lds + c + h * C::AREA;
+  float2* const my2 = my + (C::TWO ? C::AREA : 0);
   const size_t tile_base = ((((size_t)m >> QS) * L) << QS) + (m & (TQ - 1));  // column m of Q, A1, A2
   const size_t col = (size_t)m * f.h1 + N1 / 4;  // element k1 of column m at col + k1
   // loads carry no condition (a branch around a load makes the compiler wait
@@ -260,7 +268,7 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
         const float2 mu = ff::cscale(lm[kk], efactor(f, sc, k1, kap2)), z = slope(kap1, kp, sv[kk]);
         v[kk < 4 ? kk : kk + 4] = job == 0 ? mu : z;
       }
-      mix_fft<I, true, true>(v, my, tw);
+      mix_fft_in<I, true, true, C::TWO>(v, q & 1 ? my2 : my, q & 1 ? my : my2, tw);
       if (live) {
         constexpr int P = I::NPASS - 1, R = I::radix(P);
         gf2* const wd = glob(job == 1 ? f.Wp : f.Wm);
@@ -298,7 +306,7 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
           for (int r = 0; r < F::radix(0); ++r)
             v[b * F::radix(0) + r] = ld(srcp + (size_t)(t + G * b + r * F::bf(0)) * TQ);
         }
-      mix_fft<F, false, false>(v, my, tw);
+      mix_fft_in<F, false, false, C::TWO>(v, q & 1 ? my2 : my, q & 1 ? my : my2, tw);
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) (q == 0 ? u1 : w2)[kk] = v[kk < 4 ? kk : kk + 4];
     }
@@ -366,6 +374,7 @@ __global__ void __launch_bounds__((AdjMix<LOGN2, NG>::THREADS))
   const bool live = pair < n1 / 2;
   const int ja = live ? 2 * pair : 0;  // a pair past the grid reads pair 0 (never stored)
   float2* const my = lds + p + h * C::AREA;
+  float2* const my2 = my + (C::TWO ? C::AREA : 0);
   const bool act = G == NB || t < NB;
   const int jt = act ? t : 0;
   gf2* const Wp = glob(f.Wp);
@@ -394,11 +403,13 @@ __global__ void __launch_bounds__((AdjMix<LOGN2, NG>::THREADS))
   // forward transform of zeta and its split by Hermitian symmetry: the row
   // transform of w1, (Xi(k) + conj(Xi(-k)))/2 -> A1, and of i kappa2 w2,
   // kappa2 (Xi(k) - conj(Xi(-k)))/2 -> A2 (outputs as in rowm_body)
-  auto forward = [&](float2(&y)[F::REGS], const MixTw<F, C::HELD_ROW>& wf, bool store, int row) {
-    mix_fft<F, false, false>(y, my, wf);
+  auto forward = [&](float2(&y)[F::REGS], const MixTw<F, C::HELD_ROW>& wf, bool store, int row, float2* a,
+                     float2* b) {
+    mix_fft_in<F, false, false, C::TWO>(y, a, b, wf);
+    float2* const ex = C::TWO ? b : a;  // free once every lane has passed the last exchange's barrier
     if (act) {
 #pragma unroll
-      for (int r = 8; r < 12; ++r) my[(t + NB * (r - 8)) * B] = y[r];
+      for (int r = 8; r < 12; ++r) ex[(t + NB * (r - 8)) * B] = y[r];
     }
     __syncthreads();
     if (store && act) {
@@ -406,7 +417,7 @@ __global__ void __launch_bounds__((AdjMix<LOGN2, NG>::THREADS))
       for (int r = 0; r < 4; ++r) {
         const int k = t + NB * r;
         const float2 xk = y[r];
-        const float2 xo = my[(NB * (4 - r) - t - (k == 0 ? 1 : 0)) * B];
+        const float2 xo = ex[(NB * (4 - r) - t - (k == 0 ? 1 : 0)) * B];
         const float2 xm = k == 0 ? xk : xo;
         const float hk = 0.5f * f.s2 * (float)k;
         st(glob(f.A1) + tiled(row, k, n1, ts), make_float2(0.5f * (xk.x + xm.x), 0.5f * (xk.y - xm.y)));
@@ -448,23 +459,25 @@ __global__ void __launch_bounds__((AdjMix<LOGN2, NG>::THREADS))
         }
       }
     __syncthreads();  // the first group's forward pass, which nobody reads, writes its area
-    forward(y, wf, live && h > 0, ja + h - 1);
+    forward(y, wf, live && h > 0, ja + h - 1, my, my2);
   } else {
     float2 v[I::REGS], z[2][I::REGS];
     load_z(z[0], ja);
     load_z(z[1], ja + 1);
     load_m(v);
     v[8] = jt > 0 ? v[8] : make_float2(0.f, 0.f);
-    mix_fft<I, true, true>(v, my, wi);
+    mix_fft_in<I, true, true, C::TWO>(v, my, my2, wi);
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       z[half][8] = jt > 0 ? z[half][8] : make_float2(0.f, 0.f);
-      mix_fft<I, true, true>(z[half], my, wi);
+      // the areas alternate over the transforms; a forward one's split takes the one its last exchange left
+      float2 *const a = half == 0 ? my : my2, *const b = half == 0 ? my2 : my;
+      mix_fft_in<I, true, true, C::TWO>(z[half], b, a, wi);
       float2 y[F::REGS];
 #pragma unroll
       for (int i = 0; i < NV; ++i) y[i] = ff::cscale(z[half][i], half == 0 ? v[i].x : v[i].y);
-      forward(y, MixTw<F, C::HELD_ROW>(ftab, t), live, ja + half);
-      __syncthreads();  // the next transform writes the exchange area
+      forward(y, MixTw<F, C::HELD_ROW>(ftab, t), live, ja + half, a, b);
+      if (!C::TWO) __syncthreads();  // the next transform writes the exchange area
     }
   }
 }
