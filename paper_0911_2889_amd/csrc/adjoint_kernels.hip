@@ -242,6 +242,8 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
   const size_t coll = (size_t)(live ? m : 0) * f.h1 + N1 / 4;
   const float kap2 = f.s2 * (float)m;
   const StepScalars sc = step_scalars(f, n, L, f.cols);
+  // 1024 threads of 128 registers: what a transform does not need is loaded after it
+  constexpr bool LATE = LOGN1 == 14;
   const int jt = act ? t : 0;
   auto k1_of = [&](int kk) { return kk < 4 ? jt + NB * kk : jt - NB * (8 - kk); };
   gf2* const lin = glob(const_cast<float2*>(lam_in));
@@ -253,21 +255,26 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
     gf2* const one = NG == 1 || h == 0 ? lin : glob(const_cast<float2*>(state));
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) lm[kk] = ld(one + coll + k1_of(kk));
+    auto load_state = [&] {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      sv[kk] = NG == 1 ? ld(glob(const_cast<float2*>(state)) + coll + k1_of(kk)) : lm[kk];
+      for (int kk = 0; kk < 8; ++kk)
+        sv[kk] = NG == 1 ? ld(glob(const_cast<float2*>(state)) + coll + k1_of(kk)) : lm[kk];
+    };
+    if (!LATE) load_state();
     const MixTw<I, C::HELD> tw(f.twma, t);
 #pragma unroll
     for (int q = 0; q < (NG == 1 ? 3 : 1); ++q) {
       const int job = NG == 1 ? q : h;
+      if (LATE && q == 1) load_state();
       const float kp = job == 1 ? -kap2 : kap2;
       float2 v[I::REGS];
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         const int k1 = k1_of(kk);
         const float kap1 = f.s1 * (float)k1;
-        const float2 mu = ff::cscale(lm[kk], efactor(f, sc, k1, kap2)), z = slope(kap1, kp, sv[kk]);
-        v[kk < 4 ? kk : kk + 4] = job == 0 ? mu : z;
+        const int i = kk < 4 ? kk : kk + 4;
+        if (NG > 1 || q == 0) v[i] = ff::cscale(lm[kk], efactor(f, sc, k1, kap2));
+        if (NG > 1 || q > 0) v[i] = NG > 1 && job == 0 ? v[i] : slope(kap1, kp, sv[kk]);
       }
       mix_fft_in<I, true, true, C::TWO>(v, q & 1 ? my2 : my, q & 1 ? my : my2, tw);
       if (live) {
@@ -293,7 +300,8 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
     // forward column transforms of the row transforms of w1 (job 0) and i kappa2 w2 (job 1)
     float2 lam[8], u1[8], w2[8];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) lam[kk] = ld(lin + coll + k1_of(kk));
+    for (int kk = 0; kk < 8; ++kk)
+      if (!LATE) lam[kk] = ld(lin + coll + k1_of(kk));
     const MixTw<F, C::HELD> tw(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, t);
 #pragma unroll
     for (int q = 0; q < (NG == 1 ? 2 : 1); ++q) {
@@ -319,6 +327,10 @@ __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))
       __syncthreads();
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) w2[kk] = lds[c + C::AREA + (jt + NB * kk) * T];
+    }
+    if (LATE) {
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) lam[kk] = ld(lin + coll + k1_of(kk));
     }
     float2 out[8];
 #pragma unroll
