@@ -33,6 +33,7 @@
 #include "flame_kernels.hpp"
 #include "kernel_common.hpp"
 #include "mixed_bodies.hpp"
+#include "transform_shapes.hpp"
 
 namespace flame {
 
@@ -183,34 +184,6 @@ __global__ void __launch_bounds__(ColCfg<LOGN1>::THREADS) __attribute__((amdgpu_
     }
   }
 }
-
-// The product-grid kernels hold NG transforms side by side, on NG groups of G
-// lanes and in NG exchange areas (NG = 3: the three inverse transforms of a
-// column or row pair; NG = 2: the two forward ones of a column), or run them
-// one after another on N/16 lanes (NG = 1). As for the step's kernels
-// (split_pays), side by side is for launches that leave most of the chip idle.
-// At 8192 points one after another means 768 lanes and two exchange areas, for
-// the reasons at kFewLanes13 and mix_two_areas; here for many transforms too,
-// since three transforms' data leave no registers for a second workgroup
-// (adjoint steps: 16x8192 33.1 -> 30.3 us, 8192x64 31.8 -> 29.0, 8192x8192 682
-// -> 641; 512 lanes with two areas 31.6, 30.7 and 659, 768 with one 32.1, 31.1
-// and 675).
-template <int LOGN, int NG>
-struct AdjMix {
-  static constexpr int N = 1 << LOGN, NB = N / 16;
-  static constexpr int G = NG > 1 ? split_lanes(LOGN) : (LOGN == 13 ? kFewLanes13 : NB);
-  static constexpr int T = NG > 1 ? (G >= 64 ? 1 : 64 / G) : (G >= 256 ? 1 : 256 / G);
-  // twiddles in registers (MixTw); one after another, a row kernel holds both
-  // rows' inputs and m beside its transform, and at 2048 points, and from 8192
-  // on, has no registers for them (4096 points: 64x4096 28.1 -> 27.6 us)
-  static constexpr bool HELD = LOGN < 14, HELD_ROW = NG > 1 || LOGN < 11 || LOGN == 12;
-  using F = ff::Mix<typename ff::MixPlan<LOGN>::F, G, T>;
-  using I = ff::Mix<typename ff::MixPlan<LOGN>::I, G, T>;
-  static constexpr int L = F::N, AREA = F::LDS > I::LDS ? F::LDS : I::LDS;
-  static constexpr int THREADS = NG * G * T;
-  static constexpr bool TWO = NG == 1 && LOGN == 13;  // two exchange areas (mix_two_areas)
-  static constexpr int LDS_BYTES = 8 * NG * (TWO ? 2 : 1) * AREA;
-};
 
 template <int LOGN1, int MODE, int NG>
 __global__ void __launch_bounds__((AdjMix<LOGN1, NG>::THREADS))

@@ -9,31 +9,11 @@
 #include "kernel_common.hpp"
 #include "mixed_bodies.hpp"
 #include "step_bodies.hpp"
+#include "transform_shapes.hpp"
 
 namespace flame {
 
 namespace {
-
-// The power-of-two plans' inverse transforms (ff::make_pass_plan, 16 points
-// per thread: radix 16, the remainder last) as ff::Mix passes, so that they
-// run on any number of lanes with the tables of those plans.
-template <int LOGN>
-struct PowPlan;
-#define FLAME_POW_PLAN(L, ...)     \
-  template <>                      \
-  struct PowPlan<L> {              \
-    using I = ff::Radices<__VA_ARGS__>; \
-  }
-FLAME_POW_PLAN(4, 16);
-FLAME_POW_PLAN(5, 16, 2);
-FLAME_POW_PLAN(6, 16, 4);
-FLAME_POW_PLAN(7, 16, 8);
-FLAME_POW_PLAN(8, 16, 16);
-FLAME_POW_PLAN(9, 16, 16, 2);
-FLAME_POW_PLAN(10, 16, 16, 4);
-FLAME_POW_PLAN(11, 16, 16, 8);
-#undef FLAME_POW_PLAN
-constexpr int kMaxLogSide = 11;  // longer transforms run one after another (split_pays)
 
 // Whether a row pair's two transforms of the averages run side by side: as the
 // step's (split_pays), but short rows less long, because the spectral sums
@@ -45,17 +25,6 @@ constexpr bool diag_split_pays(int logn, long long pairs) {
   const long long waves = pairs * ((1 << logn) / 16) / 64;
   return split_pays(logn, pairs, false) && waves <= (logn <= 9 ? 256 : logn == 10 ? 512 : 1024);
 }
-
-// Two inverse transforms side by side on two groups of G lanes (ColSplit, RowSplit).
-template <int LOGN>
-struct PhysSplit {
-  static constexpr int N = 1 << LOGN, NB = N / 16;
-  static constexpr int G = LOGN <= 10 ? 2 * NB : NB;
-  static constexpr int T = 2 * G >= kSplitThreads ? 1 : kSplitThreads / (2 * G);
-  using I = ff::Mix<typename PowPlan<LOGN>::I, G, T>;
-  static constexpr int THREADS = 2 * G * T;
-  static constexpr int LDS_BYTES = 8 * (2 * I::LDS > THREADS ? 2 * I::LDS : THREADS);  // and the sums of a workgroup
-};
 
 // Partial sums that other workgroups read in the same launch: stores and loads
 // at agent scope, which do not stay in one XCD's L2.

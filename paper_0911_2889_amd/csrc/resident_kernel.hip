@@ -27,63 +27,11 @@
 #include "flame_kernels.hpp"
 #include "kernel_common.hpp"
 #include "mixed_bodies.hpp"
+#include "transform_shapes.hpp"
 
 namespace flame {
 
 namespace {
-
-constexpr int imin(int a, int b) { return a < b ? a : b; }
-constexpr int imax(int a, int b) { return a > b ? a : b; }
-
-template <int LOGN, bool PRODUCT>
-struct ResAxis {
-  using Plan = typename std::conditional<PRODUCT, ff::MixPlan<PRODUCT ? LOGN : 6>, ff::FullPlan<PRODUCT ? 4 : LOGN>>::type;
-  static constexpr int N = 1 << LOGN, NB = N / 16;
-  static constexpr int RS = PRODUCT ? 12 : 16;  // radix at the spectral end
-  static constexpr int L = RS * NB;
-  // register of kept mode kk = 0..7 (k = j + NB kk >= 0 for kk < 4, else j - NB (8 - kk))
-  static constexpr int reg(int kk) { return kk < 4 ? kk : kk + RS - 8; }
-  static constexpr int min_radix() {
-    int r = 16;
-    for (int x : Plan::I::radix) r = imin(r, x);
-    return r;
-  }
-  // lanes per job: at least NB, doubled while a pass has more butterflies than
-  // that and `jobs` jobs still fit `threads`
-  static constexpr int lanes(int jobs, int threads) {
-    int g = NB;
-    while (jobs * g * 2 <= threads && g < L / min_radix()) g *= 2;
-    return g;
-  }
-};
-
-constexpr int kResMaxThreads = 1024;
-// Steps whose scalars (logarithm, divisions in double) are formed at once, a
-// step per lane, and read from LDS step by step; one more for Heun's corrector.
-constexpr int kResChunk = 64, kResChunk1 = kResChunk + 1;
-constexpr int kResMaxLds = 160 * 1024;
-
-template <int L1, int L2>
-struct Res {
-  using A1 = ResAxis<L1, (L1 >= kMinLogProduct)>;
-  using A2 = ResAxis<L2, (L2 >= kMinLogRowProduct)>;
-  static constexpr int N1 = A1::N, N2 = A2::N, M = N2 / 4, R = A1::L, NP = R / 2;
-  static constexpr int GCI = A1::lanes(2 * M, kResMaxThreads), GCF = A1::lanes(M, kResMaxThreads);
-  static constexpr int GRI = A2::lanes(R, kResMaxThreads), GRF = A2::lanes(NP, kResMaxThreads);
-  using CI = ff::Mix<typename A1::Plan::I, GCI, 2 * M>;
-  using CF = ff::Mix<typename A1::Plan::F, GCF, M>;
-  using RI = ff::Mix<typename A2::Plan::I, GRI, R>;
-  using RF = ff::Mix<typename A2::Plan::F, GRF, NP>;
-  static constexpr int S = R + 1;  // stride of a column of W and Q
-  // area A: the exchanges; area B: W, then |z|^2, then Q and the split's
-  // exchange, then the updated modes
-  static constexpr int AREA_A = imax(imax(CI::LDS, CF::LDS), imax(RI::LDS, RF::LDS));
-  static constexpr int AREA_B = imax(imax(2 * M * S, A2::L * NP), imax(M * S + M * NP, 8 * A1::NB * M));
-  static constexpr int LDS_BYTES = 8 * (AREA_A + AREA_B) + kResChunk1 * (int)sizeof(StepScalars);
-  static constexpr int JOBS = imax(imax(2 * M * GCI, M * GCF), imax(R * GRI, NP * GRF));
-  static constexpr int THREADS = (JOBS + 63) / 64 * 64;
-  static constexpr bool OK = THREADS <= kResMaxThreads && LDS_BYTES <= kResMaxLds;
-};
 
 // Resident: every grid of N1 N2 <= 2^kResMaxLogs but three, which need 162 to 189 KB.
 template <int L1, int L2>
