@@ -518,8 +518,8 @@ __host__ __device__ __forceinline__ float2 twmul(float2 x, float2 w) {
 // and on the device agree.
 template <int R, class PUT>
 __host__ __device__ __forceinline__ void tw_butterfly(int ns, int k, const PUT& put) {
-  const double ang = 2.0 * M_PI * (double)k / ((double)ns * R);
-  const double c1 = cos(ang), s1 = sin(ang);
+  double c1, s1;
+  sincos(2.0 * M_PI * (double)k / ((double)ns * R), &s1, &c1);
   double c = 1.0, s = 0.0;
 #pragma unroll
   for (int r = 1; r < R; ++r) {
