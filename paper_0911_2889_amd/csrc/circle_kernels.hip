@@ -20,9 +20,9 @@
 // What bounds the step is the vector ALU. From N = 64 on the squares are
 // formed on 3 N/4 points, on which a product of two spectra |k| <= K = N/4 - 1
 // has no alias in |k| <= K either (ff::MixPlan), in shorter circles and in the
-// averages on the N points. 2048 circles of 4096 points, 50 steps: 466 us for
-// 498 on N points; 511 of 16384, 10 steps: 488 for 669; 301 of 64, 20 steps:
-// 43 for 55.
+// averages on the N points. 2048 circles of 4096 points, 50 steps: 511 us for
+// 556 on N points; 511 of 16384, 10 steps: 322 for 557; 301 of 64, 20 steps:
+// 47 for 58.
 
 #include <hip/hip_runtime.h>
 

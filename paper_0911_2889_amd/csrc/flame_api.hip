@@ -1144,8 +1144,8 @@ namespace {
 // (null if they can).
 const char* ens_reason(const Group& gr) {
   if (!flame::ensemble_supports(gr.logn1, gr.logn2)) return "the persistent kernel has bodies for n1 in [128, 1024], n2 in [128, 2048]";
-  if (!gr.product || gr.col_pts != 12) return "the persistent kernel steps the product grid with 12 column points per thread";
-  if (gr.row_pts != 16) return "the persistent kernel's row transforms use 16 points per thread";
+  if (!gr.product || gr.col_pts != 12) return "the persistent kernel runs the product grid's bodies for many transforms, at col_pts = 12";
+  if (gr.row_pts != 16) return "the persistent kernel takes row_pts = 16 (its rows are those of 12 points)";
   if (gr.nt != 0) return "the persistent kernel uses plain stores";
   if (gr.integrator != 0 || gr.forced) return "the persistent kernel runs unforced integrating-factor Euler";
   return nullptr;

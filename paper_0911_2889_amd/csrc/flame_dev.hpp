@@ -133,15 +133,14 @@ constexpr int kMaxLogFull = 6;
 // (mixed_bodies.hpp, "few transforms"): `transforms` columns or row pairs of
 // length 2^logn in the launch, which the other bodies run on N/16 lanes each.
 // Measured: up to 2048 points they win while those lanes make at most half a
-// wave per SIMD of the chip for the columns (512 waves: 1024x2048 10.3 against
-// 11.7 us; at 1024 waves, 1024x4096, 16.0 against 14.9) and one wave per SIMD
-// for the rows (768 waves: 8.8 against 9.3 us). At 4096 points a workgroup of
+// wave per SIMD of the chip for the columns (512 waves: 1024x2048 10.7 against
+// 11.5 us; at 1024 waves, 1024x4096, 15.2 against 14.1) and one wave per SIMD
+// for the rows (768 waves: 9.0 against 9.4 us). At 4096 points a workgroup of
 // either kind is one transform and fills its compute unit's issue slots, and
 // side by side is slower (9.5 against 8.5 us for 96 row pairs). At 8192 points
 // the variant is 768 lanes instead of 256: faster while every compute unit
-// has at most one transform (128x8192 12.9 against 16.5 us), slower where two
-// workgroups of 256 threads can share one (8192x8192: 196, with 512 lanes,
-// against 161 us).
+// has at most one transform (128x8192 12.8 against 16.9 us), slower where two
+// workgroups of 256 threads can share one (8192x8192: 198 against 162 us).
 constexpr bool split_pays(int logn, long long transforms, bool columns) {
   const long long waves = transforms * ((1 << logn) / 16) / 64;
   return logn <= 11 ? waves <= (columns ? 512 : 1024) : logn == 13 && transforms <= 256;

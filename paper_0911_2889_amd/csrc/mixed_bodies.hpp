@@ -396,8 +396,8 @@ __device__ __forceinline__ void rowm_body(const FlameDev& f, int group, int tid)
 // transforms, so that more compute units take part. Every transform has the
 // radices and the arithmetic of the bodies above, so the results are the same
 // bit for bit. Measured against those bodies (one flame, us per row and column
-// kernel): 256x512 7.4 + 7.5 -> 5.0 + 5.4, 512x1024 7.9 + 9.2 -> 5.2 + 5.2,
-// 1024x2048 9.3 + 11.7 -> 8.8 + 10.3.
+// kernel): 256x512 7.7 + 7.8 -> 5.1 + 5.4, 512x1024 7.9 + 8.9 -> 5.9 + 5.8,
+// 1024x2048 9.4 + 11.5 -> 9.0 + 10.7.
 constexpr int kSplitThreads = 128;  // per workgroup; 64 and 256 were 0-2 % and 5-15 % slower
 constexpr int split_lanes(int logn) { return (1 << logn) / (logn <= 10 ? 8 : 16); }
 

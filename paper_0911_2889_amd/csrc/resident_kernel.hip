@@ -4,7 +4,10 @@
 //
 // What bounds a small flame's step otherwise is not work but two launches and
 // their chains: at 64x128 each of the two kernels took 5 to 6 us for some 2 us
-// of one compute unit's arithmetic. Here a step is the four phases below with
+// of one compute unit's arithmetic (12.3 us a step, here 6.4). Many flames take
+// their turns at the compute units and still gain where the last turn has one
+// flame: 257 of 64x128 12.6 us for 18.4, of 128x128 17.7 for 25.7, of 32x256, the
+// closest, 16.6 for 17.1. Here a step is the four phases below with
 // nine to seventeen workgroup barriers between them.
 //
 //  column inverse: 2 M jobs (column m; Wp and Wm), lanes as the split bodies
