@@ -216,8 +216,9 @@ class FlameEnsemble:
             self._forcing[flame] = buf
 
     def set_product_grid(self, n1, n2, enable):
-        """Form the quadratic term on 3*n1/4 theta rows (True) or on n1 rows (False)
-        for the flames of grid n1 x n2; the results agree to rounding."""
+        """Form the quadratic term of the flames of grid n1 x n2 on the product grid of
+        3*n1/4 theta rows and 3*n2/4 phi points (True) or on the n1 x n2 grid of the
+        paper's augmented array (False); the results agree to rounding."""
         native.check(self.lib.flame_set_product_grid(self.plan, int(n1), int(n2), int(bool(enable))))
 
     def product_grid(self, n1, n2):
