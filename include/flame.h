@@ -289,7 +289,8 @@ int flame_get_product_grid(flame_plan plan, int32_t n1, int32_t n2, int32_t* ena
  * and lengthen the one that reads next, which then misses in the caches more
  * often; which way the step gains depends on the grid and on what runs beside
  * it, so flame_autotune measures both. The state, the diagnostics and the
- * adjoint use plain stores. Errors: FLAME_ERR_INVALID_ARG if no flame of the
+ * adjoint use plain stores, and so do the step kernels for few transforms
+ * (flame_set_points_per_thread), whatever is set. Errors: FLAME_ERR_INVALID_ARG if no flame of the
  * plan has that grid (or a null output pointer). Setting discards the step
  * graph (it is rebuilt at the next graph step). */
 int flame_set_streaming_stores(flame_plan plan, int32_t n1, int32_t n2, int32_t enable);

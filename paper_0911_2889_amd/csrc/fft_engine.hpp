@@ -229,13 +229,6 @@ __host__ __device__ __forceinline__ float2 mul_q(float2 a) {
   return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
 }
 
-// multiply by exp(s * i * theta) with (cos, sin) given for the forward sign convention
-template <bool INV>
-__host__ __device__ __forceinline__ float2 mul_root(float2 a, float c, float s) {
-  // forward root: c - i s ; inverse: c + i s
-  return INV ? make_float2(a.x * c - a.y * s, a.x * s + a.y * c) : make_float2(a.x * c + a.y * s, a.y * c - a.x * s);
-}
-
 // ------------------------------------------------------- small DFTs in registers
 // X[m] = sum_r x[r] w^(r m), w = exp(-2 pi i / R) (forward) or exp(+2 pi i / R) (inverse)
 
@@ -775,7 +768,5 @@ inline void build_twiddles6(int logp, float2* out, int pts = kPts) {
       out[p.tw_size + (r - 1) * n6 + k] = make_float2((float)std::cos(ang), (float)std::sin(ang));
     }
 }
-
-inline int twiddles6_size(int logp, int pts = kPts) { return make_pass_plan(logp, pts).tw_size + 5 * (1 << logp); }
 
 }  // namespace ff

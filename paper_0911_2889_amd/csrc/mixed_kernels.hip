@@ -83,7 +83,7 @@ KernelLaunch rowm_dispatch(int logn2, bool nt) {
 
 template <int L, int VAR>
 KernelLaunch cols_info(int mode) {
-  if constexpr (L > 12) {  // side by side would take 1024 threads of 128 registers: one after the other on all lanes
+  if constexpr (L > 12) {  // side by side would take 1024 threads of 128 registers: one after the other (kFewLanes13)
     using C = ColMix<L, kFewLanes13>;
     const void* fn = mode == COL_FIRST ? reinterpret_cast<const void*>(&colm_kernel<L, COL_FIRST, VAR_EULER, kFewLanes13>)
                                        : reinterpret_cast<const void*>(&colm_kernel<L, COL_STEP, VAR, kFewLanes13>);
