@@ -133,8 +133,8 @@ constexpr int kMaxLogFull = 6;
 // (mixed_bodies.hpp, "few transforms"): `transforms` columns or row pairs of
 // length 2^logn in the launch, which the other bodies run on N/16 lanes each.
 // Measured: up to 2048 points they win while those lanes make at most half a
-// wave per SIMD of the chip for the columns (512 waves: 1024x2048 10.7 against
-// 11.5 us; at 1024 waves, 1024x4096, 15.2 against 14.1) and one wave per SIMD
+// wave per SIMD of the chip for the columns (512 waves: 1024x2048 9.4 against
+// 11.6 us; at 1024 waves, 1024x4096, 15.2 against 14.9) and one wave per SIMD
 // for the rows (768 waves: 9.0 against 9.4 us). At 4096 points a workgroup of
 // either kind is one transform and fills its compute unit's issue slots, and
 // side by side is slower (9.5 against 8.5 us for 96 row pairs). At 8192 points

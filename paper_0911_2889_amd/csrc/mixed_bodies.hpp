@@ -23,9 +23,10 @@ constexpr int mix_lanes(int logn) { return (1 << logn) / (logn == 13 ? 32 : 16);
 // Lanes per transform of 8192 points where there are few: one butterfly each
 // in the radix-8 passes (the radix-12 pass leaves 4 of the 12 waves idle). A
 // compute unit has one transform at a time, of 768 lanes rather than 512: 8192x16
-// column kernel 16.0 -> 15.6 us, 16x8192 row kernel 13.3 -> 12.6. (Plans of
-// 16, 16, 4 and 6 points took 15.1 and 12.6. Both inverse transforms of a
-// column pass by pass, in the same waits: 16.0.)
+// column kernel 16.0 -> 15.6 us (15.2 with its inverse's twiddles loaded late),
+// 16x8192 row kernel 13.3 -> 12.6. (Plans of 16, 16, 4 and 6 points took 15.0
+// and 12.6. Both inverse transforms of a column pass by pass, in the same waits:
+// 16.0.)
 constexpr int kFewLanes13 = 768;
 
 // Whether a transform's exchanges alternate between two areas, so that each
@@ -219,9 +220,13 @@ __device__ __forceinline__ void colm_body(const FlameDev& f, long long n, const 
       frc[kk] = FORCED ? forcing_at(f, ms, k1_of(kk)) : make_float2(0.f, 0.f);
       prd[kk] = VAR == VAR_HEUN_C ? ld(Pl + k1_of(kk)) : make_float2(0.f, 0.f);
     }
+    const MixTw<F, mix_held_col(LOGN1, G_)> wf(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, t);
+    mix_fft_in<F, false, false, C::TWO>(v, my, my2, wf);
+    // The inverse's twiddles are loaded here, not beside the forward's: a
+    // workgroup's loads of both tables before its first transform are as long as
+    // those of its column (2048x4096 column kernel 17.4 -> 17.0 us, 4096x2048
+    // 18.4 -> 17.9, 8192x16 15.6 -> 15.2).
     wi.init(f.twma, t);
-    mix_fft_in<F, false, false, C::TWO>(
-        v, my, my2, MixTw<F, mix_held_col(LOGN1, G_)>(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, t));
     const StepScalars sc = step_scalars(f, n, L, f.cols);
     const float ac = VAR == VAR_HEUN_C ? step_scalars(f, n + 1, L, f.cols).a : 0.f;  // the corrector's dt c_{n+1} / P
     const float kap2c = f.s2 * (float)m;
@@ -396,8 +401,8 @@ __device__ __forceinline__ void rowm_body(const FlameDev& f, int group, int tid)
 // transforms, so that more compute units take part. Every transform has the
 // radices and the arithmetic of the bodies above, so the results are the same
 // bit for bit. Measured against those bodies (one flame, us per row and column
-// kernel): 256x512 7.7 + 7.8 -> 5.1 + 5.4, 512x1024 7.9 + 8.9 -> 5.9 + 5.8,
-// 1024x2048 9.4 + 11.5 -> 9.0 + 10.7.
+// kernel): 256x512 7.5 + 7.5 -> 5.0 + 5.4, 512x1024 8.0 + 8.9 -> 5.8 + 5.4,
+// 1024x2048 9.4 + 11.6 -> 9.0 + 9.4.
 constexpr int kSplitThreads = 128;  // per workgroup; 64 and 256 were 0-2 % and 5-15 % slower
 constexpr int split_lanes(int logn) { return (1 << logn) / (logn <= 10 ? 8 : 16); }
 
@@ -469,8 +474,8 @@ __device__ __forceinline__ void cols_body(const FlameDev& f, long long n, const 
       frc[kk] = FORCED ? forcing_at(f, ms, k1_of(ju, kk)) : make_float2(0.f, 0.f);
       prd[kk] = VAR == VAR_HEUN_C ? ld(Pl + k1_of(ju, kk)) : make_float2(0.f, 0.f);
     }
-    wi.init(f.twma, t);
     mix_fft<F, false, false>(v, my, MixTw<F, true>(f.twma + ff::MixTables<ff::MixPlan<LOGN1>>::F_OFF, u));
+    wi.init(f.twma, t);  // not before the forward transform (colm_body): 1024x2048 11.1 -> 9.8 us
     const StepScalars sc = step_scalars(f, n, L, f.cols);
     const float ac = VAR == VAR_HEUN_C ? step_scalars(f, n + 1, L, f.cols).a : 0.f;
     const float kap2c = f.s2 * (float)m;
